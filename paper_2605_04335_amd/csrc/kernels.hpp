@@ -2030,10 +2030,13 @@ __device__ __forceinline__ void tail_stage_coef(const Tail &T, int l, unsigned c
 }
 
 template <class Tc, class TB>
-__global__ void __launch_bounds__(TAIL_T) k_tail(Tail T, const double *mean0)
+__global__ void __launch_bounds__(TAIL_T) k_tail(Tail T, const double *part, int npart)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double mus[8];
+    // partial sums of the first tail level's mean (up to one per thread in the usual hierarchies)
+    double psum = 0.0;
+    for (int q = threadIdx.x; q < npart; q += TAIL_T) psum += part[q];
     {
         // each level is staged by its own 128 threads (at most 8 levels), so
         // the levels' global loads are in flight together: the mask in
@@ -2068,7 +2071,10 @@ __global__ void __launch_bounds__(TAIL_T) k_tail(Tail T, const double *mean0)
             }
         }
     }
-    if (threadIdx.x == 0) mus[0] = mean0[0];
+    {
+        const double tot = tail_sum(psum);
+        if (threadIdx.x == 0) mus[0] = T.t[0].volA > 0.0 ? tot / T.t[0].volA : 0.0;
+    }
     __syncthreads();
     for (int l = 0; l < T.n; ++l) {
         const Lv L = tail_lv(T, l, smem);

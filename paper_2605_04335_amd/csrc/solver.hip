@@ -15,6 +15,7 @@
 // ABI takes and returns natural x-fastest arrays, converted at the boundary.
 
 #include "kernels.hpp"
+#include "fused.hpp"
 #include "setup.hpp"
 
 #include <algorithm>
@@ -37,6 +38,11 @@ constexpr int W4MAXB = 131072;
 constexpr int PSTRIDE = W4MAXB + 2048;  // partial slots per reduction: stencil or walk blocks, then sparse blocks
 constexpr int XB = 1024;               // cap on blocks of the sparse row kernels
 
+// Coarse levels up to this size smooth on bricks (fused.hpp).  At 64^3 a phase
+// takes 19 us against 23 to 29 us of one-sweep launches; at 128^3 the bricks'
+// eightfold recomputation alone is eight times that work, against 34 to 37 us.
+constexpr long long BRICK_MAX_CELLS = 300000;
+
 inline int sparse_blocks(long long n) { return (int)std::max<long long>(1, std::min<long long>(XB, (n + TPB - 1) / TPB)); }
 
 struct Level {
@@ -56,6 +62,10 @@ struct Level {
     DBuf<double> x64, b64;
     DBuf<float> x32;
     DBuf<bf16> b16;
+    bool brick = false;              // smoothing phases on bricks (one launch each)
+    Brick br;
+    DBuf<double> k64;                // brick levels: black iterate between the phases
+    DBuf<float> k32;
     Lv lv;
     PMap pm;
     std::vector<double> hc[3], hw[3];
@@ -256,6 +266,10 @@ inline void fin(poisson_ctx &c, int n, int op, int dst, double aux, hipStream_t 
     IBM_LAUNCH_CHECK();
 }
 
+// partial sums of level l's RHS mean: alternate levels use alternate places,
+// since a brick launch reads its level's while writing the next one's
+inline double *mean_part(poisson_ctx &c, int l) { return c.part.p + (size_t)PSTRIDE * (2 + (l & 1)); }
+
 // y = A x (or y = b - A x) on level 0, with dots; returns the partial count
 template <class T>
 int launch_apply(poisson_ctx &c, int mode, bool res, int nd, const T *x, T *y, const T *b, const double *sink,
@@ -291,6 +305,7 @@ struct Store<double> {
     typedef double Tc;
     typedef double TB;
     static Tc *x(Level &L) { return L.x64.p; }
+    static Tc *k(Level &L) { return L.k64.p; }
     static TB *b(Level &L) { return L.b64.p; }
 };
 template <>
@@ -298,6 +313,7 @@ struct Store<float> {
     typedef float Tc;
     typedef bf16 TB;
     static Tc *x(Level &L) { return L.x32.p; }
+    static Tc *k(Level &L) { return L.k32.p; }
     static TB *b(Level &L) { return L.b16.p; }
 };
 
@@ -370,6 +386,76 @@ void coarse_smooth(Level &L, int steps, bool from_zero, const double *mean, hipS
     IBM_LAUNCH_CHECK();
 }
 
+template <class Tc, class TB>
+BrickArgs<Tc, TB> brick_args(poisson_ctx &c, int l, int steps)
+{
+    Level &L = c.lv[l];
+    BrickArgs<Tc, TB> a{};
+    a.b = Store<Tc>::b(L);
+    a.vol = L.volA;
+    a.mean = c.sc.p + S_MEAN0 + l;
+    a.steps = steps;
+    return a;
+}
+
+// first phase of brick level l: nu1 steps from zero (the level's mean from
+// the partial sums of the launch before) and the restriction into level l+1;
+// returns the count of partial sums of that level's mean
+template <class Tc, class TB>
+int brick_down(poisson_ctx &c, int l, int npart, hipStream_t s)
+{
+    Level &L = c.lv[l], &C = c.lv[l + 1];
+    auto a = brick_args<Tc, TB>(c, l, c.opts.nu1);
+    a.part = mean_part(c, l);
+    a.npart = npart;
+    a.xb = Store<Tc>::k(L);
+    a.bc = Store<Tc>::b(C);
+    a.pout = mean_part(c, l + 1);
+    k_brick<Tc, TB, BR_ZERO><<<L.br.nb, BR_T, 0, s>>>(L.lv, L.br, C.lv, L.pm, a);
+    IBM_LAUNCH_CHECK();
+    return L.br.nb;
+}
+
+// second phase: prolongation from level l+1 and nu2 steps
+template <class Tc, class TB>
+void brick_up(poisson_ctx &c, int l, hipStream_t s)
+{
+    Level &L = c.lv[l], &C = c.lv[l + 1];
+    auto a = brick_args<Tc, TB>(c, l, c.opts.nu2);
+    a.xin = Store<Tc>::k(L);
+    a.xr = Store<Tc>::x(L);
+    a.xb = a.xr + L.Nh;
+    a.xc = Store<Tc>::x(C);
+    a.renorm = C.n_inactive > 0;
+    k_brick<Tc, TB, BR_PROLONG><<<L.br.nb, BR_T, 0, s>>>(L.lv, L.br, C.lv, L.pm, a);
+    IBM_LAUNCH_CHECK();
+}
+
+// coarsest level on bricks: all its sweeps, two per launch, the black iterate
+// alternating between two buffers so that the last launch writes the level's own
+template <class Tc, class TB>
+void brick_coarsest(poisson_ctx &c, int l, int npart, hipStream_t s)
+{
+    Level &L = c.lv[l];
+    Tc *x = Store<Tc>::x(L), *buf[2] = {x + L.Nh, Store<Tc>::k(L)};
+    const int n = (c.opts.coarse_sweeps + 1) / 2;
+    for (int q = 0; q < n; ++q) {
+        const int left = n - 1 - q;
+        auto a = brick_args<Tc, TB>(c, l, q == n - 1 ? c.opts.coarse_sweeps - 2 * q : 2);
+        a.xb = buf[left & 1];
+        a.xr = left ? nullptr : x;
+        if (q == 0) {
+            a.part = mean_part(c, l);
+            a.npart = npart;
+            k_brick<Tc, TB, BR_ZERO><<<L.br.nb, BR_T, 0, s>>>(L.lv, L.br, L.lv, L.pm, a);
+        } else {
+            a.xin = buf[(left + 1) & 1];
+            k_brick<Tc, TB, BR_PLAIN><<<L.br.nb, BR_T, 0, s>>>(L.lv, L.br, L.lv, L.pm, a);
+        }
+    }
+    IBM_LAUNCH_CHECK();
+}
+
 // x = V-cycle(b) on the unpinned operator with the sink at the pin; x unshifted
 template <class T>
 void vcycle(poisson_ctx &c, const T *b, T *x, const double *sink, hipStream_t s)
@@ -387,13 +473,19 @@ void vcycle(poisson_ctx &c, const T *b, T *x, const double *sink, hipStream_t s)
         if (nsp) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, s>>>(c.lv[0].lv, c.sp, x, b, r0);
         Level &L1 = c.lv[1];
         k0_restrict_res<T, TB><<<L1.geon.nb, TPB, 0, s>>>(c.lv[0].lv, L1.lv, L1.geon, c.pin, x, b, sink, r0,
-                                                         Store<T>::b(L1), c.part.p);
+                                                         Store<T>::b(L1), mean_part(c, 1));
         IBM_LAUNCH_CHECK();
-        fin(c, L1.geon.nb, FIN_MEAN, S_MEAN0 + 1, L1.volA, s);
+        int npart = L1.geon.nb;  // partial sums of the next level's mean
         const int lt = std::is_same<T, double>::value ? c.tail0d : c.tail0;
         for (int l = 1; l < lt; ++l) {
             Level &L = c.lv[l];
+            if (L.brick) {
+                if (l == nl - 1) brick_coarsest<Tc, TB>(c, l, npart, s);
+                else npart = brick_down<Tc, TB>(c, l, npart, s);
+                continue;
+            }
             const double *mean = c.sc.p + S_MEAN0 + l;
+            k_fin<<<1, 1024, 0, s>>>(mean_part(c, l), PSTRIDE, npart, FIN_MEAN, S_MEAN0 + l, L.volA, c.sc.p);
             if (l == nl - 1) {
                 coarse_smooth<Tc, TB>(L, o.coarse_sweeps, true, mean, s);
                 break;
@@ -402,9 +494,9 @@ void vcycle(poisson_ctx &c, const T *b, T *x, const double *sink, hipStream_t s)
             Level &C = c.lv[l + 1];
             k_restrict<false, Tc, TB, TB><<<C.geon.nb, TPB, 0, s>>>(L.lv, C.lv, C.geon, -1, Store<T>::x(L),
                                                                    Store<T>::b(L), mean, (const Tc *)nullptr,
-                                                                   Store<T>::b(C), c.part.p);
+                                                                   Store<T>::b(C), mean_part(c, l + 1));
             IBM_LAUNCH_CHECK();
-            fin(c, C.geon.nb, FIN_MEAN, S_MEAN0 + l + 1, C.volA, s);
+            npart = C.geon.nb;
         }
         if (lt < nl) {
             Tail tl;
@@ -427,12 +519,16 @@ void vcycle(poisson_ctx &c, const T *b, T *x, const double *sink, hipStream_t s)
                 const Level &L = c.lv[lt + q];
                 off += tail_coef_bytes(L.n[0], L.n[1], L.n[2]);
             }
-            k_tail<Tc, TB><<<1, TAIL_T, off, s>>>(tl, c.sc.p + S_MEAN0 + lt);
+            k_tail<Tc, TB><<<1, TAIL_T, off, s>>>(tl, mean_part(c, lt), npart);
             IBM_LAUNCH_CHECK();
         }
         for (int l = std::min(lt, nl - 1) - 1; l >= 1; --l) {
             Level &L = c.lv[l];
             Level &C = c.lv[l + 1];
+            if (L.brick) {
+                brick_up<Tc, TB>(c, l, s);
+                continue;
+            }
             launch_prolong<false>(L, C, o.nu2 > 0, Store<T>::x(C), Store<T>::x(L), s);
             coarse_smooth<Tc, TB>(L, o.nu2, false, c.sc.p + S_MEAN0 + l, s);
         }
@@ -701,6 +797,7 @@ size_t estimate_bytes(int nx, int ny, int nz, long long nrows, int precision)
         Nc /= 8;
         if (Nc < 8) break;
         coarse += (size_t)Nc * (precision == IBM_PREC_MIXED ? (4 + 2 + 1) : (8 * 2 + 1));
+        if (Nc <= BRICK_MAX_CELLS) coarse += (size_t)Nc / 2 * (precision == IBM_PREC_MIXED ? 4 : 8);
     }
     b += coarse;
     b += (size_t)PSTRIDE * 4 * 8;
@@ -947,8 +1044,10 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
         v.f = L.m.p;
         for (int d = 0; d < 3; ++d) { L.pm.pi[d] = L.pi[d].p; L.pm.pt[d] = L.pt[d].p; }
         if (l > 0) {
-            if (c->mixed) { L.x32.alloc(2 * L.Nh); L.b16.alloc(2 * L.Nh); }
-            else { L.x64.alloc(2 * L.Nh); L.b64.alloc(2 * L.Nh); }
+            L.brick = L.N <= BRICK_MAX_CELLS && o.nu1 <= 2 && o.nu2 >= 1 && o.nu2 <= 2;
+            if (L.brick) L.br = make_brick(L.n[0], L.n[1], L.n[2]);
+            if (c->mixed) { L.x32.alloc(2 * L.Nh); L.b16.alloc(2 * L.Nh); if (L.brick) L.k32.alloc(L.Nh); }
+            else { L.x64.alloc(2 * L.Nh); L.b64.alloc(2 * L.Nh); if (L.brick) L.k64.alloc(L.Nh); }
         }
     }
     IBM_REQUIRE(c->lv[0].geo.nb <= PSTRIDE - 2048, IBM_EINVAL, "grid too large");
@@ -1019,6 +1118,7 @@ void ensure_fp64(poisson_ctx &c)
         Level &L = c.lv[l];
         if (!L.x64.p) L.x64.alloc(2 * L.Nh);
         if (!L.b64.p) L.b64.alloc(2 * L.Nh);
+        if (L.brick && !L.k64.p) L.k64.alloc(L.Nh);
     }
     DBuf<double> *v[] = {&c.rh, &c.p, &c.v, &c.ph, &c.sh, &c.rsp, &c.r2};
     for (DBuf<double> *b : v)
@@ -1418,6 +1518,8 @@ void for_scratch(poisson_ctx &c, F &&f)
         f(c.lv[l].b64);
         f(c.lv[l].x32);
         f(c.lv[l].b16);
+        f(c.lv[l].k64);
+        f(c.lv[l].k32);
     }
 }
 constexpr size_t WS_ALIGN = 256;

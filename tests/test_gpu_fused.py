@@ -1,0 +1,55 @@
+"""Fused kernels against the FP64 oracle at the sizes where they can go wrong
+(edges of bricks and tiles, remainders, the ends of the option ranges)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2605_04335_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def box_case(nx, ny, nz, bodies, stretched=False):
+    n = (nx, ny, nz)
+    L = [m / max(n) for m in n]
+    f = [W.stretched_faces(m, 1.05, e)[0] if stretched else W.uniform_faces(m, e) for m, e in zip(n, L)]
+    s, c = min(L), [0.5 * e for e in L]
+    out = []
+    if "sphere" in bodies:
+        out.append(W.sphere((c[0] - 0.2 * s, c[1], c[2]), 0.2 * s, freq=6))
+    if "plate" in bodies:
+        out.append(W.plate((c[0] + 0.15 * s, c[1], c[2]), 0.2 * s, 0.5 * s, 12, 30, 0.05 * s, 0.4))
+    return f, out
+
+
+# coarse levels smoothed on bricks: levels smaller than a brick, of one and a
+# half bricks, odd in every direction (the coarsest level of a ragged box, all
+# its sweeps on bricks), with masked cells and closed faces; every count of
+# smoothing steps that takes the fused launches and one (3) that does not.
+# The V-cycle is a fixed linear map whose global sums are reduced in another
+# order than the oracle's: the bound of the V-cycle's parity test, 1e-11.
+@pytest.mark.parametrize("shape,bodies,nu1,nu2,ncs", [
+    ((24, 40, 56), "sphere plate", 2, 2, 32),
+    ((24, 40, 56), "sphere plate", 1, 2, 32),
+    ((24, 40, 56), "sphere plate", 2, 1, 33),
+    ((24, 40, 56), "sphere", 3, 1, 32),
+    ((50, 42, 30), "sphere", 2, 2, 32),
+    ((50, 42, 62), "sphere plate", 1, 1, 31),
+    ((82, 34, 26), "", 2, 2, 1),
+    ((82, 34, 26), "plate", 2, 2, 2),
+    ((128, 32, 16), "sphere", 2, 2, 32),
+])
+def test_vcycle_on_bricks_matches_oracle(shape, bodies, nu1, nu2, ncs):
+    import torch
+    import paper_2605_04335_amd as P
+    print("[case] bricks", shape, bodies, nu1, nu2, ncs, flush=True)
+    f, bl = box_case(*shape, bodies, stretched=shape[0] == 24)
+    O = oracle.setup(*f, bl)
+    flags, st, sol, _ = P.setup(*f, bl, nu1=nu1, nu2=nu2, coarse_sweeps=ncs)
+    b = oracle.assemble_rhs(*f, O.flags, O.st, W.noise_rhs(len(O.flags), 41))
+    z = sol.precond(torch.from_numpy(b).cuda()).cpu().numpy()
+    assert rel(z, oracle.vcycle(*f, O.flags, O.st, b, nu1, nu2, ncs)) < 1e-11
