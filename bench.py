@@ -96,21 +96,32 @@ def time_solves(sol, f, reps):
 
 
 def sweep_roofline(P, sol, f, T, N, traffic):
-    """Roofline of the level-0 red/black half-sweep (k0_sweep): its launches
-    in one solve timed with HIP events on the solve stream.  Algorithmic bytes
-    per launch: the other colour's values (T bytes each), this colour's RHS
-    and flag byte and its new values, over N/2 cells each: (1.5 T + 0.5) N."""
-    sol.kernel_timing(P.KERNEL_SWEEP0)
+    """Roofline of level 0's smoothing kernel: its launches in one solve timed
+    with HIP events on the solve stream.  On large grids that is the fused
+    second phase (k_walk_up: prolongation and four half-sweeps in one pass):
+    the RHS and the new iterate (T bytes per cell each), the black iterate it
+    starts from (half of that) and the coarse correction (an eighth): 2.625 T
+    N bytes.  Otherwise the red/black half-sweep (k0_sweep): the other
+    colour's values, this colour's RHS and flag byte and its new values, over
+    N/2 cells each: (1.5 T + 0.5) N."""
+    name, bytes_launch = "k_walk_up", 2.625 * T * N
+    sol.kernel_timing(P.KERNEL_WALK_UP)
     sol.solve(f)
-    tot, cnt = sol.kernel_timing(-1)
+    tot, cnt = sol.kernel_timing(P.KERNEL_SWEEP0)
+    if cnt:
+        sol.kernel_timing(-1)
+        traffic = None  # counters are kept for the half-sweep
+    else:
+        name, bytes_launch = "k0_sweep", (1.5 * T + 0.5) * N
+        sol.solve(f)
+        tot, cnt = sol.kernel_timing(-1)
     if not cnt:
         return None
     avg_ms = tot / cnt
-    bytes_launch = (1.5 * T + 0.5) * N
     ach = bytes_launch / (avg_ms * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": (int(traffic) if traffic else None),
-            "kernel": "k0_sweep<%s>" % ("double" if T == 8 else "float"), "avg_launch_ms": round(avg_ms, 4),
+            "kernel": "%s<%s>" % (name, "double" if T == 8 else "float"), "avg_launch_ms": round(avg_ms, 4),
             "launches_per_solve": cnt, "algorithmic_bytes_per_launch": int(bytes_launch)}
 
 
@@ -144,7 +155,7 @@ def solver_source_digest():
     counters describe only the version they were taken on."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hpp", "setup.hpp", "solver.hip", "common.hpp"):
+    for f in ("kernels.hpp", "fused.hpp", "walk.hpp", "setup.hpp", "solver.hip", "common.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2605_04335_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -402,7 +402,9 @@ int32_t poisson_solve_assembled(poisson_ctx *ctx, const double *b_dev, double *x
 
 /* Per-launch device timing of one kernel of the solve, for roofline
  * reports: kernel 0 = level-0 red/black Gauss-Seidel half-sweep, 1 = level-0
- * operator apply inside BiCGSTAB, 2 = the fused x/r update; -1 = off.  While
+ * operator apply inside BiCGSTAB, 2 = the fused x/r update, 3 = the fused
+ * second smoothing phase of level 0 (prolongation and four half-sweeps in one
+ * pass; it takes the half-sweeps' place on large grids); -1 = off.  While
  * a kernel is selected, solves run without graph replay and bracket each of
  * its launches with HIP events on the solve stream.  Returns (and with reset
  * != 0 clears) the accumulated milliseconds and launch count, then selects

@@ -197,7 +197,7 @@ def hbm_stream(kind: int, nbytes: int, reps: int = 10):
     return moved.value / (ms.value * 1e-3) / 1e9, ms.value, moved.value
 
 
-KERNEL_SWEEP0, KERNEL_APPLY0, KERNEL_XR = 0, 1, 2
+KERNEL_SWEEP0, KERNEL_APPLY0, KERNEL_XR, KERNEL_WALK_UP = 0, 1, 2, 3
 
 
 # ------------------------------------------------------------------ geometry

@@ -15,7 +15,7 @@
 // ABI takes and returns natural x-fastest arrays, converted at the boundary.
 
 #include "kernels.hpp"
-#include "fused.hpp"
+#include "walk.hpp"
 #include "setup.hpp"
 
 #include <algorithm>
@@ -28,6 +28,8 @@
 #include <type_traits>
 
 namespace ibm {
+int64_t compact_cells(const uint8_t *flags, long long N, uint8_t mask, DBuf<int32_t> &out, hipStream_t s);
+
 namespace {
 
 // The Krylov vector updates run one block per 256 groups of four unknowns up
@@ -42,6 +44,19 @@ constexpr int XB = 1024;               // cap on blocks of the sparse row kernel
 // takes 19 us against 23 to 29 us of one-sweep launches; at 128^3 the bricks'
 // eightfold recomputation alone is eight times that work, against 34 to 37 us.
 constexpr long long BRICK_MAX_CELLS = 300000;
+
+// Whether level 0 may smooth with the fused passes: the two-step V-cycle of a
+// hierarchy with coarse levels (every dimension even), and enough cells.  At
+// 128^3 with a membrane the two forms are equal (447 and 449 us per FP64
+// V-cycle); below, a pass leaves part of the chip idle.
+constexpr long long WALK_MIN_CELLS = 1 << 21;
+// Largest share of the units in the near list: the listed units cost about 1.3
+// times their share of the one-sweep launches, the pass 0.4 of them all.
+constexpr double WALK_MAX_NEAR = 0.4;
+// From here on the near sequence runs beside the pass on a stream of its own;
+// the fork and join cost 10 us.  160^3 mixed: one after the other 22.3 ms per
+// step, beside 25.9; 256^3 FP64 42.0 and 40.5 ms per solve, 512^3 mixed 288 and 264.
+constexpr long long BESIDE_MIN_CELLS = 1 << 23;
 
 inline int sparse_blocks(long long n) { return (int)std::max<long long>(1, std::min<long long>(XB, (n + TPB - 1) / TPB)); }
 
@@ -181,6 +196,14 @@ struct poisson_ctx {
     DBuf<double> ssum;          // set-up sums (fluid volume, active volume per level)
     DBuf<int> serr;             // set-up error flag
     DBuf<uint8_t> hact[2];      // set-up: natural-order coarse active/cut bits of two consecutive levels
+    // fused level-0 smoothing (walk.hpp) and the units around irregular cells
+    bool walk = false, beside = false;
+    WalkGeo wg{};
+    DBuf<int32_t> units, nunits;
+    DBuf<uint8_t> ubits[2];
+    Near near{}, nearres{};     // the sequence's units; the units whose results replace the pass's
+    hipStream_t ns = nullptr;   // the near cells' launches, beside the pass over the rest
+    hipEvent_t ef = nullptr, en = nullptr;
     double *hsc = nullptr;
     hipStream_t cs = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr, ej = nullptr;
@@ -207,6 +230,9 @@ struct poisson_ctx {
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
         if (ej) (void)hipEventDestroy(ej);
+        if (ef) (void)hipEventDestroy(ef);
+        if (en) (void)hipEventDestroy(en);
+        if (ns) (void)hipStreamDestroy(ns);
         if (cs) (void)hipStreamDestroy(cs);
         for (auto e : prof_ev) (void)hipEventDestroy(e);
     }
@@ -227,7 +253,7 @@ int log_level()
 inline bool log_enabled() { return log_level() > 0; }
 
 // kernel ids of the timing hook
-enum { PK_SWEEP0 = 0, PK_APPLY0 = 1, PK_XR = 2 };
+enum { PK_SWEEP0 = 0, PK_APPLY0 = 1, PK_XR = 2, PK_WALK_UP = 3 };
 
 inline void prof_begin(poisson_ctx &c, int kid, hipStream_t s)
 {
@@ -333,13 +359,25 @@ void launch_prolong(const Level &F, const Level &C, bool skip_red, const Tc *xc,
         k_prolong_z<FINE, Tc, Tf, false, false><<<C.geon.nb, TPB, 0, s>>>(F.lv, C.lv, F.pm, C.geon, xc, xf);
 }
 
+// after a half-sweep of colour `color`: the membrane-adjacent cells of that
+// colour, then a Jacobi update of every ghost unknown
+template <class T>
+void irregular_rows(poisson_ctx &c, T *x, const T *b, int color, hipStream_t s)
+{
+    const int mb = sparse_blocks(c.nm), gb = sparse_blocks(c.nrows + c.nm);
+    if (c.nm) k0_msweep<T><<<mb, TPB, 0, s>>>(c.lv[0].lv, c.sp, x, b, color, c.mtmp.p);
+    if (c.nrows) {
+        k0_mscat_gjac<T><<<gb, TPB, 0, s>>>(c.sp, x, b, color, c.mtmp.p, c.gtmp.p);
+        k0_gscat<T><<<gb, TPB, 0, s>>>(c.sp, x, c.gtmp.p);
+    }
+}
+
 // level-0 smoothing step: for red then black, the dense half-sweep, the
 // membrane-adjacent cells of that colour, then Jacobi on all ghost unknowns
 template <class T>
 void fine_smooth(poisson_ctx &c, T *x, const T *b, const double *sink, bool from_zero, hipStream_t s)
 {
     const Level &L = c.lv[0];
-    const int mb = sparse_blocks(c.nm), gb = sparse_blocks(c.nrows + c.nm);
     for (int color = 0; color < 2; ++color) {
         if (from_zero && color == 0) {
             // the other colour is zeroed too: ghost rows and membrane rows read it before its sweep
@@ -360,11 +398,7 @@ void fine_smooth(poisson_ctx &c, T *x, const T *b, const double *sink, bool from
                                              color);
             if (!from_zero) prof_end(c, PK_SWEEP0, s);
         }
-        if (c.nm) k0_msweep<T><<<mb, TPB, 0, s>>>(L.lv, c.sp, x, b, color, c.mtmp.p);
-        if (c.nrows) {
-            k0_mscat_gjac<T><<<gb, TPB, 0, s>>>(c.sp, x, b, color, c.mtmp.p, c.gtmp.p);
-            k0_gscat<T><<<gb, TPB, 0, s>>>(c.sp, x, c.gtmp.p);
-        }
+        irregular_rows<T>(c, x, b, color, s);
     }
     IBM_LAUNCH_CHECK();
 }
@@ -456,26 +490,105 @@ void brick_coarsest(poisson_ctx &c, int l, int npart, hipStream_t s)
     IBM_LAUNCH_CHECK();
 }
 
-// x = V-cycle(b) on the unpinned operator with the sink at the pin; x unshifted
+// the near cells' launches run on c.ns between fork() and join()
+void fork(poisson_ctx &c, hipStream_t s)
+{
+    IBM_HIP(hipEventRecord(c.ef, s));
+    IBM_HIP(hipStreamWaitEvent(c.ns, c.ef, 0));
+}
+void join(poisson_ctx &c, hipStream_t s)
+{
+    IBM_HIP(hipEventRecord(c.en, c.ns));
+    IBM_HIP(hipStreamWaitEvent(s, c.en, 0));
+}
+
+// level 0, first phase (two steps from zero, residual, restriction) with the
+// fused pass; w: scratch vector of the near cells, xk: black iterate between
+// the phases, rs: scratch for the irregular cells' residuals.  Returns the
+// count of partial sums of level 1's mean.
 template <class T>
-void vcycle(poisson_ctx &c, const T *b, T *x, const double *sink, hipStream_t s)
+int walk_down(poisson_ctx &c, const T *b, T *w, T *xk, T *rs, const double *sink, hipStream_t s)
+{
+    typedef typename Store<T>::TB TB;
+    Level &L = c.lv[0], &C = c.lv[1];
+    double *part = mean_part(c, 1);
+    TB *bc = Store<T>::b(C);
+    const int nu = c.near.nb();
+    if (nu) {
+        hipStream_t n = c.beside ? c.ns : s;
+        if (c.beside) fork(c, s);
+        k_near_zero<T><<<nu + (int)cdiv(c.nm, NU_T), NU_T, 0, n>>>(L.lv, c.near, nu, c.nm, c.pin, sink, b, w);
+        irregular_rows<T>(c, w, b, 0, n);
+        for (int q = 0; q < 3; ++q) {
+            const int color = q == 1 ? 0 : 1;
+            k_near_sweep<T><<<nu, NU_T, 0, n>>>(L.lv, c.near, c.pin, sink, b, w, color);
+            irregular_rows<T>(c, w, b, color, n);
+        }
+        const int nsp = (int)(c.nrows + c.nm);
+        if (nsp) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, n>>>(L.lv, c.sp, w, b, rs);
+        k_near_restrict<T, TB><<<nu, NU_T, 0, n>>>(L.lv, C.lv, c.near, c.pin, sink, b, w, rs, bc, part + c.wg.nb);
+    }
+    k_walk_down<T, TB><<<c.wg.nb, WK_T, 0, s>>>(L.lv, C.lv, c.wg, c.near, c.pin, sink, b, xk, bc, part);
+    IBM_LAUNCH_CHECK();
+    if (nu && c.beside) join(c, s);
+    return c.wg.nb + nu;
+}
+
+// second phase: prolongation and two steps; x receives every unknown
+template <class T>
+void walk_up(poisson_ctx &c, const T *b, T *x, T *w, T *xk, const double *sink, hipStream_t s)
+{
+    Level &L = c.lv[0], &C = c.lv[1];
+    const T *xc = (const T *)Store<T>::x(C);
+    const int nu = c.near.nb();
+    if (nu) {
+        hipStream_t n = c.beside ? c.ns : s;
+        k_near_merge<T><<<nu, NU_T, 0, s>>>(L.lv, c.near, w, xk);
+        if (c.beside) fork(c, s);
+        k_near_prolong<T><<<nu, NU_T, 0, n>>>(L.lv, C.lv, L.pm, c.near, xc, w);
+        for (int q = 0; q < 4; ++q) {
+            k_near_sweep<T><<<nu, NU_T, 0, n>>>(L.lv, c.near, c.pin, sink, b, w, q & 1);
+            irregular_rows<T>(c, w, b, q & 1, n);
+        }
+    }
+    prof_begin(c, PK_WALK_UP, s);
+    k_walk_up<T><<<c.wg.nb, WK_T, 0, s>>>(L.lv, C.lv, L.pm, c.wg, c.pin, sink, b, xk, xc, x);
+    prof_end(c, PK_WALK_UP, s);
+    if (nu) {
+        if (c.beside) join(c, s);
+        const int nr = c.nearres.nb();
+        k_near_final<T><<<nr + (int)cdiv(c.nm, NU_T), NU_T, 0, s>>>(L.lv, c.nearres, nr, c.nm, w, x);
+    }
+    IBM_LAUNCH_CHECK();
+}
+
+// x = V-cycle(b) on the unpinned operator with the sink at the pin; x
+// unshifted; w: a scratch vector over the unknowns (neither b nor x)
+template <class T>
+void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStream_t s)
 {
     typedef typename Store<T>::Tc Tc;
     typedef typename Store<T>::TB TB;
     const int nl = (int)c.lv.size();
     const poisson_opts &o = c.opts;
-    for (int it = 0; it < o.nu1; ++it) fine_smooth<T>(c, x, b, sink, it == 0, s);
+    T *r0 = std::is_same<T, double>::value ? (T *)c.rsp.p : (T *)c.frsp.p;
+    if (!c.walk)
+        for (int it = 0; it < o.nu1; ++it) fine_smooth<T>(c, x, b, sink, it == 0, s);
     if (nl > 1) {
-        // level-0 residual: the sparse rows into r0, then the regular rows
-        // computed and restricted in one pass
-        T *r0 = std::is_same<T, double>::value ? (T *)c.rsp.p : (T *)c.frsp.p;
-        const int nsp = (int)(c.nrows + c.nm);
-        if (nsp) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, s>>>(c.lv[0].lv, c.sp, x, b, r0);
         Level &L1 = c.lv[1];
-        k0_restrict_res<T, TB><<<L1.geon.nb, TPB, 0, s>>>(c.lv[0].lv, L1.lv, L1.geon, c.pin, x, b, sink, r0,
-                                                         Store<T>::b(L1), mean_part(c, 1));
-        IBM_LAUNCH_CHECK();
-        int npart = L1.geon.nb;  // partial sums of the next level's mean
+        int npart;  // partial sums of the next level's mean
+        if (c.walk) {
+            npart = walk_down<T>(c, b, w, r0, x, sink, s);  // x is free until the second phase
+        } else {
+            // level-0 residual: the sparse rows into r0, then the regular rows
+            // computed and restricted in one pass
+            const int nsp = (int)(c.nrows + c.nm);
+            if (nsp) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, s>>>(c.lv[0].lv, c.sp, x, b, r0);
+            k0_restrict_res<T, TB><<<L1.geon.nb, TPB, 0, s>>>(c.lv[0].lv, L1.lv, L1.geon, c.pin, x, b, sink, r0,
+                                                             Store<T>::b(L1), mean_part(c, 1));
+            IBM_LAUNCH_CHECK();
+            npart = L1.geon.nb;
+        }
         const int lt = std::is_same<T, double>::value ? c.tail0d : c.tail0;
         for (int l = 1; l < lt; ++l) {
             Level &L = c.lv[l];
@@ -532,6 +645,10 @@ void vcycle(poisson_ctx &c, const T *b, T *x, const double *sink, hipStream_t s)
             launch_prolong<false>(L, C, o.nu2 > 0, Store<T>::x(C), Store<T>::x(L), s);
             coarse_smooth<Tc, TB>(L, o.nu2, false, c.sc.p + S_MEAN0 + l, s);
         }
+        if (c.walk) {
+            walk_up<T>(c, b, x, w, r0, sink, s);
+            return;
+        }
         Level &L0v = c.lv[0];
         launch_prolong<true>(L0v, L1, o.nu2 > 0, Store<T>::x(L1), x, s);
         IBM_LAUNCH_CHECK();
@@ -578,10 +695,10 @@ void srj_apply(poisson_ctx &c, const T *b, T *x, hipStream_t s)
 // x = M^-1 b: the V-cycle (with the pin sink) or SRJ; the output is not yet
 // shifted to a zero pin value (its consumers do that)
 template <class T>
-void precond(poisson_ctx &c, const T *b, T *x, const double *sink, hipStream_t s)
+void precond(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStream_t s)
 {
     if (c.opts.precond == IBM_PRECOND_SRJ) srj_apply<T>(c, b, x, s);
-    else vcycle<T>(c, b, x, sink, s);
+    else vcycle<T>(c, b, x, w, sink, s);
 }
 
 // One BiCGSTAB iteration (van der Vorst 1992, right preconditioning): all
@@ -593,14 +710,14 @@ void bicg_iteration(poisson_ctx &c, TX *y, T *r, T *rh, T *p, T *v, T *ph, T *sh
     const Lv &L = c.L0();
     k_p_update4<T><<<W.nb, TPB, 0, s>>>(L, W, c.Nt, r, p, v, c.sc.p, c.part.p);
     fin(c, W.nb, FIN_SINK, S_SINKP, 0.0, s);
-    precond<T>(c, p, ph, c.sc.p + S_SINKP, s);
+    precond<T>(c, p, ph, t, c.sc.p + S_SINKP, s);  // t is free until the second operator apply
     prof_begin(c, PK_APPLY0, s);
     int np = launch_apply<T>(c, M_PINZERO, false, 1, ph, v, nullptr, nullptr, rh, nullptr, s);
     prof_end(c, PK_APPLY0, s);
     fin(c, np, FIN_ALPHA, 0, 0.0, s);
     k_s_update4<T><<<W.nb, TPB, 0, s>>>(L, W, c.Nt, r, v, c.sc.p, c.part.p);
     fin(c, W.nb, FIN_SINK, S_SINKS, 0.0, s);
-    precond<T>(c, r, sh, c.sc.p + S_SINKS, s);
+    precond<T>(c, r, sh, t, c.sc.p + S_SINKS, s);
     np = launch_apply<T>(c, M_PINZERO, false, 2, sh, t, nullptr, nullptr, r, nullptr, s);
     fin(c, np, FIN_OMEGA, 0, 0.0, s);
     prof_begin(c, PK_XR, s);
@@ -788,6 +905,7 @@ size_t estimate_bytes(int nx, int ny, int nz, long long nrows, int precision)
     long long Nh = (long long)((nx + 1) / 2) * ny * nz;
     long long Nt = 2 * Nh + nrows;
     size_t b = (size_t)2 * Nh;  // flags
+    if (2 * Nh >= WALK_MIN_CELLS) b += (size_t)(2 * Nh) / 128 * 2 + (size_t)nrows * 8;  // near units' bits and lists
     b += (size_t)nrows * (8 * 4 + 8 * 8 + 16 + 8 + 4 + 6 * 4 + 4 + 8 * 4 + 8);
     b += (size_t)Nt * 8 * (precision == IBM_PREC_MIXED ? 4 : 10);
     if (precision == IBM_PREC_MIXED) b += (size_t)Nt * (4 * 8 + 8);
@@ -809,6 +927,59 @@ template <class T>
 void reserve(DBuf<T> &b, size_t n)
 {
     if (!b.p || b.n < n) b.alloc(n);
+}
+
+bool walk_wanted(const poisson_ctx &c)
+{
+    return c.opts.precond == IBM_PRECOND_MG && c.opts.nu1 == 2 && c.opts.nu2 == 2 && c.lv.size() > 1 &&
+           c.N >= WALK_MIN_CELLS;
+}
+
+// Lists of the fused level-0 pass for the current classification: near and
+// listed units, the blocks' plane runs.
+void plan_walk(poisson_ctx &c, hipStream_t s)
+{
+    c.walk = walk_wanted(c);
+    if (!c.walk) return;
+    const Level &Z = c.lv[0];
+    const int nux = (Z.H + 3) / 4, nuy = (Z.n[1] + 3) / 4, nuz = (Z.n[2] + 3) / 4;
+    const long long nu = (long long)nux * nuy * nuz;
+    c.near = Near{};
+    if (c.nrows || c.nm) {
+        for (auto &q : c.ubits) reserve(q, nu);
+        k_unit_cells<<<cdiv(nu, 4), NU_T, 0, s>>>(Z.lv, nux, nuy, nu, c.ubits[0].p);
+        k_unit_near<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[0].p, c.ubits[1].p);
+        k_unit_list<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[1].p, c.ubits[0].p);
+        IBM_LAUNCH_CHECK();
+        const int64_t n = compact_cells(c.ubits[0].p, nu, UB_LIST, c.units, s);
+        const int64_t nr = compact_cells(c.ubits[0].p, nu, UB_NEAR, c.nunits, s);
+        c.near = Near{c.units.p, c.ubits[0].p, (int)n, nux, nuy, nuz};
+        c.nearres = Near{c.nunits.p, c.ubits[0].p, (int)nr, nux, nuy, nuz};
+        c.walk = n <= WALK_MAX_NEAR * nu;
+    }
+    // planes per block: a block fills a CU and computes eight planes more than
+    // it owns; the length that takes the fewest plane steps over the rounds
+    WalkGeo &g = c.wg;
+    g.ntx = (Z.H + WK_OH - 1) / WK_OH;
+    g.nty = (Z.n[1] + WK_OJ - 1) / WK_OJ;
+    long long best = -1;
+    for (int kz = 4; kz <= WK_KZMAX; kz += 4) {
+        const int ncz = (Z.n[2] + kz - 1) / kz;
+        const long long cost = ((long long)g.ntx * g.nty * ncz + 255) / 256 * (kz + 8 + 2);
+        if (best < 0 || cost < best) {
+            best = cost;
+            g.kz = kz;
+            g.ncz = ncz;
+        }
+    }
+    g.nb = (g.ntx * g.nty * g.ncz + 7) / 8 * 8;
+    if ((long long)g.nb + c.near.nb() > PSTRIDE) c.walk = false;
+    c.beside = c.N >= BESIDE_MIN_CELLS;
+    if (c.walk && c.beside && !c.ns) {
+        IBM_HIP(hipStreamCreateWithFlags(&c.ns, hipStreamNonBlocking));
+        IBM_HIP(hipEventCreateWithFlags(&c.ef, hipEventDisableTiming));
+        IBM_HIP(hipEventCreateWithFlags(&c.en, hipEventDisableTiming));
+    }
 }
 
 // Flag-dependent parts of a context -- level-0 flags, ghost and membrane rows
@@ -893,6 +1064,7 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     IBM_HIP(hipMemcpyAsync(&herr, c.serr.p, sizeof(int), hipMemcpyDeviceToHost, s));
     IBM_HIP(hipStreamSynchronize(s));
     IBM_REQUIRE(herr == 0, IBM_EGEOM, "cut link without ghost");
+    plan_walk(c, s);
     c.vol_fluid = hs[0];
     for (int l = 1; l < nl; ++l) {
         c.lv[l].volA = hs[l];
@@ -1468,7 +1640,7 @@ extern "C" int32_t poisson_precond(poisson_ctx *c, const double *b_dev, double *
         to_split(*c, b_dev, c->r.p, c->nm, s);
         k_vsum<double, true><<<c->Wc.nb, TPB, 0, s>>>(c->L0(), c->Wc, c->r.p, c->part.p);
         fin(*c, c->Wc.nb, FIN_SINK, S_SINKP, 0.0, s);
-        precond<double>(*c, c->r.p, c->t.p, c->sc.p + S_SINKP, s);
+        precond<double>(*c, c->r.p, c->t.p, c->sh.p, c->sc.p + S_SINKP, s);
         // shift: every active unknown minus the pin value, then the pin itself
         k_shift<double><<<c->W0.nb, TPB, 0, s>>>(c->L0(), c->W0, c->pin, c->t.p);
         k_shift_pin<<<1, 1, 0, s>>>(c->pin, c->t.p);
@@ -1482,7 +1654,7 @@ extern "C" int32_t poisson_kernel_timing(poisson_ctx *c, int32_t kernel, int32_t
 {
     return guarded([&] {
         IBM_REQUIRE(c, IBM_EINVAL, "null context");
-        IBM_REQUIRE(kernel >= -1 && kernel <= PK_XR, IBM_EINVAL, "unknown kernel id");
+        IBM_REQUIRE(kernel >= -1 && kernel <= PK_WALK_UP, IBM_EINVAL, "unknown kernel id");
         if (total_ms) *total_ms = c->prof_ms;
         if (launches) *launches = c->prof_count;
         if (reset) { c->prof_ms = 0.0; c->prof_count = 0; c->prof_used = 0; }
