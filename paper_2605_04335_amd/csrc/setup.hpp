@@ -26,14 +26,16 @@ __device__ __forceinline__ long long col_unknown(const SlotMap &m, long long col
     return col < m.N ? cell_slot(m, col) : m.N2 + (col - m.N);
 }
 
-// level-0 flags in split layout; padding slots (i == nx on odd nx) are solid
+// level-0 flags in split layout, without the cut bits (their places hold bits
+// of the solver's own); padding slots (i == nx on odd nx) are solid
 __global__ void __launch_bounds__(TPB) k_setup_flags0(Lv L, Walk W, const uint8_t *__restrict__ nat,
                                                       uint8_t *__restrict__ spl)
 {
     WALK_BEGIN(W, p)
         int c, h, j, k, i;
         decode_slot(L, p, c, h, j, k, i);
-        spl[p] = i < L.nx ? nat[(long long)i + (long long)L.nx * (j + (long long)L.ny * k)] : (uint8_t)F_SOLID;
+        spl[p] = i < L.nx ? (uint8_t)(nat[(long long)i + (long long)L.nx * (j + (long long)L.ny * k)] & 0x8f)
+                          : (uint8_t)F_SOLID;
     WALK_END
 }
 

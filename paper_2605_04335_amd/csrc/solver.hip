@@ -15,7 +15,7 @@
 // ABI takes and returns natural x-fastest arrays, converted at the boundary.
 
 #include "kernels.hpp"
-#include "walk.hpp"
+#include "rows.hpp"
 #include "setup.hpp"
 
 #include <algorithm>
@@ -57,6 +57,12 @@ constexpr double WALK_MAX_NEAR = 0.4;
 // the fork and join cost 10 us.  160^3 mixed: one after the other 22.3 ms per
 // step, beside 25.9; 256^3 FP64 42.0 and 40.5 ms per solve, 512^3 mixed 288 and 264.
 constexpr long long BESIDE_MIN_CELLS = 1 << 23;
+// Up to this many rows the near units take the half-sweeps of rows.hpp (one
+// or two launches each instead of four); beyond, their recomputed cells cost
+// more than the launches.  FP64 V-cycle at 128^3 with a membrane: 440 us
+// without, 406 us with; 256^3 with 63 thousand rows: 41.2 and 42.2 ms per
+// solve; 512^3 with 150 thousand: 11.1 and 11.4 ms per iteration.
+constexpr long long FEW_ROWS = 1 << 15;
 
 inline int sparse_blocks(long long n) { return (int)std::max<long long>(1, std::min<long long>(XB, (n + TPB - 1) / TPB)); }
 
@@ -198,6 +204,12 @@ struct poisson_ctx {
     DBuf<uint8_t> hact[2];      // set-up: natural-order coarse active/cut bits of two consecutive levels
     // fused level-0 smoothing (walk.hpp) and the units around irregular cells
     bool walk = false, beside = false;
+    // level-0 half-sweeps with the sparse rows in the same launch (rows.hpp):
+    // on all of level 0 (flat), or on the near units of the fused passes (few)
+    bool flat = false, few = false;
+    Rows rows{};
+    DBuf<int32_t> code, rix, mcode, aslot, acode;
+    DBuf<double> gtmp2;
     WalkGeo wg{};
     DBuf<int32_t> units, nunits;
     DBuf<uint8_t> ubits[2];
@@ -490,6 +502,50 @@ void brick_coarsest(poisson_ctx &c, int l, int npart, hipStream_t s)
     IBM_LAUNCH_CHECK();
 }
 
+// n half-sweeps (red first) with the sparse rows, over every cell of level 0
+// or (UNITS) the near units; zero: from a zero iterate.  Ghost values start
+// at their unknowns in x and then alternate between two arrays: the array that
+// holds them at the end is returned (null without ghost rows).
+template <class T, bool UNITS>
+T *half_sweeps(poisson_ctx &c, T *x, const T *b, const double *sink, int n, bool zero, hipStream_t s)
+{
+    const Level &L = c.lv[0];
+    const Rows &R = c.rows;
+    T *G[2] = {(T *)c.gtmp.p, (T *)c.gtmp2.p}, *g = nullptr;
+    HalfBlocks B;
+    B.cells = UNITS ? c.near.nb() : (int)((L.Nh + 8 * TPB - 1) / (8 * TPB) * 8);
+    for (int q = 0; q < n; ++q) {
+        const int color = q & 1;
+        const RowsIn<T> I{x, g, b, sink, zero && q == 0};
+        T *gn = g == G[0] ? G[1] : G[0];
+        B.adj = I.zero ? 0 : (int)cdiv(R.na, TPB);
+        B.rows = (int)cdiv(8LL * (R.nm ? R.nm : R.nrows), TPB);
+        if (!UNITS && !I.zero) prof_begin(c, PK_SWEEP0, s);
+        if (R.nm) {
+            k_half<T, UNITS, false><<<B.total(), TPB, 0, s>>>(L.lv, R, c.near, B, I, x, color, gn, c.mtmp.p);
+            k_half_ghosts<T><<<cdiv(R.nrows + R.nm, TPB), TPB, 0, s>>>(L.lv, R, I, x, color, c.mtmp.p, gn);
+        } else {
+            k_half<T, UNITS, true><<<B.total(), TPB, 0, s>>>(L.lv, R, c.near, B, I, x, color, gn, nullptr);
+        }
+        if (!UNITS && !I.zero) prof_end(c, PK_SWEEP0, s);
+        if (R.nrows) g = gn;
+    }
+    IBM_LAUNCH_CHECK();
+    return g;
+}
+
+// ghost values to their unknowns in x; rs: also the sparse cells' residuals
+template <class T>
+void rows_out(poisson_ctx &c, T *x, const T *b, const T *g, T *rs, hipStream_t s)
+{
+    const Rows &R = c.rows;
+    if (!R.nrows || !g) return;
+    const RowsIn<T> I{x, g, b, nullptr, false};
+    if (rs) k_rows_out<T, true><<<cdiv(R.nrows + R.nm, TPB), TPB, 0, s>>>(c.lv[0].lv, R, I, x, rs);
+    else k_rows_out<T, false><<<cdiv(R.nrows, TPB), TPB, 0, s>>>(c.lv[0].lv, R, I, x, rs);
+    IBM_LAUNCH_CHECK();
+}
+
 // the near cells' launches run on c.ns between fork() and join()
 void fork(poisson_ctx &c, hipStream_t s)
 {
@@ -517,15 +573,19 @@ int walk_down(poisson_ctx &c, const T *b, T *w, T *xk, T *rs, const double *sink
     if (nu) {
         hipStream_t n = c.beside ? c.ns : s;
         if (c.beside) fork(c, s);
-        k_near_zero<T><<<nu + (int)cdiv(c.nm, NU_T), NU_T, 0, n>>>(L.lv, c.near, nu, c.nm, c.pin, sink, b, w);
-        irregular_rows<T>(c, w, b, 0, n);
-        for (int q = 0; q < 3; ++q) {
-            const int color = q == 1 ? 0 : 1;
-            k_near_sweep<T><<<nu, NU_T, 0, n>>>(L.lv, c.near, c.pin, sink, b, w, color);
-            irregular_rows<T>(c, w, b, color, n);
+        if (c.few) {
+            rows_out<T>(c, w, b, half_sweeps<T, true>(c, w, b, sink, 4, true, n), rs, n);
+        } else {
+            k_near_zero<T><<<nu + (int)cdiv(c.nm, NU_T), NU_T, 0, n>>>(L.lv, c.near, nu, c.nm, c.pin, sink, b, w);
+            irregular_rows<T>(c, w, b, 0, n);
+            for (int q = 0; q < 3; ++q) {
+                const int color = q == 1 ? 0 : 1;
+                k_near_sweep<T><<<nu, NU_T, 0, n>>>(L.lv, c.near, c.pin, sink, b, w, color);
+                irregular_rows<T>(c, w, b, color, n);
+            }
+            const int nsp = (int)(c.nrows + c.nm);
+            if (nsp) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, n>>>(L.lv, c.sp, w, b, rs);
         }
-        const int nsp = (int)(c.nrows + c.nm);
-        if (nsp) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, n>>>(L.lv, c.sp, w, b, rs);
         k_near_restrict<T, TB><<<nu, NU_T, 0, n>>>(L.lv, C.lv, c.near, c.pin, sink, b, w, rs, bc, part + c.wg.nb);
     }
     k_walk_down<T, TB><<<c.wg.nb, WK_T, 0, s>>>(L.lv, C.lv, c.wg, c.near, c.pin, sink, b, xk, bc, part);
@@ -546,9 +606,13 @@ void walk_up(poisson_ctx &c, const T *b, T *x, T *w, T *xk, const double *sink, 
         k_near_merge<T><<<nu, NU_T, 0, s>>>(L.lv, c.near, w, xk);
         if (c.beside) fork(c, s);
         k_near_prolong<T><<<nu, NU_T, 0, n>>>(L.lv, C.lv, L.pm, c.near, xc, w);
-        for (int q = 0; q < 4; ++q) {
-            k_near_sweep<T><<<nu, NU_T, 0, n>>>(L.lv, c.near, c.pin, sink, b, w, q & 1);
-            irregular_rows<T>(c, w, b, q & 1, n);
+        if (c.few) {
+            rows_out<T>(c, w, b, half_sweeps<T, true>(c, w, b, sink, 4, false, n), (T *)nullptr, n);
+        } else {
+            for (int q = 0; q < 4; ++q) {
+                k_near_sweep<T><<<nu, NU_T, 0, n>>>(L.lv, c.near, c.pin, sink, b, w, q & 1);
+                irregular_rows<T>(c, w, b, q & 1, n);
+            }
         }
     }
     prof_begin(c, PK_WALK_UP, s);
@@ -572,7 +636,9 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
     const int nl = (int)c.lv.size();
     const poisson_opts &o = c.opts;
     T *r0 = std::is_same<T, double>::value ? (T *)c.rsp.p : (T *)c.frsp.p;
-    if (!c.walk)
+    if (c.flat)
+        rows_out<T>(c, x, b, half_sweeps<T, false>(c, x, b, sink, 2 * o.nu1, true, s), nl > 1 ? r0 : (T *)nullptr, s);
+    else if (!c.walk)
         for (int it = 0; it < o.nu1; ++it) fine_smooth<T>(c, x, b, sink, it == 0, s);
     if (nl > 1) {
         Level &L1 = c.lv[1];
@@ -583,7 +649,7 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
             // level-0 residual: the sparse rows into r0, then the regular rows
             // computed and restricted in one pass
             const int nsp = (int)(c.nrows + c.nm);
-            if (nsp) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, s>>>(c.lv[0].lv, c.sp, x, b, r0);
+            if (nsp && !c.flat) k0_sparse_res<T><<<sparse_blocks(nsp), TPB, 0, s>>>(c.lv[0].lv, c.sp, x, b, r0);
             k0_restrict_res<T, TB><<<L1.geon.nb, TPB, 0, s>>>(c.lv[0].lv, L1.lv, L1.geon, c.pin, x, b, sink, r0,
                                                              Store<T>::b(L1), mean_part(c, 1));
             IBM_LAUNCH_CHECK();
@@ -653,7 +719,9 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
         launch_prolong<true>(L0v, L1, o.nu2 > 0, Store<T>::x(L1), x, s);
         IBM_LAUNCH_CHECK();
     }
-    for (int it = 0; it < o.nu2; ++it) fine_smooth<T>(c, x, b, sink, false, s);
+    if (c.flat) rows_out<T>(c, x, b, half_sweeps<T, false>(c, x, b, sink, 2 * o.nu2, false, s), (T *)nullptr, s);
+    else
+        for (int it = 0; it < o.nu2; ++it) fine_smooth<T>(c, x, b, sink, false, s);
 }
 
 // SRJ schedule: the reciprocals of the roots of the degree-m Chebyshev
@@ -907,6 +975,7 @@ size_t estimate_bytes(int nx, int ny, int nz, long long nrows, int precision)
     size_t b = (size_t)2 * Nh;  // flags
     if (2 * Nh >= WALK_MIN_CELLS) b += (size_t)(2 * Nh) / 128 * 2 + (size_t)nrows * 8;  // near units' bits and lists
     b += (size_t)nrows * (8 * 4 + 8 * 8 + 16 + 8 + 4 + 6 * 4 + 4 + 8 * 4 + 8);
+    b += (size_t)nrows * (16 * 4 + 6 * 4 + 2 * (4 + 6 * 4) + 8);  // coded rows, adjacent cells
     b += (size_t)Nt * 8 * (precision == IBM_PREC_MIXED ? 4 : 10);
     if (precision == IBM_PREC_MIXED) b += (size_t)Nt * (4 * 8 + 8);
     long long Nc = 2 * Nh;
@@ -982,6 +1051,46 @@ void plan_walk(poisson_ctx &c, hipStream_t s)
     }
 }
 
+// Coded sparse rows of the fused half-sweeps, from the rows in slot numbering.
+void code_rows(poisson_ctx &c, const ibm_stencils *st, hipStream_t s)
+{
+    const Level &Z = c.lv[0];
+    Rows &R = c.rows;
+    R = Rows{};
+    R.N2 = c.N2;
+    R.Nh = Z.Nh;
+    R.pin = c.pin;
+    R.ng = (int)c.ng;
+    R.nrows = (int)c.nrows;
+    R.nm = (int)c.nm;
+    if (!c.nrows) return;
+    if (c.ng) {
+        k_mark_adjacent<<<Z.walk.nb, TPB, 0, s>>>(Z.lv, Z.walk, Z.m.p);
+        IBM_LAUNCH_CHECK();
+        R.na = (int)compact_cells(Z.m.p, c.N2, F_ADJ, c.aslot, s);
+    }
+    const CodeMap M{Z.lv, st->cell.p, st->cell.p + c.ng, c.aslot.p, R.ng, R.nm, R.na};
+    auto blocks = [](long long n) { return (int)std::min<long long>(std::max<long long>((n + TPB - 1) / TPB, 1), 4096); };
+    reserve(c.code, 8 * c.nrows);
+    reserve(c.rix, 8 * c.nrows);
+    reserve(c.mcode, std::max<long long>(6 * c.nm, 1));
+    reserve(c.acode, std::max(6 * R.na, 1));
+    k_code_columns<<<blocks(8 * c.nrows), TPB, 0, s>>>(M, 8 * c.nrows, c.rcol.p, c.code.p, c.rix.p);
+    if (c.nm) k_code_columns<<<blocks(6 * c.nm), TPB, 0, s>>>(M, 6 * c.nm, c.mcol.p, c.mcode.p, nullptr);
+    if (R.na) k_code_adjacent<<<blocks(R.na), TPB, 0, s>>>(M, c.acode.p);
+    IBM_LAUNCH_CHECK();
+    R.rslot = c.rslot.p;
+    R.code = c.code.p;
+    R.rix = c.rix.p;
+    R.rw = c.rw.p;
+    R.rsG = c.rsG.p;
+    R.mslot = c.mslot.p;
+    R.mcode = c.mcode.p;
+    R.mcolor = c.mcolor.p;
+    R.aslot = c.aslot.p;
+    R.acode = c.acode.p;
+}
+
 // Flag-dependent parts of a context -- level-0 flags, ghost and membrane rows
 // in slot numbering, fluid and pin volumes, coarse masks, vectors sized by
 // the unknown count -- built on the device from the classification and the
@@ -1023,6 +1132,7 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     reserve(c.rsG, R1);
     reserve(c.rdlb, R1);
     reserve(c.gtmp, R1);
+    reserve(c.gtmp2, R1);
     reserve(c.mtmp, M1);
     reserve(c.rmrow, R1 * 8);
     reserve(c.mslot, M1);
@@ -1065,6 +1175,9 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     IBM_HIP(hipStreamSynchronize(s));
     IBM_REQUIRE(herr == 0, IBM_EGEOM, "cut link without ghost");
     plan_walk(c, s);
+    c.flat = c.opts.precond == IBM_PRECOND_MG && c.N < WALK_MIN_CELLS;
+    c.few = c.walk && c.nrows <= FEW_ROWS;
+    if (c.few || c.flat) code_rows(c, st, s);
     c.vol_fluid = hs[0];
     for (int l = 1; l < nl; ++l) {
         c.lv[l].volA = hs[l];

@@ -562,7 +562,7 @@ __device__ __forceinline__ double near_nb(const Lv &L, const UnitPos &u, const T
 {
     const T *xo = W + (long long)(1 - c) * L.Nh;
     const long long pl = (long long)L.H * L.ny;
-    const int p = (c + u.j + u.k) & 1, i = 2 * u.h + p;
+    const int p = (c + u.j + u.k) & 1, i = min(2 * u.h + p, L.nx - 1);  // (a padding slot: as its neighbour, dropped)
     const double cpx = L.cp[0][i], cmx = L.cm[0][i], cpy = L.cp[1][u.j], cmy = L.cm[1][u.j], cpz = L.cp[2][u.k],
                  cmz = L.cm[2][u.k];
     const double vxp = ld(xo, s + (i + 1 < L.nx ? p : 0)), vxm = ld(xo, s + (i > 0 ? p - 1 : 0));

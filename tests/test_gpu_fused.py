@@ -111,3 +111,44 @@ def test_fused_pass_after_update_equals_fresh_setup():
         sol.update(flags, st)
         x = torch.from_numpy(W.noise_rhs(fresh.n_unknowns, 44)).cuda()
         assert torch.equal(sol.precond(x), fresh.precond(x))
+
+
+# half-sweeps with the sparse rows in the same launch: closed ghosts, membranes
+# and both, next to each other and at the walls, odd edges (padding slots),
+# one to three steps before and none to three after the coarse correction, a
+# box of a single block of cells, no rows at all; and a box with enough rows
+# for the one-sweep row kernels beside the fused pass.  The same bound and the
+# same comparison modulo a constant.
+@pytest.mark.parametrize("shape,bodies,nu1,nu2", [
+    ((8, 6, 4), "", 2, 2),
+    ((16, 16, 16), "plate", 1, 1),
+    ((25, 31, 27), "sphere plate", 2, 2),
+    ((40, 34, 38), "touching", 2, 2),
+    ((40, 34, 38), "touching", 3, 1),
+    ((36, 28, 46), "wall", 1, 3),
+    ((36, 28, 46), "wall", 2, 0),
+    ((176, 160, 152), "large", 2, 2),
+])
+def test_fused_rows_match_oracle(shape, bodies, nu1, nu2):
+    import torch
+    import paper_2605_04335_amd as P
+    print("[case] rows", shape, bodies, nu1, nu2, flush=True)
+    f, bl = walk_case(shape, bodies)
+    L = [m / max(shape) for m in shape]
+    c, s = [0.5 * e for e in L], min(L)
+    if "touching" in bodies:  # the membrane's edge one cell from the sphere
+        bl = [W.sphere((c[0], c[1], c[2]), 0.2 * s, freq=6),
+              W.plate((c[0], c[1], c[2] + 0.2 * s + 1.5 / max(shape)), 0.3 * s, 0.5 * s, 12, 30)]
+    if "large" in bodies:
+        bl = [W.sphere((c[0], c[1], c[2]), 0.4 * s, freq=12)]
+    O = oracle.setup(*f, bl)
+    flags, st, sol, _ = P.setup(*f, bl, nu1=nu1, nu2=nu2)
+    assert bodies != "large" or O.st.ng + O.st.nm > 1 << 15
+    b = oracle.assemble_rhs(*f, O.flags, O.st, W.noise_rhs(len(O.flags), 45))
+    bt = torch.from_numpy(b).cuda()
+    z = sol.precond(bt)
+    zo = oracle.vcycle(*f, O.flags, O.st, b, nu1, nu2, 32)
+    act = zo != 0.0
+    d = z.cpu().numpy() - zo
+    assert np.linalg.norm(d[act] - d[act].mean()) < 1e-11 * np.linalg.norm(zo)
+    assert torch.equal(z, sol.precond(bt))
