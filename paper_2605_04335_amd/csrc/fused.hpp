@@ -170,12 +170,6 @@ __global__ void __launch_bounds__(BR_T) k_brick(Lv L, Brick G, Lv C, PMap M, Bri
             act[c][u] = (f & CM_ACT) != 0;
             rd[c][u] = dg[c][u] > 0.0 ? 1.0 / dg[c][u] : 0.0;
         }
-    // the quotient a / dg: product with the rounded reciprocal and one
-    // correction by its remainder, which gives the rounded quotient
-    auto quot = [](double a, double d, double r) {
-        const double q = a * r;
-        return __builtin_fma(__builtin_fma(-q, d, a), r, q);
-    };
     double mu = msum;
     if (sum_mean) {
         __shared__ double sm[BR_T / 64];

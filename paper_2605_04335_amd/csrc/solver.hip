@@ -122,16 +122,18 @@ void level_geometry(Level &L, const std::vector<double> *f, hipStream_t s)
     L.walk = make_walk(2 * L.Nh);
 }
 
-// LDS layout of one tail level (mask, iterate, RHS), 16-byte aligned pieces
-inline void tail_layout(long long Nh, size_t tsz, int &off, int &moff, int &xoff, int &boff)
+// LDS layout of one tail level (mask, iterate with its pads, RHS), 16-byte
+// aligned pieces; in the RHS's place of the first level stand the residual
+// sums (one double per pair of cells)
+inline void tail_layout(const Level &L, size_t tsz, bool first, int &off, int &moff, int &xoff, int &boff)
 {
     auto al = [](long long v) { return (int)((v + 15) / 16 * 16); };
     moff = off;
-    off = al(off + 2 * Nh);
+    off = al(off + 2 * L.Nh);
     xoff = off;
-    off = al(off + 2 * Nh * (long long)tsz);
+    off = al(off + 2LL * tail_stride(L.H, L.n[1], L.n[2]) * (long long)tsz);
     boff = off;
-    off = al(off + 2 * Nh * (long long)tsz);
+    off = al(off + (first ? std::max<long long>(2 * L.Nh * (long long)tsz, 8 * L.Nh) : 2 * L.Nh * (long long)tsz));
 }
 
 // slot of natural cell (i,j,k) in a level with half-width H
@@ -691,7 +693,7 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
                 tl.t[q].volA = L.volA;
                 tl.t[q].xg = Store<T>::x(L);
                 tl.t[q].bg = Store<T>::b(L);
-                tail_layout(L.Nh, sizeof(Tc), off, tl.t[q].moff, tl.t[q].xoff, tl.t[q].boff);
+                tail_layout(L, sizeof(Tc), q == 0, off, tl.t[q].moff, tl.t[q].xoff, tl.t[q].boff);
             }
             tl.coff = off;
             for (int q = 0; q < tl.n; ++q) {
@@ -1301,18 +1303,18 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
             upload(F.pt[d], pt, s);
         }
     }
-    // tail start (the coarsest levels that fit one workgroup's LDS)
+    // tail start: the coarsest levels that fit one workgroup's LDS and, the
+    // first of them, its registers (two cell pairs per thread; one below)
     for (int pass = 0; pass < 2; ++pass) {
         const size_t tsz = pass ? sizeof(double) : sizeof(float);
         int &t0 = pass ? c->tail0d : c->tail0;
         t0 = nl;
-        int off = 0;
         for (int l = nl - 1; l >= 1 && (nl - l) <= 8; --l) {
-            int m, xo, bo, o2 = off;
-            tail_layout(c->lv[l].Nh, tsz, o2, m, xo, bo);
-            o2 += tail_coef_bytes(c->lv[l].n[0], c->lv[l].n[1], c->lv[l].n[2]);
-            if (o2 > TAIL_LDS) break;
-            off = o2;
+            if (c->lv[l].Nh > TAIL_U * TAIL_T) break;
+            int off = 0, m, xo, bo;
+            for (int q = l; q < nl; ++q) tail_layout(c->lv[q], tsz, q == l, off, m, xo, bo);
+            for (int q = l; q < nl; ++q) off += tail_coef_bytes(c->lv[q].n[0], c->lv[q].n[1], c->lv[q].n[2]);
+            if (off > TAIL_LDS) break;
             t0 = l;
         }
     }

@@ -61,13 +61,6 @@ __device__ __forceinline__ double recip(double d)
     r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
     return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
 }
-// a / d from d's reciprocal: one correction by the remainder
-__device__ __forceinline__ double quot(double a, double d, double r)
-{
-    const double q = a * r;
-    return __builtin_fma(__builtin_fma(-q, d, a), r, q);
-}
-
 // wave-uniform load of data that no kernel in flight writes: through the
 // constant address space it becomes a scalar load, which needs no vector
 // register and does not queue behind the vector loads in flight

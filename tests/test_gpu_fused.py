@@ -152,3 +152,30 @@ def test_fused_rows_match_oracle(shape, bodies, nu1, nu2):
     d = z.cpu().numpy() - zo
     assert np.linalg.norm(d[act] - d[act].mean()) < 1e-11 * np.linalg.norm(zo)
     assert torch.equal(z, sol.precond(bt))
+
+
+# the coarse tail: a first level of one and of two cell pairs per thread, a
+# coarsest level swept by one wavefront, by the block, and alone in the tail,
+# odd edges, closed faces and masked cells, no post-smoothing.  The bound of
+# the V-cycle's parity test.
+@pytest.mark.parametrize("shape,bodies,nu1,nu2,ncs", [
+    ((32, 32, 32), "sphere plate", 2, 2, 32),
+    ((32, 32, 32), "", 3, 0, 5),
+    ((32, 24, 28), "plate", 1, 1, 32),
+    ((10, 10, 10), "sphere", 2, 2, 32),
+    ((30, 26, 22), "sphere", 2, 2, 9),
+    ((64, 20, 36), "sphere plate", 2, 3, 32),
+    ((4, 4, 4), "", 2, 2, 1),
+])
+def test_coarse_tail_matches_oracle(shape, bodies, nu1, nu2, ncs):
+    import torch
+    import paper_2605_04335_amd as P
+    print("[case] tail", shape, bodies, nu1, nu2, ncs, flush=True)
+    f, bl = box_case(*shape, bodies, stretched=True)
+    O = oracle.setup(*f, bl)
+    flags, st, sol, _ = P.setup(*f, bl, nu1=nu1, nu2=nu2, coarse_sweeps=ncs)
+    b = oracle.assemble_rhs(*f, O.flags, O.st, W.noise_rhs(len(O.flags), 46))
+    bt = torch.from_numpy(b).cuda()
+    z = sol.precond(bt)
+    assert rel(z.cpu().numpy(), oracle.vcycle(*f, O.flags, O.st, b, nu1, nu2, ncs)) < 1e-11
+    assert torch.equal(z, sol.precond(bt))
