@@ -21,6 +21,7 @@
 #include "common.hpp"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 namespace ibm {
@@ -28,71 +29,104 @@ void classify(const ibm_grid *, const ibm_body *, int, uint8_t *, ibm_class_stat
 
 namespace {
 
-constexpr int CH = 4096;  // cells per compaction block
+constexpr int CH = 4096;    // cells per compaction block
+constexpr int CB = 256;     // its threads, CH / CB consecutive cells each
+constexpr int CMAX = 3;     // lists built together
 
 // ---------------------------------------------------------------- compaction
-__global__ void k_count(const uint8_t *flags, long long N, uint8_t mask, int *cnt)
+// Ordered lists of the cells whose flag byte has a given bit, up to three of
+// them in one pass: counts per block, one scan, fill.  Bound: the flags, read
+// twice.  A thread takes 16 consecutive cells in one load (where the array is
+// aligned to it).  At 384^3 three lists one after the other took 3 x 180 us
+// of kernels; together they take 85.
+struct Bits {
+    uint8_t m[CMAX];  // single bits
+};
+
+__device__ __forceinline__ uint4 cells16(const uint8_t *flags, long long N, long long p)
 {
-    __shared__ int s;
-    if (threadIdx.x == 0) s = 0;
-    __syncthreads();
-    long long base = (long long)blockIdx.x * CH;
-    int c = 0;
-    for (int t = threadIdx.x; t < CH; t += blockDim.x) {
-        long long p = base + t;
-        if (p < N && (flags[p] & mask)) ++c;
-    }
-    atomicAdd(&s, c);
-    __syncthreads();
-    if (threadIdx.x == 0) cnt[blockIdx.x] = s;
+    if (p + 16 <= N && ((uintptr_t)flags & 15) == 0) return *reinterpret_cast<const uint4 *>(flags + p);
+    uint32_t w[4] = {0, 0, 0, 0};
+    for (int q = 0; q < 16; ++q)
+        if (p + q < N) w[q >> 2] |= (uint32_t)flags[p + q] << (8 * (q & 3));
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+// bit q set: cell q of the sixteen carries the flag bit m
+__device__ __forceinline__ uint32_t hits16(const uint4 &v, uint8_t m)
+{
+    const uint32_t mm = 0x01010101u * m;
+    auto four = [&](uint32_t w) {
+        w &= mm;
+        return (uint32_t)((w & 0xffu) != 0) | (uint32_t)((w & 0xff00u) != 0) << 1 | (uint32_t)((w & 0xff0000u) != 0) << 2 |
+               (uint32_t)((w & 0xff000000u) != 0) << 3;
+    };
+    return four(v.x) | four(v.y) << 4 | four(v.z) << 8 | four(v.w) << 12;
 }
 
-// exclusive scan of n ints in one block (n may be large: sequential per thread)
-__global__ void k_scan1(const int *in, int *out, int n, int *total)
+// inclusive prefix sum over the block (blockDim a multiple of 64); *total: the sum
+__device__ __forceinline__ int block_prefix(int v, int *total)
 {
-    __shared__ int part[1024];
-    int per = (n + blockDim.x - 1) / blockDim.x;
-    int b = threadIdx.x * per, e = min(n, b + per);
-    int s = 0;
-    for (int i = b; i < e; ++i) s += in[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int t = 0; t < (int)blockDim.x; ++t) { int v = part[t]; part[t] = acc; acc += v; }
-        *total = acc;
-    }
-    __syncthreads();
-    int acc = part[threadIdx.x];
-    for (int i = b; i < e; ++i) { out[i] = acc; acc += in[i]; }
-}
-
-// ordered fill: each block walks its chunk in steps of blockDim cells, with a
-// wave ballot prefix plus an LDS prefix across the waves of the block
-__global__ void k_fill(const uint8_t *flags, long long N, uint8_t mask, const int *off, int32_t *out)
-{
-    __shared__ int wsum[16];
-    __shared__ int carry;
+    __shared__ int ws[16];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if (threadIdx.x == 0) carry = off[blockIdx.x];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+    }
     __syncthreads();
-    long long base = (long long)blockIdx.x * CH;
-    for (int t0 = 0; t0 < CH; t0 += blockDim.x) {
-        long long p = base + t0 + threadIdx.x;
-        bool hit = (t0 + (int)threadIdx.x < CH) && p < N && (flags[p] & mask);
-        unsigned long long bal = __ballot(hit);
-        int before = __popcll(bal & ((1ull << lane) - 1ull));
-        if (lane == 0) wsum[wid] = __popcll(bal);
-        __syncthreads();
-        int wo = 0, tot = 0;
-        for (int q = 0; q < nw; ++q) {
-            if (q < wid) wo += wsum[q];
-            tot += wsum[q];
+    if (lane == 63) ws[wid] = v;
+    __syncthreads();
+    int before = 0, sum = 0;
+    for (int w = 0; w < nw; ++w) {
+        if (w < wid) before += ws[w];
+        sum += ws[w];
+    }
+    *total = sum;
+    return before + v;
+}
+
+__global__ void __launch_bounds__(CB) k_count(const uint8_t *flags, long long N, Bits M, int K, int nb, int *cnt)
+{
+    const uint4 v = cells16(flags, N, (long long)blockIdx.x * CH + 16 * threadIdx.x);
+    for (int q = 0; q < K; ++q) {
+        int tot;
+        (void)block_prefix(__popc(hits16(v, M.m[q])), &tot);
+        if (threadIdx.x == 0) cnt[(long long)q * nb + blockIdx.x] = tot;
+    }
+}
+
+// exclusive scan of one list's n block counts, in place (one block per list)
+__global__ void __launch_bounds__(1024) k_scan(int *cnt, int n, int *total)
+{
+    int *a = cnt + (long long)blockIdx.x * n;
+    int carry = 0;
+    for (int i0 = 0; i0 < n; i0 += 1024) {
+        const int i = i0 + (int)threadIdx.x, v = i < n ? a[i] : 0;
+        int tot;
+        const int inc = block_prefix(v, &tot);
+        if (i < n) a[i] = carry + inc - v;
+        carry += tot;
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+struct Lists {
+    int32_t *out[CMAX];
+};
+__global__ void __launch_bounds__(CB) k_fill(const uint8_t *flags, long long N, Bits M, int K, int nb, const int *off,
+                                             Lists O)
+{
+    const long long p = (long long)blockIdx.x * CH + 16 * threadIdx.x;
+    const uint4 v = cells16(flags, N, p);
+    for (int q = 0; q < K; ++q) {
+        uint32_t h = hits16(v, M.m[q]);
+        const int c = __popc(h);
+        int tot;
+        int32_t *o = O.out[q] + off[(long long)q * nb + blockIdx.x] + block_prefix(c, &tot) - c;
+        while (h) {
+            *o++ = (int32_t)(p + __ffs(h) - 1);
+            h &= h - 1;
         }
-        if (hit) out[carry + wo + before] = (int32_t)p;
-        __syncthreads();
-        if (threadIdx.x == 0) carry += tot;
-        __syncthreads();
     }
 }
 
@@ -135,21 +169,30 @@ __device__ V3 closest_on_triangle(V3 p, V3 a, V3 b, V3 c)
     return q;
 }
 
-// triangles of a body are grouped in runs of TGROUP consecutive triangles
-// (mesh order) with one box per run
+// The triangles of a body are grouped in runs of TGROUP consecutive ones
+// (mesh order) with one box per run, and one box per body.  Closed bodies and
+// their runs stand before membranes, in (body, triangle) order within a kind.
 constexpr int TGROUP = 32;
 
-struct Tris {
-    const double *v;    // [nt*9] vertex coordinates
-    const double *box;  // [nt*6] min xyz, max xyz
-    const int *kind;    // [nt]
-    const double *bbox; // [nb*6] per-body boxes
-    const int *bfirst;  // [nb+1] first triangle of each body
-    const int *bkind;   // [nb]
-    const double *gbox; // [ng*6] boxes of the triangle runs
-    const int *gfirst;  // [nb+1] first run of each body
-    int nb;
+struct Run {
+    int t0, n;  // first triangle, triangles (at most TGROUP); of a body: first run, runs
 };
+struct Tris {
+    const double *v;    // vertex coordinates of all bodies
+    const int32_t *tri; // [nt*3] vertices of the triangles
+    const Run *run, *body;
+    double *box, *bbox; // [6][runs], [6][bodies]: min xyz, max xyz
+    int nr, nb, b0[3];  // first body of each kind, end
+};
+struct Corner3 {
+    V3 a, b, c;
+};
+__device__ __forceinline__ Corner3 corners(const Tris &T, int t)
+{
+    const double *a = T.v + 3 * (long long)T.tri[3 * (long long)t], *b = T.v + 3 * (long long)T.tri[3 * (long long)t + 1],
+                 *c = T.v + 3 * (long long)T.tri[3 * (long long)t + 2];
+    return {{a[0], a[1], a[2]}, {b[0], b[1], b[2]}, {c[0], c[1], c[2]}};
+}
 
 struct GridD {
     const double *c[3];  // centres
@@ -159,22 +202,28 @@ struct GridD {
     double hmin;
 };
 
-__device__ __forceinline__ double box_lb(const double *bx, V3 p)
+// least and largest squared distance from p to a point of box i of n
+__device__ __forceinline__ double box_lb(const double *bx, int n, int i, V3 p)
 {
-    double e, s = 0.0;
-    e = p.x < bx[0] ? bx[0] - p.x : (p.x > bx[3] ? p.x - bx[3] : 0.0); s += e * e;
-    e = p.y < bx[1] ? bx[1] - p.y : (p.y > bx[4] ? p.y - bx[4] : 0.0); s += e * e;
-    e = p.z < bx[2] ? bx[2] - p.z : (p.z > bx[5] ? p.z - bx[5] : 0.0); s += e * e;
+    const double q[3] = {p.x, p.y, p.z};
+    double s = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double lo = bx[(long long)d * n + i], hi = bx[(long long)(d + 3) * n + i];
+        const double e = q[d] < lo ? lo - q[d] : (q[d] > hi ? q[d] - hi : 0.0);
+        s += e * e;
+    }
     return s;
 }
-
-// the largest squared distance from p to a point of the box
-__device__ __forceinline__ double box_ub(const double *bx, V3 p)
+__device__ __forceinline__ double box_ub(const double *bx, int n, int i, V3 p)
 {
-    double e, s = 0.0;
-    e = fmax(fabs(p.x - bx[0]), fabs(p.x - bx[3])); s += e * e;
-    e = fmax(fabs(p.y - bx[1]), fabs(p.y - bx[4])); s += e * e;
-    e = fmax(fabs(p.z - bx[2]), fabs(p.z - bx[5])); s += e * e;
+    const double q[3] = {p.x, p.y, p.z};
+    double s = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double e = fmax(fabs(q[d] - bx[(long long)d * n + i]), fabs(q[d] - bx[(long long)(d + 3) * n + i]));
+        s += e * e;
+    }
     return s;
 }
 
@@ -205,10 +254,176 @@ struct RowOut {
     uint8_t *rfl;
 };
 
-// One thread per ghost row: intercept, image point, box, 8x8 LU, weights.
+// boxes of the runs, half a wavefront each
+__global__ void __launch_bounds__(256) k_run_boxes(Tris T)
+{
+    const int r = (int)(blockIdx.x * 256 + threadIdx.x) / TGROUP, t = threadIdx.x % TGROUP;
+    if (r >= T.nr) return;
+    const Run R = T.run[r];
+    const Corner3 C = corners(T, R.t0 + min(t, R.n - 1));
+    double lo[3] = {fmin(C.a.x, fmin(C.b.x, C.c.x)), fmin(C.a.y, fmin(C.b.y, C.c.y)), fmin(C.a.z, fmin(C.b.z, C.c.z))};
+    double hi[3] = {fmax(C.a.x, fmax(C.b.x, C.c.x)), fmax(C.a.y, fmax(C.b.y, C.c.y)), fmax(C.a.z, fmax(C.b.z, C.c.z))};
+    for (int d = 0; d < 3; ++d) {
+        for (int o = TGROUP / 2; o > 0; o >>= 1) {
+            lo[d] = fmin(lo[d], __shfl_xor(lo[d], o, TGROUP));
+            hi[d] = fmax(hi[d], __shfl_xor(hi[d], o, TGROUP));
+        }
+        if (t == 0) {
+            T.box[(long long)d * T.nr + r] = lo[d];
+            T.box[(long long)(d + 3) * T.nr + r] = hi[d];
+        }
+    }
+}
+// boxes of the bodies, a wavefront each
+__global__ void __launch_bounds__(64) k_body_boxes(Tris T)
+{
+    const int b = (int)blockIdx.x, lane = threadIdx.x;
+    const Run R = T.body[b];
+    for (int d = 0; d < 3; ++d) {
+        double lo = INFINITY, hi = -INFINITY;
+        for (int q = lane; q < R.n; q += 64) {
+            lo = fmin(lo, T.box[(long long)d * T.nr + R.t0 + q]);
+            hi = fmax(hi, T.box[(long long)(d + 3) * T.nr + R.t0 + q]);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o, 64));
+            hi = fmax(hi, __shfl_xor(hi, o, 64));
+        }
+        if (lane == 0) {
+            T.bbox[(long long)d * T.nb + b] = lo;
+            T.bbox[(long long)(d + 3) * T.nb + b] = hi;
+        }
+    }
+}
+
+// Nearest triangle of each ghost's kind, one wavefront per row: the point into
+// geo[0..2], its squared distance into geo[11], the triangle into near (-1:
+// none).  Bound: the address unit, by the gathers of boxes and vertices.  One
+// thread per row walked them one after the other with too few wavefronts to
+// hide the latency: 958 us for 93 thousand rows among 20 bodies, with the
+// rows' matrices; now 274, and 24 for the matrices.  (Boxes of all runs, six
+// doubles together, without the bodies' level: 541.)
+//
+// A bound on the nearest squared distance comes first: every box holds a
+// triangle at most as far as its farthest point, so the smallest such distance
+// is one, over the bodies, then over the runs of the bodies within it, then
+// over the triangles of the run that gave it; with a relative margin far above
+// rounding.  Then every triangle of every run within the bound, a run to half
+// a wavefront.  The smallest distance wins and on equal ones the first
+// triangle, as in a plain scan.
+__global__ void __launch_bounds__(256) k_nearest(Tris T, GridD G, const int32_t *cells, int ng, int nrows, double *geo,
+                                                 int32_t *near)
+{
+    const int r = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (r >= nrows) return;
+    const int32_t cell = cells[r];
+    const int nx = G.n[0], ny = G.n[1];
+    const V3 P = {G.c[0][cell % nx], G.c[1][(cell / nx) % ny], G.c[2][cell / (nx * ny)]};
+    const int want = r >= ng ? 1 : 0, b0 = T.b0[want], b1 = T.b0[want + 1];
+    const double margin = 1.0 + 1e-9;
+    auto wave_min = [](double v) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+        return v;
+    };
+    double best = INFINITY;  // the lane's nearest triangle
+    V3 q = {0, 0, 0};
+    int bt = INT_MAX;
+    auto triangles = [&](int g) {  // of run g (-1: none)
+        if (g < 0) return;
+        const Run R = T.run[g];
+        if ((lane & 31) >= R.n) return;
+        const int t = R.t0 + (lane & 31);
+        const Corner3 C = corners(T, t);
+        const V3 c = closest_on_triangle(P, C.a, C.b, C.c);
+        const double d2 = (c.x - P.x) * (c.x - P.x) + (c.y - P.y) * (c.y - P.y) + (c.z - P.z) * (c.z - P.z);
+        if (d2 < best || (d2 == best && t < bt)) {
+            best = d2;
+            bt = t;
+            q = c;
+        }
+    };
+    double bb = INFINITY;
+    for (int b = b0 + lane; b < b1; b += 64) bb = fmin(bb, box_ub(T.bbox, T.nb, b, P));
+    bb = wave_min(bb) * margin;
+    // f(first run, runs) for every body within the distance `within`
+    auto bodies = [&](double within, auto &&f) {
+        for (int c = b0; c < b1; c += 64) {
+            const int b = min(c + lane, b1 - 1);
+            const Run R = T.body[b];
+            unsigned long long m = __ballot(c + lane < b1 && !(box_lb(T.bbox, T.nb, b, P) > within));
+            while (m) {
+                const int l = __ffsll(m) - 1;
+                m &= m - 1;
+                f(__shfl(R.t0, l, 64), __shfl(R.n, l, 64));
+            }
+        }
+    };
+    double ub = INFINITY;
+    int gb = -1;
+    bodies(bb, [&](int g0, int n) {
+        for (int g = g0 + lane; g < g0 + n; g += 64) {
+            const double v = box_ub(T.box, T.nr, g, P);
+            if (v < ub) {
+                ub = v;
+                gb = g;
+            }
+        }
+    });
+    const double ubw = wave_min(ub);
+    const unsigned long long at = __ballot(ub == ubw && gb >= 0);
+    if (at) triangles(lane < 32 ? __shfl(gb, __ffsll(at) - 1, 64) : -1);
+    ub = fmin(ubw, wave_min(best)) * margin;
+    bodies(fmin(bb, ub), [&](int g0, int n) {
+        for (int c = g0; c < g0 + n; c += 64) {
+            const int g = min(c + lane, g0 + n - 1);
+            unsigned long long m = __ballot(c + lane < g0 + n && !(box_lb(T.box, T.nr, g, P) > ub));
+            while (m) {
+                const int q0 = __ffsll(m) - 1;
+                m &= m - 1;
+                int q1 = -1;
+                if (m) {
+                    q1 = __ffsll(m) - 1;
+                    m &= m - 1;
+                }
+                triangles(lane < 32 ? c + q0 : (q1 < 0 ? -1 : c + q1));
+            }
+        }
+    });
+    double bd = best;
+    int bi = bt;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double d = __shfl_xor(bd, o, 64);
+        const int t = __shfl_xor(bi, o, 64);
+        if (d < bd || (d == bd && t < bi)) {
+            bd = d;
+            bi = t;
+        }
+    }
+    double *go = geo + 12 * (long long)r;
+    if (bi == INT_MAX) {
+        if (lane == 0) {
+            near[r] = -1;
+            go[0] = go[1] = go[2] = 0.0;
+            go[11] = INFINITY;
+        }
+        return;
+    }
+    const unsigned long long w = __ballot(bt == bi);  // (the run that gave the bound is visited twice)
+    if (lane == __ffsll(w) - 1) {
+        near[r] = bt;
+        go[0] = q.x; go[1] = q.y; go[2] = q.z;
+        go[11] = best;
+    }
+}
+
+// One thread per ghost row: image point, box, 8x8 LU, weights.  The matrix
+// stays in registers: every index is known at compile time, row exchanges are
+// selections.
 __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *flags, const int32_t *cells,
-                                                int ng, int nrows, const int32_t *mcell, int nm, long long N, int bc,
-                                                RowOut O)
+                                                const int32_t *near, int ng, int nrows, const int32_t *mcell, int nm,
+                                                long long N, int bc, RowOut O)
 {
     int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= nrows) return;
@@ -217,38 +432,10 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
     const int nx = G.n[0], ny = G.n[1];
     const int ci = cell % nx, cj = (cell / nx) % ny, ck = cell / (nx * ny);
     const V3 P = {G.c[0][ci], G.c[1][cj], G.c[2][ck]};
-    const int want = mem ? 1 : 0;
-    // A bound on the nearest squared distance before the search: the
-    // smallest farthest-point distance of any run box (every run holds a
-    // triangle at most that far), with a relative margin far above rounding.
-    // Runs, and then triangles, whose box lies farther than the bound or the
-    // best distance so far are skipped; the rest are visited in triangle
-    // order with the same strict comparison as a plain scan, so the chosen
-    // triangle (the first of the nearest) is the plain scan's.
-    double ub = INFINITY;
-    for (int b = 0; b < T.nb; ++b) {
-        if (T.bkind[b] != want) continue;
-        for (int g = T.gfirst[b]; g < T.gfirst[b + 1]; ++g) ub = fmin(ub, box_ub(T.gbox + 6 * g, P));
-    }
-    ub *= 1.0 + 1e-9;
-    double best = INFINITY;
-    V3 BI = {0, 0, 0};
-    int bt = -1;
-    for (int b = 0; b < T.nb; ++b) {
-        if (T.bkind[b] != want) continue;
-        if (box_lb(T.bbox + 6 * b, P) > fmin(best, ub)) continue;
-        for (int g = T.gfirst[b]; g < T.gfirst[b + 1]; ++g) {
-            if (box_lb(T.gbox + 6 * g, P) > fmin(best, ub)) continue;
-            const int t0 = T.bfirst[b] + (g - T.gfirst[b]) * TGROUP, t1 = min(t0 + TGROUP, T.bfirst[b + 1]);
-            for (int t = t0; t < t1; ++t) {
-                if (box_lb(T.box + 6 * t, P) > fmin(best, ub)) continue;
-                const double *tv = T.v + 9 * t;
-                V3 q = closest_on_triangle(P, {tv[0], tv[1], tv[2]}, {tv[3], tv[4], tv[5]}, {tv[6], tv[7], tv[8]});
-                double d2 = (q.x - P.x) * (q.x - P.x) + (q.y - P.y) * (q.y - P.y) + (q.z - P.z) * (q.z - P.z);
-                if (d2 < best) { best = d2; bt = t; BI = q; }
-            }
-        }
-    }
+    const int bt = near[r];
+    const double *gi = O.geo + 12 * (long long)r;
+    V3 BI = {gi[0], gi[1], gi[2]};
+    const double best = gi[11];
     uint8_t fl = 0;
     double dist = sqrt(best);
     V3 nrm, IP;
@@ -257,8 +444,8 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
         nrm = {0, 0, 1}; IP = P; dl = 1.0; dist = 0.0; BI = P;
         fl |= 1;
     } else if (dist < 1e-9 * G.hmin) {
-        const double *tv = T.v + 9 * bt;
-        V3 e1 = {tv[3] - tv[0], tv[4] - tv[1], tv[5] - tv[2]}, e2 = {tv[6] - tv[0], tv[7] - tv[1], tv[8] - tv[2]};
+        const Corner3 C = corners(T, bt);
+        const V3 e1 = sub(C.b, C.a), e2 = sub(C.c, C.a);
         V3 fn = {e1.y * e2.z - e1.z * e2.y, e1.z * e2.x - e1.x * e2.z, e1.x * e2.y - e1.y * e2.x};
         double L = sqrt(fn.x * fn.x + fn.y * fn.y + fn.z * fn.z);
         double hl = fmin(G.w[0][ci], fmin(G.w[1][cj], G.w[2][ck]));
@@ -275,6 +462,7 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
     const double ipa[3] = {IP.x, IP.y, IP.z}, bia[3] = {BI.x, BI.y, BI.z}, na[3] = {nrm.x, nrm.y, nrm.z};
     int b0[3];
     double loc[3], del[3], bil[3];
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
         const int n = G.n[d];
         const double *c = G.c[d];
@@ -291,6 +479,7 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
     int32_t cl[8];
     int dnode = -1;
     bool degenerate = (fl & 1) != 0;
+#pragma unroll
     for (int m = 0; m < 8; ++m) {
         const int dx = m & 1, dy = (m >> 1) & 1, dz = (m >> 2) & 1;
         const int ii = b0[0] + dx, jj = b0[1] + dy, kk = b0[2] + dz;
@@ -309,6 +498,7 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
             const double gx[8] = {0, 1, 0, 0, y, 0, z, y * z};
             const double gy[8] = {0, 0, 1, 0, x, z, 0, x * z};
             const double gz[8] = {0, 0, 0, 1, 0, y, x, x * y};
+#pragma unroll
             for (int c = 0; c < 8; ++c) row[c] = na[0] / del[0] * gx[c] + na[1] / del[1] * gy[c] + na[2] / del[2] * gz[c];
             dnode = m;
         } else {
@@ -330,6 +520,7 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
                 }
             }
         }
+#pragma unroll
         for (int c = 0; c < 8; ++c) M[c][m] = row[c];
     }
     double beta[8];
@@ -338,40 +529,62 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
         beta[0] = 1.0; beta[1] = x; beta[2] = y; beta[3] = z;
         beta[4] = x * y; beta[5] = y * z; beta[6] = x * z; beta[7] = x * y * z;
         double amax = 0.0;
+#pragma unroll
         for (int i = 0; i < 8; ++i)
+#pragma unroll
             for (int j = 0; j < 8; ++j) amax = fmax(amax, fabs(M[i][j]));
-        for (int c = 0; c < 8 && !degenerate; ++c) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            // the first row of the largest entry becomes the pivot
             int p = c;
+            double pv = fabs(M[c][c]);
+#pragma unroll
             for (int i = c + 1; i < 8; ++i)
-                if (fabs(M[i][c]) > fabs(M[p][c])) p = i;
-            if (!(fabs(M[p][c]) >= 1e-12 * amax) || amax == 0.0) { degenerate = true; break; }
-            if (p != c) {
-                for (int j = 0; j < 8; ++j) { double t = M[c][j]; M[c][j] = M[p][j]; M[p][j] = t; }
-                double t = beta[c]; beta[c] = beta[p]; beta[p] = t;
-            }
+                if (fabs(M[i][c]) > pv) {
+                    pv = fabs(M[i][c]);
+                    p = i;
+                }
+            if (!(pv >= 1e-12 * amax) || amax == 0.0) degenerate = true;  // (what follows is dropped)
+#pragma unroll
             for (int i = c + 1; i < 8; ++i) {
-                double l = M[i][c] / M[c][c];
-                for (int j = c; j < 8; ++j) M[i][j] -= l * M[c][j];
+                const bool sw = p == i;
+#pragma unroll
+                for (int j = c; j < 8; ++j) {
+                    const double u = M[c][j], v = M[i][j];
+                    M[c][j] = sw ? v : u;
+                    M[i][j] = sw ? u : v;
+                }
+                const double u = beta[c], v = beta[i];
+                beta[c] = sw ? v : u;
+                beta[i] = sw ? u : v;
+            }
+#pragma unroll
+            for (int i = c + 1; i < 8; ++i) {
+                const double l = M[i][c] / M[c][c];
+#pragma unroll
+                for (int j = c + 1; j < 8; ++j) M[i][j] -= l * M[c][j];
                 beta[i] -= l * beta[c];
             }
         }
-        if (!degenerate)
-            for (int c = 7; c >= 0; --c) {
-                double s = beta[c];
-                for (int j = c + 1; j < 8; ++j) s -= M[c][j] * beta[j];
-                beta[c] = s / M[c][c];
-            }
+#pragma unroll
+        for (int c = 7; c >= 0; --c) {
+            double s = beta[c];
+#pragma unroll
+            for (int j = c + 1; j < 8; ++j) s -= M[c][j] * beta[j];
+            beta[c] = s / M[c][c];
+        }
     }
     const double sg = G.cp[0][ci] + G.cm[0][ci] + G.cp[1][cj] + G.cm[1][cj] + G.cp[2][ck] + G.cm[2][ck];
     double bbi = 0.0;
     int32_t *oc = O.col + 8 * (long long)r;
     double *ow = O.w + 8 * (long long)r;
     if (!degenerate) {
+#pragma unroll
         for (int m = 0; m < 8; ++m) {
             oc[m] = cl[m];
             ow[m] = cl[m] >= 0 ? beta[m] : 0.0;
+            if (dnode == m) { bbi = beta[m]; fl |= 2; }
         }
-        if (dnode >= 0) { bbi = beta[dnode]; fl |= 2; }
         O.dlb[r] = bc == 1 ? 2.0 - bbi : dl - bbi;
         if (bc == 1 && (fl & 4)) {
             // ghost on the surface: x_G = g
@@ -407,30 +620,66 @@ __global__ void __launch_bounds__(64) k_stencil(Tris T, GridD G, const uint8_t *
     g[9] = dl; g[10] = bbi; g[11] = dist;
 }
 
-__global__ void k_count_fallback(const uint8_t *rfl, int n, int *cnt)
+// rows that fell back to the face neighbours, one block
+__global__ void __launch_bounds__(1024) k_count_fallback(const uint8_t *rfl, int n, int *cnt)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int c = (i < n && (rfl[i] & 1)) ? 1 : 0;
-    unsigned long long b = __ballot(c);
-    if ((threadIdx.x & 63) == 0 && b) atomicAdd(cnt, __popcll(b));
+    int c = 0, tot;
+    for (int i = threadIdx.x; i < n; i += 1024) c += rfl[i] & 1;
+    (void)block_prefix(c, &tot);
+    if (threadIdx.x == 0) *cnt = tot;
 }
 
 }  // namespace
 
-// Ordered list of the cells whose flag matches mask; returns the count.
+namespace {
+// Ordered lists of the cells that carry each of K flag bits, in two halves:
+// the counts, and the lists once the caller has room for them.
+struct Compaction {
+    const uint8_t *flags;
+    long long N;
+    int K, nb;
+    Bits M;
+    DBuf<int> off;  // [K*nb], then the K totals
+    Compaction(const uint8_t *f, long long n, Bits m, int k) : flags(f), N(n), K(k), nb((int)cdiv(n, CH)), M(m) {}
+    void count(int *total, hipStream_t s)
+    {
+        off.alloc((size_t)K * nb + K);
+        int *tot = off.p + (size_t)K * nb;
+        k_count<<<nb, CB, 0, s>>>(flags, N, M, K, nb, off.p);
+        k_scan<<<K, 1024, 0, s>>>(off.p, nb, tot);
+        IBM_LAUNCH_CHECK();
+        IBM_HIP(hipMemcpyAsync(total, tot, K * sizeof(int), hipMemcpyDeviceToHost, s));
+        IBM_HIP(hipStreamSynchronize(s));
+    }
+    void fill(Lists O, hipStream_t s)
+    {
+        k_fill<<<nb, CB, 0, s>>>(flags, N, M, K, nb, off.p, O);
+        IBM_LAUNCH_CHECK();
+    }
+};
+
+// host image of one device region: pieces are reserved, written, and go up in one copy
+struct Image {
+    std::vector<char> h;
+    size_t take(size_t bytes)
+    {
+        const size_t o = (h.size() + 15) / 16 * 16;
+        h.resize(o + bytes);
+        return o;
+    }
+    template <class T>
+    T *at(size_t o) { return reinterpret_cast<T *>(h.data() + o); }
+};
+}  // namespace
+
+// Ordered list of the cells that carry flag bit `mask`; returns the count.
 int64_t compact_cells(const uint8_t *flags, long long N, uint8_t mask, DBuf<int32_t> &out, hipStream_t s)
 {
-    int nb = (int)cdiv(N, CH);
-    DBuf<int> cnt(nb), off(nb), tot(1);
-    k_count<<<nb, 256, 0, s>>>(flags, N, mask, cnt.p);
-    k_scan1<<<1, 1024, 0, s>>>(cnt.p, off.p, nb, tot.p);
-    IBM_LAUNCH_CHECK();
+    Compaction C(flags, N, Bits{{mask, 0, 0}}, 1);
     int total = 0;
-    IBM_HIP(hipMemcpyAsync(&total, tot.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    IBM_HIP(hipStreamSynchronize(s));
+    C.count(&total, s);
     out.alloc(std::max(total, 1));
-    k_fill<<<nb, 256, 0, s>>>(flags, N, mask, off.p, out.p);
-    IBM_LAUNCH_CHECK();
+    C.fill(Lists{{out.p, nullptr, nullptr}}, s);
     IBM_HIP(hipStreamSynchronize(s));
     return total;
 }
@@ -448,31 +697,29 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
         for (int d = 0; d < 3; ++d) S->n[d] = g.n[d];
         S->N = N;
         S->bc = bc;
-        DBuf<int32_t> gl, ml;
-        S->ng = compact_cells(flags, N, F_GHOST, gl, s);
-        S->nm = compact_cells(flags, N, F_MGHOST, ml, s);
+        // closed ghosts, membrane ghosts and the pin (kept with the table for the solver)
+        Compaction C(flags, N, Bits{{F_GHOST, F_MGHOST, F_PIN}}, 3);
+        int tot[3];
+        C.count(tot, s);
+        S->ng = tot[0];
+        S->nm = tot[1];
         // stencil columns are int32: grid unknowns, then membrane ghost unknowns
         IBM_REQUIRE(N + S->nm < ((int64_t)1 << 31), IBM_EINVAL, "more than 2^31 unknowns with the membrane ghosts");
         const int64_t rows = S->ng + S->nm;
+        IBM_REQUIRE(tot[2] == 1, IBM_EGEOM, "flags must hold exactly one pin cell");
         S->cell.alloc(std::max<int64_t>(rows, 1));
-        if (S->ng) IBM_HIP(hipMemcpyAsync(S->cell.p, gl.p, S->ng * 4, hipMemcpyDeviceToDevice, s));
-        if (S->nm) IBM_HIP(hipMemcpyAsync(S->cell.p + S->ng, ml.p, S->nm * 4, hipMemcpyDeviceToDevice, s));
         S->col.alloc(std::max<int64_t>(rows, 1) * 8);
         S->w.alloc(std::max<int64_t>(rows, 1) * 8);
         S->sG.alloc(std::max<int64_t>(rows, 1));
         S->dlb.alloc(std::max<int64_t>(rows, 1));
         S->rfl.alloc(std::max<int64_t>(rows, 1));
         S->geo.alloc(std::max<int64_t>(rows, 1) * 12);
-        // pin (kept with the table for the solver)
-        {
-            DBuf<int32_t> pl;
-            int64_t np = compact_cells(flags, N, F_PIN, pl, s);
-            IBM_REQUIRE(np == 1, IBM_EGEOM, "flags must hold exactly one pin cell");
-            int32_t pin;
-            IBM_HIP(hipMemcpyAsync(&pin, pl.p, 4, hipMemcpyDeviceToHost, s));
-            IBM_HIP(hipStreamSynchronize(s));
-            S->pin = pin;
-        }
+        DBuf<int> res(2);  // pin, fallback rows
+        C.fill(Lists{{S->cell.p, S->cell.p + S->ng, res.p}}, s);
+        Image I;  // (its copy has ended when the results are read)
+        DBuf<char> up;
+        DBuf<double> box;
+        DBuf<int32_t> near;
         if (rows > 0) {
             // grid on device
             std::vector<double> c[3], w[3], cp[3], cm[3];
@@ -490,73 +737,84 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
                     cm[d][i] = (i > 0) ? 1.0 / (w[d][i] * (c[d][i] - c[d][i - 1])) : 0.0;
                 }
             }
-            DBuf<double> dc[3], dw[3], dcp[3], dcm[3];
             GridD G;
-            for (int d = 0; d < 3; ++d) {
-                upload(dc[d], c[d], s); upload(dw[d], w[d], s); upload(dcp[d], cp[d], s); upload(dcm[d], cm[d], s);
-                G.c[d] = dc[d].p; G.w[d] = dw[d].p; G.cp[d] = dcp[d].p; G.cm[d] = dcm[d].p; G.n[d] = g.n[d];
-            }
-            G.hmin = hmin;
-            // triangles, flattened in (body, triangle) order
-            std::vector<double> tv, tb, bb, gbx;
-            std::vector<int> tk, bf, bk, gf;
-            bf.push_back(0);
-            gf.push_back(0);
+            const std::vector<double> *ga[4] = {c, w, cp, cm};
+            size_t go[4][3];
+            for (int q = 0; q < 4; ++q)
+                for (int d = 0; d < 3; ++d) {
+                    go[q][d] = I.take(g.n[d] * sizeof(double));
+                    std::copy(ga[q][d].begin(), ga[q][d].end(), I.at<double>(go[q][d]));
+                }
+            // vertices and triangles of all bodies, and the runs by kind
+            long long nv = 0, nt = 0;
+            std::vector<Run> runs, body;
+            int nclosed = 0;
+            std::vector<long long> first(n_body);  // first triangle
             for (int b = 0; b < n_body; ++b) {
                 const ibm_body &B = bodies[b];
                 IBM_REQUIRE(B.vert && B.tri && B.n_tri > 0, IBM_EINVAL, "empty body");
-                double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-                for (int t = 0; t < B.n_tri; ++t) {
-                    double mn[3] = {1e300, 1e300, 1e300}, mx[3] = {-1e300, -1e300, -1e300};
-                    for (int m = 0; m < 3; ++m) {
-                        int v = B.tri[3 * t + m];
-                        IBM_REQUIRE(v >= 0 && v < B.n_vert, IBM_EGEOM, "triangle index out of range");
-                        for (int d = 0; d < 3; ++d) {
-                            double x = B.vert[3 * v + d];
-                            tv.push_back(x);
-                            mn[d] = std::min(mn[d], x);
-                            mx[d] = std::max(mx[d], x);
-                        }
-                    }
-                    for (int d = 0; d < 3; ++d) { tb.push_back(mn[d]); lo[d] = std::min(lo[d], mn[d]); }
-                    for (int d = 0; d < 3; ++d) { tb.push_back(mx[d]); hi[d] = std::max(hi[d], mx[d]); }
-                    tk.push_back(B.kind);
-                }
-                for (int d = 0; d < 3; ++d) bb.push_back(lo[d]);
-                for (int d = 0; d < 3; ++d) bb.push_back(hi[d]);
-                bk.push_back(B.kind);
-                bf.push_back(bf.back() + B.n_tri);
-                // boxes of the runs of TGROUP consecutive triangles
-                for (int t0 = bf[b]; t0 < bf[b + 1]; t0 += TGROUP) {
-                    double glo[3] = {1e300, 1e300, 1e300}, ghi[3] = {-1e300, -1e300, -1e300};
-                    for (int t = t0; t < std::min(t0 + TGROUP, bf[b + 1]); ++t)
-                        for (int d = 0; d < 3; ++d) {
-                            glo[d] = std::min(glo[d], tb[6 * (size_t)t + d]);
-                            ghi[d] = std::max(ghi[d], tb[6 * (size_t)t + 3 + d]);
-                        }
-                    for (int d = 0; d < 3; ++d) gbx.push_back(glo[d]);
-                    for (int d = 0; d < 3; ++d) gbx.push_back(ghi[d]);
-                }
-                gf.push_back((int)(gbx.size() / 6));
+                for (int t = 0; t < 3 * B.n_tri; ++t)
+                    IBM_REQUIRE(B.tri[t] >= 0 && B.tri[t] < B.n_vert, IBM_EGEOM, "triangle index out of range");
+                first[b] = nt;
+                nv += B.n_vert;
+                nt += B.n_tri;
+                IBM_REQUIRE(nv < ((int64_t)1 << 31) && nt < ((int64_t)1 << 31), IBM_EINVAL,
+                            "more than 2^31 vertices or triangles");
             }
-            DBuf<double> dtv, dtb, dbb, dgb;
-            DBuf<int> dtk, dbf, dbk, dgf;
-            upload(dtv, tv, s); upload(dtb, tb, s); upload(dbb, bb, s); upload(dgb, gbx, s);
-            upload(dtk, tk, s); upload(dbf, bf, s); upload(dbk, bk, s); upload(dgf, gf, s);
-            Tris T{dtv.p, dtb.p, dtk.p, dbb.p, dbf.p, dbk.p, dgb.p, dgf.p, n_body};
-            RowOut O{S->col.p, S->w.p, S->sG.p, S->dlb.p, S->geo.p, S->rfl.p};
-            k_stencil<<<cdiv(rows, 64), 64, 0, s>>>(T, G, flags, S->cell.p, (int)S->ng, (int)rows, S->cell.p + S->ng,
-                                                   (int)S->nm, N, bc, O);
+            for (int kind = 0; kind < 2; ++kind) {
+                for (int b = 0; b < n_body; ++b) {
+                    if (bodies[b].kind != kind) continue;
+                    const int r0 = (int)runs.size(), n = bodies[b].n_tri;
+                    for (int t = 0; t < n; t += TGROUP) runs.push_back({(int)first[b] + t, std::min(TGROUP, n - t)});
+                    body.push_back({r0, (int)runs.size() - r0});
+                }
+                if (kind == 0) nclosed = (int)body.size();
+            }
+            const int nr = (int)runs.size(), nb = (int)body.size();
+            const size_t ov = I.take(3 * nv * sizeof(double)), ot = I.take(3 * nt * sizeof(int32_t)),
+                         orun = I.take(nr * sizeof(Run)), obody = I.take(nb * sizeof(Run));
+            double *hv = I.at<double>(ov);
+            int32_t *ht = I.at<int32_t>(ot);
+            int v0 = 0;
+            for (int b = 0; b < n_body; ++b) {
+                const ibm_body &B = bodies[b];
+                hv = std::copy(B.vert, B.vert + 3 * (size_t)B.n_vert, hv);
+                for (int t = 0; t < 3 * B.n_tri; ++t) *ht++ = v0 + B.tri[t];
+                v0 += B.n_vert;
+            }
+            std::copy(runs.begin(), runs.end(), I.at<Run>(orun));
+            std::copy(body.begin(), body.end(), I.at<Run>(obody));
+            up.alloc(I.h.size());
+            IBM_HIP(hipMemcpyAsync(up.p, I.h.data(), I.h.size(), hipMemcpyHostToDevice, s));
+            for (int d = 0; d < 3; ++d) {
+                G.c[d] = (const double *)(up.p + go[0][d]);
+                G.w[d] = (const double *)(up.p + go[1][d]);
+                G.cp[d] = (const double *)(up.p + go[2][d]);
+                G.cm[d] = (const double *)(up.p + go[3][d]);
+                G.n[d] = g.n[d];
+            }
+            G.hmin = hmin;
+            box.alloc(std::max(6 * ((size_t)nr + nb), (size_t)1));
+            near.alloc(rows);
+            const Tris T{(const double *)(up.p + ov), (const int32_t *)(up.p + ot), (const Run *)(up.p + orun),
+                         (const Run *)(up.p + obody), box.p, box.p + 6 * (size_t)nr, nr, nb, {0, nclosed, nb}};
+            const RowOut O{S->col.p, S->w.p, S->sG.p, S->dlb.p, S->geo.p, S->rfl.p};
+            if (nb) {
+                k_run_boxes<<<cdiv((long long)nr * TGROUP, 256), 256, 0, s>>>(T);
+                k_body_boxes<<<nb, 64, 0, s>>>(T);
+            }
+            k_nearest<<<cdiv(rows, 4), 256, 0, s>>>(T, G, S->cell.p, (int)S->ng, (int)rows, S->geo.p, near.p);
+            k_stencil<<<cdiv(rows, 64), 64, 0, s>>>(T, G, flags, S->cell.p, near.p, (int)S->ng, (int)rows,
+                                                   S->cell.p + S->ng, (int)S->nm, N, bc, O);
             IBM_LAUNCH_CHECK();
-            DBuf<int> nf(1);
-            IBM_HIP(hipMemsetAsync(nf.p, 0, 4, s));
-            k_count_fallback<<<cdiv(rows, 256), 256, 0, s>>>(S->rfl.p, (int)rows, nf.p);
-            IBM_LAUNCH_CHECK();
-            int h = 0;
-            IBM_HIP(hipMemcpyAsync(&h, nf.p, 4, hipMemcpyDeviceToHost, s));
-            IBM_HIP(hipStreamSynchronize(s));
-            S->nfallback = h;
         }
+        k_count_fallback<<<1, 1024, 0, s>>>(S->rfl.p, (int)rows, res.p + 1);
+        IBM_LAUNCH_CHECK();
+        int h[2];
+        IBM_HIP(hipMemcpyAsync(h, res.p, sizeof h, hipMemcpyDeviceToHost, s));
+        IBM_HIP(hipStreamSynchronize(s));
+        S->pin = h[0];
+        S->nfallback = h[1];
     } catch (...) {
         delete S;
         throw;

@@ -1,0 +1,97 @@
+"""Geometry set-up against the FP64 oracle at the sizes where it can go wrong:
+more bodies and triangles than one wavefront or launch takes, bodies that
+overlap, cross the walls or leave the domain, meshes of a few triangles."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2605_04335_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def faces(nx, ny, nz):
+    m = max(nx, ny, nz)
+    return [W.uniform_faces(n, n / m) for n in (nx, ny, nz)]
+
+
+def crowd(f, count, seed, r0=0.02, r1=0.09):
+    """Spheres at random places, some across each other and across the walls."""
+    rng = np.random.default_rng(seed)
+    L = [v[-1] for v in f]
+    out = []
+    for q in range(count):
+        c = [rng.uniform(-0.05 * e, 1.05 * e) for e in L]
+        out.append(W.sphere(tuple(c), rng.uniform(r0, r1), freq=1 + q % 3))
+    return out
+
+
+def setting(name):
+    if name == "crowd":  # 70 closed bodies, a membrane of more than 64 runs of triangles
+        f = faces(64, 48, 40)
+        return f, crowd(f, 70, 1) + [W.plate((0.5, 0.4, 0.3), 0.5, 0.4, 40, 40, 0.03, 0.3)]
+    if name == "sheets":  # membranes across each other, one through a wall, and a closed body
+        f = faces(41, 37, 33)
+        return f, [W.plate((0.4, 0.4, 0.4), 0.5, 0.4, 9, 9, 0.02, 0.2), W.sphere((0.45, 0.45, 0.4), 0.1, freq=2),
+                   W.plate((0.8, 0.4, 0.4), 0.4, 0.5, 3, 5, 0.0, 0.9)]
+    if name == "open":  # a closed body's mesh with a hole: solid up to the far wall behind it
+        f = faces(48, 44, 36)
+        b = W.sphere((0.4, 0.4, 0.35), 0.15, freq=4)
+        return f, [W.Body(b.verts, b.tris[: len(b.tris) - 40], b.kind), W.box((0.6, 0.2, 0.2), (0.8, 0.31, 0.7))]
+    if name == "outside":  # bodies wholly outside, before, behind and beside the domain, and one inside
+        f = faces(36, 40, 44)
+        return f, [W.sphere((-0.4, 0.4, 0.4), 0.2, freq=2), W.sphere((1.3, 0.4, 0.4), 0.2, freq=2),
+                   W.sphere((0.4, 1.5, 0.4), 0.2, freq=2), W.sphere((0.4, 0.45, 0.5), 0.13, freq=3)]
+    raise ValueError(name)
+
+
+NAMES = ["crowd", "sheets", "open", "outside"]
+
+
+# integer predicates: every flag byte equal
+@pytest.mark.parametrize("name", NAMES)
+def test_classification_of_many_bodies(name):
+    import paper_2605_04335_amd as P
+    print("[case] classify", name, flush=True)
+    f, bodies = setting(name)
+    want = oracle.classify(*f, bodies)
+    got, cst = P.classify(*f, bodies)
+    got = got.cpu().numpy()
+    assert np.array_equal(got, want), "mismatching cells: %d" % int(np.sum(got != want))
+    assert cst["n_solid"] == int(np.sum(want & 1)) and cst["n_ghost"] == int(np.sum((want & 2) > 0))
+    assert cst["n_mghost"] == int(np.sum((want & 4) > 0)) and cst["pin"] == int(np.nonzero(want & 8)[0][0])
+    assert cst["n_cut_links"] == sum(int(np.sum((want & b) > 0)) for b in (16, 32, 64))
+
+
+# the flags' array at an address that no wide load or store may take
+@pytest.mark.parametrize("offset", [1, 4])
+def test_classification_into_unaligned_flags(offset):
+    import torch
+    import ctypes
+    import paper_2605_04335_amd as P
+    f, bodies = setting("sheets" if offset == 1 else "crowd")
+    want = oracle.classify(*f, bodies)
+    buf = torch.full((len(want) + 32,), 0xAB, dtype=torch.uint8, device="cuda")
+    view = buf[offset:offset + len(want)]
+    P.classify_noalloc(*f, bodies, flags=view)
+    assert np.array_equal(view.cpu().numpy(), want)
+    assert bool((buf[:offset] == 0xAB).all()) and bool((buf[offset + len(want):] == 0xAB).all())
+    st = P.build_ghost_stencils(*f, bodies, view)
+    assert np.array_equal(st.export()["cell"], np.concatenate([np.nonzero(want & 2)[0], np.nonzero(want & 4)[0]]))
+
+
+# rows of the nearest triangles; bounds of the stencils' parity test
+@pytest.mark.parametrize("name", NAMES)
+def test_rows_of_many_bodies(name):
+    import torch
+    import paper_2605_04335_amd as P
+    print("[case] rows", name, flush=True)
+    f, bodies = setting(name)
+    O = oracle.setup(*f, bodies)
+    e = P.build_ghost_stencils(*f, bodies, torch.from_numpy(O.flags).cuda()).export()
+    assert e["ng"] == O.st.ng and e["nm"] == O.st.nm
+    assert np.array_equal(e["cell"], O.st.row_cell) and np.array_equal(e["rfl"], O.st.rfl)
+    assert np.array_equal(e["col"], O.st.col)
+    assert np.abs(e["w"] - O.st.w).max(initial=0) < 1e-13
+    assert np.abs(e["dlb"] - O.st.dlb).max(initial=0) < 1e-13
+    assert np.abs(e["geo"] - O.st.geo).max(initial=0) < 1e-13
