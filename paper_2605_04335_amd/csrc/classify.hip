@@ -9,11 +9,15 @@
 // to the triangle for which that edge is "top-left" (d_w < 0, or d_w == 0 and
 // d_u > 0), the same as perturbing the ray by (+e, +e^2).
 //
-// GPU form: one thread per triangle walks the rays its projected bounding box
-// covers, finds the first cell beyond the crossing by binary search and flips
-// one bit of a toggle bitset with an integer atomic XOR; one thread per ray
-// then turns toggles into parity.  This file is compiled with
-// -ffp-contract=off so that the quantisation rounds exactly as written.
+// GPU form: sixteen lanes per triangle walk the rays its projected bounding
+// box covers, find the first cell beyond the crossing by binary search and flip
+// one bit of a toggle bitset with an integer atomic XOR; one wavefront per ray
+// then turns toggles into parity.  A closed body's toggles cover its own box of
+// cells, so that many bodies share one launch of each kind and one bitset.
+// Twenty bodies at 384^3, body after body with a bitset of the whole grid and
+// one thread per triangle and per ray: 2.2 ms of kernels and 46 copies; now
+// 34 us and one copy.  This file is compiled with -ffp-contract=off so that the quantisation, here on the
+// host and there on the device, rounds exactly as written.
 
 #include "common.hpp"
 
@@ -47,26 +51,11 @@ struct Lat {
     double S;
 };
 
-__device__ __forceinline__ long long qnt(double v, double lo, double S)
+__host__ __device__ __forceinline__ long long qnt(double v, double lo, double S)
 {
     double t = (v - lo) * S;
     t = t + 0.5;
     return (long long)floor(t);
-}
-
-__global__ void k_quant_centres(const double *f, int n, double lo, double S, long long *q)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) q[i] = qnt(0.5 * (f[i] + f[i + 1]), lo, S);
-}
-
-__global__ void k_quant_verts(const double *v, int nv, Lat L, long long *q)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nv * 3) {
-        int d = i % 3;
-        q[i] = qnt(v[i], L.lo[d], L.S);
-    }
 }
 
 __global__ void k_fill_u32(uint32_t *a, long long n, uint32_t v)
@@ -104,27 +93,43 @@ __device__ __forceinline__ int lower_bound_ll(const long long *a, int n, long lo
     return lo;
 }
 
-struct RayArgs {
+// One body of a launch.  Closed: its toggles are one bit per cell of its box
+// [at, at + ext), x fastest, from word w0 of the bitset; every cell that a
+// crossing of the body can toggle lies in the box.
+struct RayBody {
+    const double *v;     // vertices
+    const int32_t *tri;
+    int nt, closed;
+    int at[3], ext[3];
+    long long w0;
+};
+constexpr int RAY_BODIES = 40;  // per launch: the descriptions travel as a kernel argument (3 of 4 KiB)
+struct RayBatch {
+    Lat lat;
     const long long *qc[3];  // lattice centres per axis
     int n[3];
-    const long long *qv;     // lattice vertices of the body
-    const int32_t *tri;      // triangles of the body
-    int nt;
-    int d;                   // ray axis
-    int mode;                // 0 closed parity toggles at the first cell beyond; 1 cut-link toggles
-    uint32_t *bits;          // toggle bitset over cells
-    uint8_t *has;            // per-ray "touched" marker (closed mode)
+    uint32_t *tog, *cut[3];
+    RayBody body[RAY_BODIES];
 };
+constexpr int RAY_LANES = 16;  // per triangle
 
-// One thread per triangle: every covered ray flips the bit of the first cell
-// whose centre lies strictly beyond the crossing (closed mode), or the link
-// just before it (membrane mode).
-__global__ void k_rays(RayArgs A)
+// Triangles of body blockIdx.y along axis blockIdx.z (closed bodies: x only):
+// every covered ray flips the bit of the first cell whose centre lies strictly
+// beyond the crossing (closed), or the link just before it (membrane).
+__global__ void __launch_bounds__(256) k_rays(RayBatch A)
 {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= A.nt) return;
-    const int d = A.d, u = (d + 1) % 3, w = (d + 2) % 3;
-    const long long *P0 = A.qv + 3 * A.tri[3 * t], *P1 = A.qv + 3 * A.tri[3 * t + 1], *P2 = A.qv + 3 * A.tri[3 * t + 2];
+    const RayBody &B = A.body[blockIdx.y];
+    const int d = (int)blockIdx.z;
+    if (B.closed && d > 0) return;
+    const int t = (int)((blockIdx.x * 256u + threadIdx.x) / RAY_LANES), lane = threadIdx.x % RAY_LANES;
+    if (t >= B.nt) return;
+    const int u = (d + 1) % 3, w = (d + 2) % 3;
+    long long P[3][3];
+    for (int m = 0; m < 3; ++m) {
+        const double *v = B.v + 3 * (long long)B.tri[3 * (long long)t + m];
+        for (int c = 0; c < 3; ++c) P[m][c] = qnt(v[c], A.lat.lo[c], A.lat.S);
+    }
+    const long long *P0 = P[0], *P1 = P[1], *P2 = P[2];
     long long e1[3], e2[3], Nn[3];
     for (int c = 0; c < 3; ++c) { e1[c] = P1[c] - P0[c]; e2[c] = P2[c] - P0[c]; }
     Nn[0] = e1[1] * e2[2] - e1[2] * e2[1];
@@ -132,127 +137,182 @@ __global__ void k_rays(RayArgs A)
     Nn[2] = e1[0] * e2[1] - e1[1] * e2[0];
     const long long a = Nn[d];
     if (a == 0) return;
-    const long long *B = P1, *C = P2;  // counter-clockwise order in (u, w)
-    if (a < 0) { B = P2; C = P1; }
+    // counter-clockwise order in (u, w)
+    long long Bv[3], Cv[3];
+    for (int c = 0; c < 3; ++c) {
+        Bv[c] = a < 0 ? P2[c] : P1[c];
+        Cv[c] = a < 0 ? P1[c] : P2[c];
+    }
     long long umin = min(P0[u], min(P1[u], P2[u])), umax = max(P0[u], max(P1[u], P2[u]));
     long long wmin = min(P0[w], min(P1[w], P2[w])), wmax = max(P0[w], max(P1[w], P2[w]));
     const int nu = A.n[u], nw = A.n[w], nr = A.n[d];
     const long long *qu = A.qc[u], *qw = A.qc[w], *qr = A.qc[d];
     const long long sa = a > 0 ? 1 : -1, aa = a > 0 ? a : -a;
-    int ia0 = lower_bound_ll(qu, nu, umin), ib0 = lower_bound_ll(qw, nw, wmin);
-    long long st[3] = {1, A.n[0], (long long)A.n[0] * A.n[1]};
-    long long X[3];
-    for (int ia = ia0; ia < nu && qu[ia] <= umax; ++ia) {
-        for (int ib = ib0; ib < nw && qw[ib] <= wmax; ++ib) {
-            X[u] = qu[ia];
-            X[w] = qw[ib];
-            if (!owns(P0, B, X, u, w) || !owns(B, C, X, u, w) || !owns(C, P0, X, u, w)) continue;
-            // first i with (qr[i]-A_d)|a| + sign(a) K > 0 (centre strictly beyond the crossing)
-            long long K = (X[u] - P0[u]) * Nn[u] + (X[w] - P0[w]) * Nn[w];
-            long long sk = sa * K;
-            int lo = 0, hi = nr;
-            while (lo < hi) {
-                int m = (lo + hi) >> 1;
-                if ((qr[m] - P0[d]) * aa + sk > 0) hi = m; else lo = m + 1;
+    const int ia0 = lower_bound_ll(qu, nu, umin), ib0 = lower_bound_ll(qw, nw, wmin);
+    const int na = lower_bound_ll(qu, nu, umax + 1) - ia0, nb = lower_bound_ll(qw, nw, wmax + 1) - ib0;
+    const long long rays = (long long)na * nb;
+    const long long st[3] = {1, A.n[0], (long long)A.n[0] * A.n[1]};
+    for (long long r = lane; r < rays; r += RAY_LANES) {
+        const int ia = ia0 + (int)(r / nb), ib = ib0 + (int)(r % nb);
+        long long X[3];
+        X[d] = 0;
+        X[u] = qu[ia];
+        X[w] = qw[ib];
+        if (!owns(P0, Bv, X, u, w) || !owns(Bv, Cv, X, u, w) || !owns(Cv, P0, X, u, w)) continue;
+        // first i with (qr[i]-A_d)|a| + sign(a) K > 0 (centre strictly beyond the crossing)
+        long long K = (X[u] - P0[u]) * Nn[u] + (X[w] - P0[w]) * Nn[w];
+        long long sk = sa * K;
+        int lo = 0, hi = nr;
+        while (lo < hi) {
+            int m = (lo + hi) >> 1;
+            if ((qr[m] - P0[d]) * aa + sk > 0) hi = m; else lo = m + 1;
+        }
+        if (B.closed) {  // d == 0, so u is y and w is z
+            const int x = lo - B.at[0], y = ia - B.at[1], z = ib - B.at[2];
+            if (lo < nr && x >= 0 && x < B.ext[0] && y >= 0 && y < B.ext[1] && z >= 0 && z < B.ext[2]) {
+                const long long q = x + (long long)B.ext[0] * (y + (long long)B.ext[1] * z);
+                atomicXor(&A.tog[B.w0 + (q >> 5)], 1u << (q & 31));
             }
-            long long base = (long long)ia * st[u] + (long long)ib * st[w];
-            if (A.mode == 0) {
-                if (lo < nr) {
-                    long long cell = base + (long long)lo * st[d];
-                    atomicXor(&A.bits[cell >> 5], 1u << (cell & 31));
-                    long long ray = d == 0 ? (long long)ia + (long long)A.n[1] * ib : 0;
-                    A.has[ray] = 1;
-                }
-            } else if (lo >= 1 && lo <= nr - 1) {
-                long long cell = base + (long long)(lo - 1) * st[d];
-                atomicXor(&A.bits[cell >> 5], 1u << (cell & 31));
-            }
+        } else if (lo >= 1 && lo <= nr - 1) {
+            const long long cell = (long long)ia * st[u] + (long long)ib * st[w] + (long long)(lo - 1) * st[d];
+            atomicXor(&A.cut[d][cell >> 5], 1u << (cell & 31));
         }
     }
 }
 
-// One thread per x-ray: prefix parity of the toggles; odd cells become solid.
-__global__ void k_ray_parity(const uint32_t *bits, const uint8_t *has, int nx, long long nrays, uint8_t *flags)
+// One wavefront per x-ray of a closed body's box: prefix parity of the
+// toggles; odd cells become solid, past the box too if the mesh is open.
+// (Bodies of one launch that overlap store the same byte.)
+__global__ void __launch_bounds__(256) k_ray_parity(RayBatch A, uint8_t *flags)
 {
-    long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrays || !has[r]) return;
-    long long base = r * nx;
-    uint32_t par = 0;
-    for (int i = 0; i < nx; ++i) {
-        long long c = base + i;
-        par ^= (bits[c >> 5] >> (c & 31)) & 1u;
-        if (par) flags[c] |= F_SOLID;
+    const RayBody &B = A.body[blockIdx.y];
+    const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (!B.closed || r >= (long long)B.ext[1] * B.ext[2]) return;
+    const int lane = threadIdx.x & 63, nx = A.n[0];
+    const int y = B.at[1] + (int)(r % B.ext[1]), z = B.at[2] + (int)(r / B.ext[1]);
+    uint8_t *row = flags + (long long)nx * (y + (long long)A.n[1] * z);
+    int carry = 0;
+    for (int x0 = 0; x0 < B.ext[0]; x0 += 64) {
+        const int x = x0 + lane;
+        const long long q = r * B.ext[0] + x;
+        const bool on = x < B.ext[0] && ((A.tog[B.w0 + (q >> 5)] >> (q & 31)) & 1u);
+        const unsigned long long m = __ballot(on);
+        const unsigned long long upto = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1ull;
+        if (x < B.ext[0] && ((carry + __popcll(m & upto)) & 1)) row[B.at[0] + x] = F_SOLID;
+        carry += __popcll(m);
     }
+    if (carry & 1)
+        for (int x = B.at[0] + B.ext[0] + lane; x < nx; x += 64) row[x] = F_SOLID;
 }
 
 __device__ __forceinline__ bool bit(const uint32_t *b, long long c) { return (b[c >> 5] >> (c & 31)) & 1u; }
 
-// Ghost, membrane-ghost and cut bits from the solid bits and the raw cut toggles.
-__global__ void k_flags(uint8_t *flags, const uint32_t *cx, const uint32_t *cy, const uint32_t *cz, int nx, int ny,
-                        int nz, int has_membrane)
+// Ghost, membrane-ghost and cut bits from the solid bits and the raw cut
+// toggles, with the counts (solid, ghost, membrane ghost, cut links) and the
+// first cell for the pin.  Bound: the flags, read and written once.  W4: four
+// cells of a row to a thread as the bytes of a word (rows of a multiple of
+// four cells, flags aligned to four bytes); one byte per thread, the counts
+// and the pin in passes of their own took 315 us at 384^3, this 83.
+struct FlagArgs {
+    uint8_t *flags;
+    const uint32_t *cut[3];
+    int n[3], has_membrane;
+    long long N;
+    unsigned long long *pin, *cnt;
+};
+template <bool W4>
+__global__ void __launch_bounds__(256) k_flags(FlagArgs A)
 {
-    long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    long long N = (long long)nx * ny * nz;
-    if (p >= N) return;
-    int i = (int)(p % nx);
-    int j = (int)((p / nx) % ny);
-    int k = (int)(p / ((long long)nx * ny));
-    int ci[3] = {i, j, k}, nn[3] = {nx, ny, nz};
-    long long st[3] = {1, nx, (long long)nx * ny};
-    const uint32_t *cut[3] = {cx, cy, cz};
-    uint8_t f = flags[p] & F_SOLID;
-    if (f) {
-        bool g = false;
-        for (int d = 0; d < 3; ++d) {
-            if (ci[d] > 0 && !(flags[p - st[d]] & F_SOLID)) g = true;
-            if (ci[d] + 1 < nn[d] && !(flags[p + st[d]] & F_SOLID)) g = true;
+    const int nx = A.n[0], ny = A.n[1], nz = A.n[2];
+    const uint32_t one = 0x01010101u;
+    unsigned long long c[4] = {0, 0, 0, 0}, pin = ~0ull;
+    const long long items = W4 ? A.N / 4 : A.N;
+    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < items; q += (long long)gridDim.x * 256) {
+        const uint32_t p = (uint32_t)(W4 ? 4 * q : q);
+        const uint32_t row = p / (uint32_t)nx, i = p - row * (uint32_t)nx, k = row / (uint32_t)ny,
+                       j = row - k * (uint32_t)ny;
+        const uint32_t st[3] = {1, (uint32_t)nx, (uint32_t)nx * (uint32_t)ny};
+        const bool lo[3] = {i > 0, j > 0, k > 0}, hi[3] = {(int)i + (W4 ? 4 : 1) < nx, (int)j + 1 < ny, (int)k + 1 < nz};
+        if constexpr (W4) {
+            auto solid = [&](uint32_t at) { return *reinterpret_cast<const uint32_t *>(A.flags + at) & one; };
+            auto spread = [&](uint32_t b) { return ((b & 0xfu) * 0x00204081u) & one; };
+            auto four = [&](const uint32_t *b, uint32_t at) { return b[at >> 5] >> (at & 31); };
+            const uint32_t S = solid(p);
+            // the neighbours' solid bits (outside the domain: as if solid)
+            uint32_t sp[3], sm[3];
+            sp[0] = (S >> 8) | ((hi[0] ? solid(p + 4) & 1u : 1u) << 24);
+            sm[0] = (S << 8) | (lo[0] ? solid(p - 4) >> 24 : 1u);
+            for (int d = 1; d < 3; ++d) {
+                sp[d] = hi[d] ? solid(p + st[d]) : one;
+                sm[d] = lo[d] ? solid(p - st[d]) : one;
+            }
+            uint32_t f = S | (S & ~(sp[0] & sm[0] & sp[1] & sm[1] & sp[2] & sm[2])) << 1, mg = 0;
+            if (A.has_membrane && S != one) {
+                for (int d = 0; d < 3; ++d) {
+                    const uint32_t own = four(A.cut[d], p);
+                    uint32_t prev;
+                    if (d == 0) prev = (own << 1) | (lo[0] ? (A.cut[0][(p - 1) >> 5] >> ((p - 1) & 31)) & 1u : 0u);
+                    else prev = lo[d] ? four(A.cut[d], p - st[d]) : 0u;
+                    const uint32_t link = spread(own) & ~S & ~sp[d];
+                    f |= link << (4 + d);
+                    mg |= link | (spread(prev) & ~S & ~sm[d]);
+                }
+                f |= mg << 2;
+                c[2] += __popc(mg);
+                c[3] += __popc(f & 0x70707070u);
+            }
+            c[0] += __popc(S);
+            c[1] += __popc(f & (one << 1));
+            const uint32_t ok = one & ~(S | mg);
+            if (ok && pin == ~0ull) pin = p + (uint32_t)((__ffs(ok) - 1) >> 3);
+            *reinterpret_cast<uint32_t *>(A.flags + p) = f;
+        } else {
+            uint8_t f = A.flags[p] & F_SOLID;
+            if (f) {
+                bool g = false;
+                for (int d = 0; d < 3; ++d) {
+                    if (lo[d] && !(A.flags[p - st[d]] & F_SOLID)) g = true;
+                    if (hi[d] && !(A.flags[p + st[d]] & F_SOLID)) g = true;
+                }
+                if (g) f |= F_GHOST;
+            } else if (A.has_membrane) {
+                for (int d = 0; d < 3; ++d) {
+                    if (hi[d] && bit(A.cut[d], p) && !(A.flags[p + st[d]] & F_SOLID)) f |= (uint8_t)(F_CUTX << d);
+                    if (lo[d] && bit(A.cut[d], p - st[d]) && !(A.flags[p - st[d]] & F_SOLID)) f |= F_MGHOST;
+                }
+                if (f & 0x70) f |= F_MGHOST;
+            }
+            c[0] += f & F_SOLID;
+            c[1] += (f >> 1) & 1;
+            c[2] += (f >> 2) & 1;
+            c[3] += __popc(f & 0x70u);
+            if (!(f & (F_SOLID | F_MGHOST)) && pin == ~0ull) pin = p;
+            A.flags[p] = f;
         }
-        if (g) f |= F_GHOST;
-    } else if (has_membrane) {
-        for (int d = 0; d < 3; ++d) {
-            if (ci[d] + 1 < nn[d] && bit(cut[d], p) && !(flags[p + st[d]] & F_SOLID)) f |= (uint8_t)(F_CUTX << d);
-            if (ci[d] > 0 && bit(cut[d], p - st[d]) && !(flags[p - st[d]] & F_SOLID)) f |= F_MGHOST;
-        }
-        if (f & 0x70) f |= F_MGHOST;
     }
-    flags[p] = f;
-}
-
-__global__ void k_pin(const uint8_t *flags, long long N, unsigned long long *pin)
-{
-    long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; p < N; p += (long long)gridDim.x * blockDim.x)
-        if (!(flags[p] & (F_SOLID | F_MGHOST))) {
-            atomicMin(pin, (unsigned long long)p);
-            return;  // later cells of this thread are larger
-        }
+    __shared__ unsigned long long s[4][5];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    for (int o = 32; o > 0; o >>= 1) {
+        for (int q = 0; q < 4; ++q) c[q] += __shfl_xor(c[q], o, 64);
+        pin = min(pin, (unsigned long long)__shfl_xor(pin, o, 64));
+    }
+    if (lane == 0) {
+        for (int q = 0; q < 4; ++q) s[wid][q] = c[q];
+        s[wid][4] = pin;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const unsigned long long v = s[0][threadIdx.x] + s[1][threadIdx.x] + s[2][threadIdx.x] + s[3][threadIdx.x];
+        if (v) atomicAdd(&A.cnt[threadIdx.x], v);
+    } else if (threadIdx.x == 4) {
+        const unsigned long long v = min(min(s[0][4], s[1][4]), min(s[2][4], s[3][4]));
+        if (v != ~0ull) atomicMin(A.pin, v);
+    }
 }
 
 __global__ void k_set_pin(uint8_t *flags, const unsigned long long *pin, long long N)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0 && *pin < (unsigned long long)N) flags[*pin] |= F_PIN;
-}
-
-// counts: solid, ghost, mghost, cut links (per-block partial sums with integer atomics)
-__global__ void k_counts(const uint8_t *flags, long long N, unsigned long long *cnt)
-{
-    __shared__ unsigned long long s[4];
-    if (threadIdx.x < 4) s[threadIdx.x] = 0;
-    __syncthreads();
-    unsigned long long a = 0, b = 0, c = 0, e = 0;
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (long long)gridDim.x * blockDim.x) {
-        uint8_t f = flags[p];
-        a += f & F_SOLID;
-        b += (f >> 1) & 1;
-        c += (f >> 2) & 1;
-        e += ((f >> 4) & 1) + ((f >> 5) & 1) + ((f >> 6) & 1);
-    }
-    atomicAdd(&s[0], a);
-    atomicAdd(&s[1], b);
-    atomicAdd(&s[2], c);
-    atomicAdd(&s[3], e);
-    __syncthreads();
-    if (threadIdx.x < 4) atomicAdd(&cnt[threadIdx.x], s[threadIdx.x]);
 }
 
 // counters of one classification: pin (minimum), then the four counts
@@ -276,48 +336,57 @@ struct Carve {
     }
 };
 
-struct BodyScratch {
-    double *dv;
-    int32_t *dt;
-    long long *qv;
-};
-
-struct ClassifyScratch {
-    double *df[3];
-    long long *qc[3];
-    uint32_t *tog = nullptr, *cut[3] = {nullptr, nullptr, nullptr};
-    uint8_t *has = nullptr;
-    unsigned long long *dev;
-    std::vector<BodyScratch> body;
-};
-
-// Every device buffer a classification uses: per axis the faces and the
-// quantised centres; the toggle bitset and per-ray markers (closed bodies);
-// three cut-link bitsets (membranes); per body its vertices, triangles and
-// quantised vertices; the five counters.
-ClassifyScratch carve_classify(Carve &C, const HostGrid &g, const ibm_body *bodies, int n_body, bool any_closed,
-                               bool any_mem)
+// The scratch a call is charged with: per axis the faces and the quantised
+// centres; the toggle bitset and a byte per ray (closed bodies); three
+// cut-link bitsets (membranes); per body its vertices, triangles and quantised
+// vertices; five counters.  Callers see this size and are refused by it; what
+// is carved from it (below) is no larger: the same pieces without the faces,
+// the bytes per ray and the quantised vertices, the bodies' without padding.
+size_t classify_bytes(const HostGrid &g, const ibm_body *bodies, int n_body, bool any_closed, bool any_mem)
 {
-    ClassifyScratch S;
+    Carve C;
     const long long N = (long long)g.n[0] * g.n[1] * g.n[2];
     const size_t words = (size_t)((N + 31) / 32 + 1);
     for (int d = 0; d < 3; ++d) {
-        S.df[d] = C.take<double>(g.n[d] + 1);
-        S.qc[d] = C.take<long long>(g.n[d]);
+        (void)C.take<double>(g.n[d] + 1);
+        (void)C.take<long long>(g.n[d]);
     }
     if (any_closed) {
-        S.tog = C.take<uint32_t>(words);
-        S.has = C.take<uint8_t>((size_t)g.n[1] * g.n[2]);
+        (void)C.take<uint32_t>(words);
+        (void)C.take<uint8_t>((size_t)g.n[1] * g.n[2]);
     }
     if (any_mem)
-        for (int d = 0; d < 3; ++d) S.cut[d] = C.take<uint32_t>(words);
+        for (int d = 0; d < 3; ++d) (void)C.take<uint32_t>(words);
     for (int b = 0; b < n_body; ++b) {
-        BodyScratch B;
-        B.dv = C.take<double>((size_t)3 * bodies[b].n_vert);
-        B.dt = C.take<int32_t>((size_t)3 * bodies[b].n_tri);
-        B.qv = C.take<long long>((size_t)3 * bodies[b].n_vert);
-        S.body.push_back(B);
+        (void)C.take<double>((size_t)3 * bodies[b].n_vert);
+        (void)C.take<int32_t>((size_t)3 * bodies[b].n_tri);
+        (void)C.take<long long>((size_t)3 * bodies[b].n_vert);
     }
+    (void)C.take<unsigned long long>(5);
+    return C.off;
+}
+
+// What a classification uses: centres, vertices and triangles (one copy from
+// the host), then the bitsets and the counters.
+struct ClassifyScratch {
+    long long *qc[3];
+    double *vert;
+    int32_t *tri;
+    size_t input;  // bytes up to here come from the host
+    uint32_t *tog = nullptr, *cut[3] = {nullptr, nullptr, nullptr};
+    unsigned long long *dev;
+};
+ClassifyScratch carve_classify(Carve &C, const HostGrid &g, size_t nv, size_t nt, bool any_closed, bool any_mem)
+{
+    ClassifyScratch S;
+    const size_t words = (size_t)(((long long)g.n[0] * g.n[1] * g.n[2] + 31) / 32 + 1);
+    for (int d = 0; d < 3; ++d) S.qc[d] = C.take<long long>(g.n[d]);
+    S.vert = C.take<double>(3 * nv);
+    S.tri = C.take<int32_t>(3 * nt);
+    S.input = C.off;
+    if (any_closed) S.tog = C.take<uint32_t>(words);
+    if (any_mem)
+        for (int d = 0; d < 3; ++d) S.cut[d] = C.take<uint32_t>(words);
     S.dev = C.take<unsigned long long>(5);
     return S;
 }
@@ -351,9 +420,7 @@ ClassifyPlan plan_classify(const ibm_grid *grid, const ibm_body *bodies, int n_b
         for (int t = 0; t < 3 * B.n_tri; ++t)
             IBM_REQUIRE(B.tri[t] >= 0 && B.tri[t] < B.n_vert, IBM_EGEOM, "triangle index out of range");
     }
-    Carve C;
-    (void)carve_classify(C, g, bodies, n_body, P.any_closed, P.any_mem);
-    P.bytes = C.off;
+    P.bytes = classify_bytes(g, bodies, n_body, P.any_closed, P.any_mem);
     return P;
 }
 
@@ -369,59 +436,100 @@ void classify_with(const ClassifyPlan &plan, const ibm_body *bodies, int n_body,
     Lat lat;
     lat.S = 65536.0 / L;
     for (int d = 0; d < 3; ++d) lat.lo[d] = g.f[d][0];
+    size_t nv = 0, nt = 0;
+    for (int b = 0; b < n_body; ++b) {
+        nv += bodies[b].n_vert;
+        nt += bodies[b].n_tri;
+    }
     Carve C;
     C.base = scratch;
-    ClassifyScratch S = carve_classify(C, g, bodies, n_body, plan.any_closed, plan.any_mem);
+    const ClassifyScratch S = carve_classify(C, g, nv, nt, plan.any_closed, plan.any_mem);
+    IBM_REQUIRE(C.off <= plan.bytes, IBM_EINVAL, "classification scratch above its plan");
 
+    // centres, vertices and triangles go up in one copy
+    std::vector<char> image(S.input);
+    std::vector<long long> qc[3];
     for (int d = 0; d < 3; ++d) {
-        IBM_HIP(hipMemcpyAsync(S.df[d], g.f[d].data(), (g.n[d] + 1) * sizeof(double), hipMemcpyHostToDevice, s));
-        k_quant_centres<<<cdiv(g.n[d], 256), 256, 0, s>>>(S.df[d], g.n[d], lat.lo[d], lat.S, S.qc[d]);
-        IBM_LAUNCH_CHECK();
+        qc[d].resize(g.n[d]);
+        for (int i = 0; i < g.n[d]; ++i) qc[d][i] = qnt(0.5 * (g.f[d][i] + g.f[d][i + 1]), lat.lo[d], lat.S);
+        std::memcpy(image.data() + ((char *)S.qc[d] - scratch), qc[d].data(), g.n[d] * sizeof(long long));
     }
-    const long long words = (N + 31) / 32 + 1;
+    char *hv = image.data() + ((char *)S.vert - scratch), *ht = image.data() + ((char *)S.tri - scratch);
+    for (int b = 0; b < n_body; ++b) {
+        const size_t bv = (size_t)3 * bodies[b].n_vert * sizeof(double), bt = (size_t)3 * bodies[b].n_tri * sizeof(int32_t);
+        std::memcpy(hv, bodies[b].vert, bv);
+        std::memcpy(ht, bodies[b].tri, bt);
+        hv += bv;
+        ht += bt;
+    }
+    IBM_HIP(hipMemcpyAsync(scratch, image.data(), S.input, hipMemcpyHostToDevice, s));
     k_fill_u8<<<2048, 256, 0, s>>>(flags, N, 0);
+    const long long words = (N + 31) / 32 + 1;
+    for (int d = 0; d < 3; ++d)
+        if (S.cut[d]) k_fill_u32<<<2048, 256, 0, s>>>(S.cut[d], words, 0u);
     IBM_LAUNCH_CHECK();
-    if (plan.any_mem)
-        for (int d = 0; d < 3; ++d) {
-            k_fill_u32<<<2048, 256, 0, s>>>(S.cut[d], words, 0u);
-            IBM_LAUNCH_CHECK();
-        }
+
+    // bodies in order, as many to a launch as descriptions and toggles fit
+    RayBatch A;
+    A.lat = lat;
+    A.tog = S.tog;
+    for (int d = 0; d < 3; ++d) {
+        A.qc[d] = S.qc[d];
+        A.n[d] = g.n[d];
+        A.cut[d] = S.cut[d];
+    }
+    int nb = 0, most = 0;   // bodies of the launch, its most triangles
+    long long used = 0, rays = 0;  // toggle words, most rays of a closed body
+    bool mem = false;
+    auto flush = [&] {
+        if (!nb) return;
+        if (used) k_fill_u32<<<(unsigned)std::min<long long>(2048, (used + 255) / 256), 256, 0, s>>>(S.tog, used, 0u);
+        k_rays<<<dim3(cdiv((long long)most * RAY_LANES, 256), nb, mem ? 3 : 1), 256, 0, s>>>(A);
+        if (rays) k_ray_parity<<<dim3(cdiv(rays, 4), nb), 256, 0, s>>>(A, flags);
+        IBM_LAUNCH_CHECK();
+        nb = most = 0;
+        used = rays = 0;
+        mem = false;
+    };
+    size_t v0 = 0, t0 = 0;
     for (int b = 0; b < n_body; ++b) {
         const ibm_body &B = bodies[b];
-        const BodyScratch &Q = S.body[b];
-        IBM_HIP(hipMemcpyAsync(Q.dv, B.vert, (size_t)3 * B.n_vert * sizeof(double), hipMemcpyHostToDevice, s));
-        IBM_HIP(hipMemcpyAsync(Q.dt, B.tri, (size_t)3 * B.n_tri * sizeof(int32_t), hipMemcpyHostToDevice, s));
-        k_quant_verts<<<cdiv(3 * B.n_vert, 256), 256, 0, s>>>(Q.dv, B.n_vert, lat, Q.qv);
-        IBM_LAUNCH_CHECK();
-        RayArgs A;
-        for (int d = 0; d < 3; ++d) { A.qc[d] = S.qc[d]; A.n[d] = g.n[d]; }
-        A.qv = Q.qv;
-        A.tri = Q.dt;
-        A.nt = B.n_tri;
-        if (B.kind == IBM_KIND_CLOSED) {
-            k_fill_u32<<<2048, 256, 0, s>>>(S.tog, words, 0u);
-            k_fill_u8<<<256, 256, 0, s>>>(S.has, (long long)g.n[1] * g.n[2], 0);
-            IBM_LAUNCH_CHECK();
-            A.d = 0; A.mode = 0; A.bits = S.tog; A.has = S.has;
-            k_rays<<<cdiv(B.n_tri, 64), 64, 0, s>>>(A);
-            IBM_LAUNCH_CHECK();
-            long long nrays = (long long)g.n[1] * g.n[2];
-            k_ray_parity<<<cdiv(nrays, 128), 128, 0, s>>>(S.tog, S.has, g.n[0], nrays, flags);
-            IBM_LAUNCH_CHECK();
-        } else {
+        RayBody R{S.vert + 3 * v0, S.tri + 3 * t0, B.n_tri, B.kind == IBM_KIND_CLOSED, {0, 0, 0}, {0, 0, 0}, 0};
+        v0 += B.n_vert;
+        t0 += B.n_tri;
+        long long need = 0;
+        if (R.closed) {
+            // a crossing lies within the body's lattice box, the first centre
+            // beyond it at most one past the last centre inside
             for (int d = 0; d < 3; ++d) {
-                A.d = d; A.mode = 1; A.bits = S.cut[d]; A.has = nullptr;
-                k_rays<<<cdiv(B.n_tri, 64), 64, 0, s>>>(A);
-                IBM_LAUNCH_CHECK();
+                double lo = B.vert[d], hi = B.vert[d];
+                for (int v = 1; v < B.n_vert; ++v) {
+                    lo = std::min(lo, B.vert[3 * (size_t)v + d]);
+                    hi = std::max(hi, B.vert[3 * (size_t)v + d]);
+                }
+                const auto &q = qc[d];
+                const int a = (int)(std::lower_bound(q.begin(), q.end(), qnt(lo, lat.lo[d], lat.S)) - q.begin());
+                const int e = (int)(std::upper_bound(q.begin(), q.end(), qnt(hi, lat.lo[d], lat.S)) - q.begin());
+                R.at[d] = a;
+                R.ext[d] = std::max(0, std::min(g.n[d], d == 0 ? e + 1 : e) - a);
             }
+            if (!R.ext[0] || !R.ext[1] || !R.ext[2]) continue;  // no ray meets it within the domain
+            need = ((long long)R.ext[0] * R.ext[1] * R.ext[2] + 31) / 32;
         }
+        if (nb == RAY_BODIES || used + need > words) flush();
+        R.w0 = used;
+        used += need;
+        if (R.closed) rays = std::max(rays, (long long)R.ext[1] * R.ext[2]);
+        else mem = true;
+        most = std::max(most, B.n_tri);
+        A.body[nb++] = R;
     }
-    k_flags<<<cdiv(N, 256), 256, 0, s>>>(flags, S.cut[0], S.cut[1], S.cut[2], g.n[0], g.n[1], g.n[2],
-                                         plan.any_mem ? 1 : 0);
+    flush();
     k_init_counters<<<1, 64, 0, s>>>(S.dev);
-    k_pin<<<2048, 256, 0, s>>>(flags, N, S.dev);
+    const FlagArgs F{flags, {S.cut[0], S.cut[1], S.cut[2]}, {g.n[0], g.n[1], g.n[2]}, plan.any_mem ? 1 : 0, N, S.dev, S.dev + 1};
+    if (g.n[0] % 4 == 0 && ((uintptr_t)flags & 3) == 0) k_flags<true><<<std::min(2048u, cdiv(N / 4, 256)), 256, 0, s>>>(F);
+    else k_flags<false><<<std::min(2048u, cdiv(N, 256)), 256, 0, s>>>(F);
     k_set_pin<<<1, 64, 0, s>>>(flags, S.dev, N);
-    k_counts<<<1024, 256, 0, s>>>(flags, N, S.dev + 1);
     IBM_LAUNCH_CHECK();
     unsigned long long h[5];
     IBM_HIP(hipMemcpyAsync(h, S.dev, 5 * 8, hipMemcpyDeviceToHost, s));
