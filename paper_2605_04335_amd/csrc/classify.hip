@@ -16,8 +16,8 @@
 // cells, so that many bodies share one launch of each kind and one bitset.
 // Twenty bodies at 384^3, body after body with a bitset of the whole grid and
 // one thread per triangle and per ray: 2.2 ms of kernels and 46 copies; now
-// 34 us and one copy.  This file is compiled with -ffp-contract=off so that the quantisation, here on the
-// host and there on the device, rounds exactly as written.
+// 34 us and one copy.  This file is compiled with -ffp-contract=off so that
+// the quantisation, on the host and on the device, rounds exactly as written.
 
 #include "common.hpp"
 

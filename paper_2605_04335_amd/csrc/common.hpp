@@ -9,6 +9,7 @@
 #include <shared_mutex>
 #include <stdexcept>
 #include <string>
+#include <algorithm>
 #include <vector>
 
 #include "ibm_poisson.h"
@@ -129,6 +130,32 @@ void upload(DBuf<T> &d, const std::vector<T> &h, hipStream_t s)
     d.alloc(h.size());
     if (!h.empty()) IBM_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
 }
+
+// Host image of one device region: pieces are reserved and written, and all go
+// up in one copy.  The image has to live until the copy's stream is waited for.
+struct Image {
+    std::vector<char> h;
+    size_t take(size_t bytes)
+    {
+        const size_t o = (h.size() + 15) / 16 * 16;
+        h.resize(o + bytes);
+        return o;
+    }
+    template <class T>
+    T *at(size_t o) { return reinterpret_cast<T *>(h.data() + o); }
+    template <class T>
+    size_t put(const std::vector<T> &v)
+    {
+        const size_t o = take(v.size() * sizeof(T));
+        std::copy(v.begin(), v.end(), at<T>(o));
+        return o;
+    }
+    void upload(DBuf<char> &d, hipStream_t s)
+    {
+        d.alloc(h.size());
+        if (!h.empty()) IBM_HIP(hipMemcpyAsync(d.p, h.data(), h.size(), hipMemcpyHostToDevice, s));
+    }
+};
 
 inline unsigned cdiv(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
 

@@ -29,6 +29,8 @@
 
 namespace ibm {
 int64_t compact_cells(const uint8_t *flags, long long N, uint8_t mask, DBuf<int32_t> &out, hipStream_t s);
+void compact_two(const uint8_t *flags, long long N, uint8_t m0, DBuf<int32_t> &o0, int64_t &n0, uint8_t m1,
+                 DBuf<int32_t> &o1, int64_t &n1, hipStream_t s);
 
 namespace {
 
@@ -70,10 +72,9 @@ struct Level {
     int n[3] = {0, 0, 0};
     int H = 0;
     long long N = 0, Nh = 0;
-    DBuf<double> cp[3], cm[3], w[3];
+    size_t cp[3], cm[3], w[3];       // places of the coefficients in the context's image
     DBuf<uint8_t> m;                 // split layout: coarse mask (CM_* bits); level 0 flags
-    DBuf<int> pi[3];                 // prolongation map from the coarse parent
-    DBuf<double> pt[3];
+    size_t pi[3] = {0, 0, 0}, pt[3] = {0, 0, 0};  // prolongation map from the coarse parent
     double volA = 0.0;               // volume of the active cells
     long long n_inactive = 0;        // coarse levels: inactive cells (inside bodies)
     Geo geo;                         // tiles over (h, j, k) of one colour
@@ -88,11 +89,11 @@ struct Level {
     DBuf<double> k64;                // brick levels: black iterate between the phases
     DBuf<float> k32;
     Lv lv;
-    PMap pm;
+    PMap pm{};
     std::vector<double> hc[3], hw[3];
 };
 
-void level_geometry(Level &L, const std::vector<double> *f, hipStream_t s)
+void level_geometry(Level &L, const std::vector<double> *f, Image &I)
 {
     for (int d = 0; d < 3; ++d) {
         int n = L.n[d];
@@ -107,9 +108,9 @@ void level_geometry(Level &L, const std::vector<double> *f, hipStream_t s)
             cp[i] = (i + 1 < n) ? 1.0 / (L.hw[d][i] * (L.hc[d][i + 1] - L.hc[d][i])) : 0.0;
             cm[i] = (i > 0) ? 1.0 / (L.hw[d][i] * (L.hc[d][i] - L.hc[d][i - 1])) : 0.0;
         }
-        upload(L.cp[d], cp, s);
-        upload(L.cm[d], cm, s);
-        upload(L.w[d], L.hw[d], s);
+        L.cp[d] = I.put(cp);
+        L.cm[d] = I.put(cm);
+        L.w[d] = I.put(L.hw[d]);
     }
     L.N = (long long)L.n[0] * L.n[1] * L.n[2];
     L.H = (L.n[0] + 1) / 2;
@@ -193,6 +194,7 @@ struct poisson_ctx {
     Walk W0;   // over Nt unknowns
     Walk W4;   // over ceil(Nt / 4) groups of 4 unknowns
     Walk Wc;   // over 2 Nh cell slots
+    Walk Wp;   // over Nh pairs of cells, then the membrane unknowns
     DBuf<double> x, r, rh, p, v, ph, sh, t, rsp, b;
     DBuf<float> fr, frh, fp, fv, fph, fsh, ft, frsp;
     // mixed: the inner solution accumulates in FP64 (a smooth correction
@@ -206,6 +208,7 @@ struct poisson_ctx {
     DBuf<uint8_t> hact[2];      // set-up: natural-order coarse active/cut bits of two consecutive levels
     // fused level-0 smoothing (walk.hpp) and the units around irregular cells
     bool walk = false, beside = false;
+    DBuf<char> coef;            // coefficients and prolongation maps of all levels
     // level-0 half-sweeps with the sparse rows in the same launch (rows.hpp):
     // on all of level 0 (flat), or on the near units of the fused passes (few)
     bool flat = false, few = false;
@@ -918,30 +921,14 @@ int bicgstab(poisson_ctx &c, const TR *rhs, TX *y, T *r, T *rh, T *p, T *v, T *p
 }
 
 // ------------------------------------------------------------------ RHS, gauge (split layout)
-__global__ void __launch_bounds__(TPB) k_rhs(Lv L, Walk W, long long pin, const double *fs, const double *sc,
-                                             int slot_, double *b)
+// ghost rows of the RHS, in split or (NAT) natural order
+template <bool NAT>
+__global__ void __launch_bounds__(TPB) k_rhs_ghost(Lv L, Sp S, const double *dlb, const double *g, double *b)
 {
-    const double mean = sc[slot_];
-    WALK_BEGIN(W, p)
-        if (p >= 2 * L.Nh) { b[p] = 0.0; continue; }
-        const uint8_t fl = L.f[p];
-        b[p] = ((fl & F_SOLID) || p == pin) ? 0.0 : fs[p] - mean;
-    WALK_END
-}
-
-__global__ void __launch_bounds__(TPB) k_rhs_ghost(Sp S, const double *dlb, const double *g, double *b)
-{
-    for (int r = blockIdx.x * TPB + threadIdx.x; r < S.nrows; r += gridDim.x * TPB)
-        b[ghost_unknown(S, r)] = g ? S.rsG[r] * dlb[r] * g[r] : 0.0;
-}
-
-__global__ void __launch_bounds__(TPB) k_gauge(Lv L, Walk W, const double *x, const double *sc, int slot_, double *out)
-{
-    const double mean = sc[slot_];
-    WALK_BEGIN(W, p)
-        const bool act = p >= 2 * L.Nh || active0(L.f[p]);
-        out[p] = act ? x[p] - mean : 0.0;
-    WALK_END
+    for (int r = blockIdx.x * TPB + threadIdx.x; r < S.nrows; r += gridDim.x * TPB) {
+        const long long u = ghost_unknown(S, r);
+        b[NAT ? natural_of(L, u) : u] = g ? S.rsG[r] * dlb[r] * g[r] : 0.0;
+    }
 }
 
 template <class T>
@@ -1018,12 +1005,12 @@ void plan_walk(poisson_ctx &c, hipStream_t s)
     c.near = Near{};
     if (c.nrows || c.nm) {
         for (auto &q : c.ubits) reserve(q, nu);
-        k_unit_cells<<<cdiv(nu, 4), NU_T, 0, s>>>(Z.lv, nux, nuy, nu, c.ubits[0].p);
+        k_unit_cells<<<cdiv(16 * nu, NU_T), NU_T, 0, s>>>(Z.lv, nux, nuy, nu, c.ubits[0].p);
         k_unit_near<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[0].p, c.ubits[1].p);
         k_unit_list<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[1].p, c.ubits[0].p);
         IBM_LAUNCH_CHECK();
-        const int64_t n = compact_cells(c.ubits[0].p, nu, UB_LIST, c.units, s);
-        const int64_t nr = compact_cells(c.ubits[0].p, nu, UB_NEAR, c.nunits, s);
+        int64_t n, nr;
+        compact_two(c.ubits[0].p, nu, UB_LIST, c.units, n, UB_NEAR, c.nunits, nr, s);
         c.near = Near{c.units.p, c.ubits[0].p, (int)n, nux, nuy, nuz};
         c.nearres = Near{c.nunits.p, c.ubits[0].p, (int)nr, nux, nuy, nuz};
         c.walk = n <= WALK_MAX_NEAR * nu;
@@ -1125,7 +1112,11 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     if (c.g64) { (void)hipGraphExecDestroy(c.g64); c.g64 = nullptr; }
     if (c.g32) { (void)hipGraphExecDestroy(c.g32); c.g32 = nullptr; }
     if (c.g64w) { (void)hipGraphExecDestroy(c.g64w); c.g64w = nullptr; }
-    k_setup_flags0<<<Z.walk.nb, TPB, 0, s>>>(Z.lv, Z.walk, flags, Z.m.p);
+    const bool w8 = nx % 8 == 0 && ((uintptr_t)flags & 7) == 0;
+    const Walk WF = make_walk(w8 ? Z.Nh / 4 : Z.Nh);
+    if (w8) k_setup_flags0<true><<<WF.nb, TPB, 0, s>>>(Z.lv, WF, flags, Z.m.p, c.part.p);
+    else k_setup_flags0<false><<<WF.nb, TPB, 0, s>>>(Z.lv, WF, flags, Z.m.p, c.part.p);
+    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, WF.nb, FIN_SUM, 0, 0.0, c.ssum.p);  // fluid volume
     // ghost and membrane rows
     const long long R1 = std::max<long long>(R, 1), M1 = std::max<long long>(nm, 1);
     reserve(c.rslot, std::max<long long>(c.ng, 1));
@@ -1157,9 +1148,7 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     // these, not every black slot)
     if (R) k_mark_read<<<blocks(8 * R), TPB, 0, s>>>(8 * R, c.rcol.p, c.N2, Z.m.p);
     if (nm) k_mark_read<<<blocks(6 * nm), TPB, 0, s>>>(6 * nm, c.mcol.p, c.N2, Z.m.p);
-    // fluid volume, then the coarse masks level by level with their active volumes
-    k_fluid_volume<<<Z.walk.nb, TPB, 0, s>>>(Z.lv, Z.walk, c.part.p);
-    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, Z.walk.nb, FIN_SUM, 0, 0.0, c.ssum.p);
+    // the coarse masks level by level with their active volumes
     for (int l = 1; l < nl; ++l) {
         Level &F = c.lv[l - 1], &C = c.lv[l];
         const uint8_t *fine = l == 1 ? flags : c.hact[l & 1].p;
@@ -1200,6 +1189,7 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     const bool first = !c.x.p;
     c.Nt = Nt;
     c.W0 = make_walk(Nt);
+    c.Wp = make_walk(Z.Nh + nm);
     c.W4 = make_walk((Nt + 3) / 4, W4MAXB);
     const long long cap = first ? Nt : Nt + nm / 4 + 1024;
     DBuf<double> *dv[] = {&c.x, &c.r, &c.b, &c.t, &c.rh, &c.p, &c.v, &c.ph, &c.sh, &c.rsp, &c.d64, &c.r2};
@@ -1263,6 +1253,7 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
         }
     }
     c->lv.resize(nl);
+    Image I;  // every level's coefficients and maps: one copy instead of up to fifteen per level
     std::vector<double> faces[3];
     for (int d = 0; d < 3; ++d) faces[d] = g.f[d];
     for (int l = 0; l < nl; ++l) {
@@ -1274,7 +1265,7 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
                 for (int i = 0; i <= L.n[d]; ++i) cf[i] = faces[d][2 * i];
                 faces[d] = cf;
             }
-        level_geometry(L, faces, s);
+        level_geometry(L, faces, I);
     }
     // level 0: shorter plane runs per thread (more tiles) measured faster;
     // the half-sweep addresses a tile's planes with 32-bit byte offsets
@@ -1299,10 +1290,11 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
                 pi[i] = I0;
                 pt[i] = (x - C.hc[d][I0]) / (C.hc[d][I0 + 1] - C.hc[d][I0]);
             }
-            upload(F.pi[d], pi, s);
-            upload(F.pt[d], pt, s);
+            F.pi[d] = I.put(pi);
+            F.pt[d] = I.put(pt);
         }
     }
+    I.upload(c->coef, s);
     // tail start: the coarsest levels that fit one workgroup's LDS and, the
     // first of them, its registers (two cell pairs per thread; one below)
     for (int pass = 0; pass < 2; ++pass) {
@@ -1327,9 +1319,17 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
         v.nx = L.n[0]; v.ny = L.n[1]; v.nz = L.n[2]; v.H = L.H; v.Nh = L.Nh;
         v.fH = make_fdiv(L.H);
         v.fy = make_fdiv(L.n[1]);
-        for (int d = 0; d < 3; ++d) { v.cp[d] = L.cp[d].p; v.cm[d] = L.cm[d].p; v.w[d] = L.w[d].p; }
+        for (int d = 0; d < 3; ++d) {
+            v.cp[d] = (const double *)(c->coef.p + L.cp[d]);
+            v.cm[d] = (const double *)(c->coef.p + L.cm[d]);
+            v.w[d] = (const double *)(c->coef.p + L.w[d]);
+        }
         v.f = L.m.p;
-        for (int d = 0; d < 3; ++d) { L.pm.pi[d] = L.pi[d].p; L.pm.pt[d] = L.pt[d].p; }
+        if (l + 1 < nl)
+            for (int d = 0; d < 3; ++d) {
+                L.pm.pi[d] = (const int *)(c->coef.p + L.pi[d]);
+                L.pm.pt[d] = (const double *)(c->coef.p + L.pt[d]);
+            }
         if (l > 0) {
             L.brick = L.N <= BRICK_MAX_CELLS && o.nu1 <= 2 && o.nu2 >= 1 && o.nu2 <= 2;
             if (L.brick) L.br = make_brick(L.n[0], L.n[1], L.n[2]);
@@ -1376,24 +1376,35 @@ namespace {
 
 void to_split(poisson_ctx &c, const double *nat, double *spl, long long tail, hipStream_t s)
 {
-    k_to_split<double, double><<<c.W0.nb, TPB, 0, s>>>(c.L0(), c.W0, nat, spl, tail);
+    k_to_split<false><<<c.Wp.nb, TPB, 0, s>>>(c.L0(), c.Wp, nat, pairs_aligned(c.L0().nx, nat), spl, tail, nullptr);
     IBM_LAUNCH_CHECK();
 }
 
+template <int MODE>
 void from_split(poisson_ctx &c, const double *spl, double *nat, long long tail, hipStream_t s)
 {
-    k_from_split<double, double><<<c.W0.nb, TPB, 0, s>>>(c.L0(), c.W0, spl, nat, tail);
+    k_from_split<MODE><<<c.Wp.nb, TPB, 0, s>>>(c.L0(), c.Wp, spl, nat, pairs_aligned(c.L0().nx, nat), tail, c.pin,
+                                               c.sc.p + S_TMP2);
     IBM_LAUNCH_CHECK();
 }
 
-// b (split) from raw natural f and optional g
+// whether the na values from a and the nb values from b share memory
+bool overlap(const double *a, long long na, const double *b, long long nb)
+{
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + nb * sizeof(double) && y < x + na * sizeof(double);
+}
+
+// b (split, or NAT natural) from raw natural f and optional g; NAT: b overlaps neither
+template <bool NAT = false>
 void assemble_rhs(poisson_ctx &c, const double *f, const double *gval, double *b, hipStream_t s)
 {
-    to_split(c, f, c.t.p, 0, s);
-    k_vsum<double, false><<<c.Wc.nb, TPB, 0, s>>>(c.L0(), c.Wc, c.t.p, c.part.p);
-    fin(c, c.Wc.nb, FIN_MEAN, S_TMP, c.vol_fluid, s);
-    k_rhs<<<c.W0.nb, TPB, 0, s>>>(c.L0(), c.W0, c.pin, c.t.p, c.sc.p, S_TMP, b);
-    if (c.nrows) k_rhs_ghost<<<sparse_blocks(c.nrows), TPB, 0, s>>>(c.sp, c.rdlb.p, gval, b);
+    const int nx = c.L0().nx;
+    k_vsum<true, false><<<c.Wp.nb, TPB, 0, s>>>(c.L0(), c.Wp, f, pairs_aligned(nx, f), c.part.p);
+    fin(c, c.Wp.nb, FIN_MEAN, S_TMP, c.vol_fluid, s);
+    k_rhs<NAT><<<c.Wp.nb, TPB, 0, s>>>(c.L0(), c.Wp, c.pin, f, pairs_aligned(nx, f), c.sc.p + S_TMP, b,
+                                       pairs_aligned(nx, b), c.nm);
+    if (c.nrows) k_rhs_ghost<NAT><<<sparse_blocks(c.nrows), TPB, 0, s>>>(c.L0(), c.sp, c.rdlb.p, gval, b);
     IBM_LAUNCH_CHECK();
 }
 
@@ -1615,10 +1626,9 @@ extern "C" int32_t poisson_solve(poisson_ctx *c, const double *f_dev, const doub
         int rc = solve_core(*c, stats, s);
         // gauge: volume-weighted fluid mean removed from fluid, ghost and membrane-ghost values
         k_pinres<<<1, 64, 0, s>>>(c->L0(), c->pin, c->x.p, c->sc.p);
-        k_vsum<double, false><<<c->Wc.nb, TPB, 0, s>>>(c->L0(), c->Wc, c->x.p, c->part.p);
-        fin(*c, c->Wc.nb, FIN_MEAN, S_TMP2, c->vol_fluid, s);
-        k_gauge<<<c->W0.nb, TPB, 0, s>>>(c->L0(), c->W0, c->x.p, c->sc.p, S_TMP2, c->t.p);
-        from_split(*c, c->t.p, x_dev, c->nm, s);
+        k_vsum<false, false><<<c->Wp.nb, TPB, 0, s>>>(c->L0(), c->Wp, c->x.p, false, c->part.p);
+        fin(*c, c->Wp.nb, FIN_MEAN, S_TMP2, c->vol_fluid, s);
+        from_split<OUT_GAUGE>(*c, c->x.p, x_dev, c->nm, s);
         IBM_HIP(hipEventRecord(c->e1, s));
         read_scalars(*c, s);
         if (stats) {
@@ -1645,7 +1655,7 @@ extern "C" int32_t poisson_solve_from(poisson_ctx *c, const double *f_dev, const
         // initial guess: the cells (and membrane ghost unknowns when given)
         // from x0, inactive slots zero, shifted to a zero pin value
         const bool ghosts = n_x0 > c->N;
-        k_to_split<double, double><<<c->W0.nb, TPB, 0, s>>>(c->L0(), c->W0, x0_dev, c->x.p, ghosts ? c->nm : 0);
+        to_split(*c, x0_dev, c->x.p, ghosts ? c->nm : 0, s);
         if (c->nm && !ghosts)
             k_warm_membrane<<<(int)std::min<long long>((c->nm + TPB - 1) / TPB, 4096), TPB, 0, s>>>(c->sp, c->x.p);
         k_zero_inactive<<<c->Wc.nb, TPB, 0, s>>>(c->L0(), c->Wc, c->x.p);
@@ -1654,10 +1664,9 @@ extern "C" int32_t poisson_solve_from(poisson_ctx *c, const double *f_dev, const
         IBM_LAUNCH_CHECK();
         int rc = solve_core(*c, stats, s, true);
         k_pinres<<<1, 64, 0, s>>>(c->L0(), c->pin, c->x.p, c->sc.p);
-        k_vsum<double, false><<<c->Wc.nb, TPB, 0, s>>>(c->L0(), c->Wc, c->x.p, c->part.p);
-        fin(*c, c->Wc.nb, FIN_MEAN, S_TMP2, c->vol_fluid, s);
-        k_gauge<<<c->W0.nb, TPB, 0, s>>>(c->L0(), c->W0, c->x.p, c->sc.p, S_TMP2, c->t.p);
-        from_split(*c, c->t.p, x_dev, c->nm, s);
+        k_vsum<false, false><<<c->Wp.nb, TPB, 0, s>>>(c->L0(), c->Wp, c->x.p, false, c->part.p);
+        fin(*c, c->Wp.nb, FIN_MEAN, S_TMP2, c->vol_fluid, s);
+        from_split<OUT_GAUGE>(*c, c->x.p, x_dev, c->nm, s);
         IBM_HIP(hipEventRecord(c->e1, s));
         read_scalars(*c, s);
         if (stats) {
@@ -1709,7 +1718,7 @@ extern "C" int32_t poisson_solve_assembled(poisson_ctx *c, const double *b_dev, 
         IBM_HIP(hipEventRecord(c->e0, s));
         to_split(*c, b_dev, c->b.p, c->nm, s);
         int rc = solve_core(*c, stats, s);
-        from_split(*c, c->x.p, x_dev, c->nm, s);
+        from_split<OUT_PLAIN>(*c, c->x.p, x_dev, c->nm, s);
         IBM_HIP(hipEventRecord(c->e1, s));
         IBM_HIP(hipStreamSynchronize(s));
         if (stats) {
@@ -1727,9 +1736,21 @@ extern "C" int32_t poisson_apply(poisson_ctx *c, const double *x_dev, double *y_
         IBM_REQUIRE(c && x_dev && y_dev, IBM_EINVAL, "null argument");
         StreamJoin j(*c, (hipStream_t)stream);
         hipStream_t s = c->cs;
+        const long long n = c->N + c->nm;
+        if (!overlap(x_dev, n, y_dev, n)) {
+            const bool v2 = pairs_aligned(c->L0().nx, x_dev) && pairs_aligned(c->L0().nx, y_dev);
+            const int nsp = (int)(c->nrows + c->nm);
+            const Geo &G = c->lv[0].geo;
+            if (v2) k_apply_nat<true><<<G.nb, TPB, 0, s>>>(c->L0(), G, c->pin, x_dev, y_dev);
+            else k_apply_nat<false><<<G.nb, TPB, 0, s>>>(c->L0(), G, c->pin, x_dev, y_dev);
+            if (nsp) k_sparse_nat<<<sparse_blocks(nsp), TPB, 0, s>>>(c->L0(), c->sp, x_dev, y_dev);
+            IBM_LAUNCH_CHECK();
+            return;
+        }
+        // in place: through split copies
         to_split(*c, x_dev, c->r.p, c->nm, s);
         launch_apply<double>(*c, M_PINNED, false, 0, c->r.p, c->t.p, nullptr, nullptr, nullptr, nullptr, s);
-        from_split(*c, c->t.p, y_dev, c->nm, s);
+        from_split<OUT_PLAIN>(*c, c->t.p, y_dev, c->nm, s);
     });
 }
 
@@ -1740,8 +1761,13 @@ extern "C" int32_t poisson_assemble_rhs(poisson_ctx *c, const double *f_dev, con
         IBM_REQUIRE(c && f_dev && b_dev, IBM_EINVAL, "null argument");
         StreamJoin j(*c, (hipStream_t)stream);
         hipStream_t s = c->cs;
+        const long long n = c->N + c->nm;
+        if (!overlap(f_dev, c->N, b_dev, n) && !(g_dev && overlap(g_dev, c->nrows, b_dev, n))) {
+            assemble_rhs<true>(*c, f_dev, g_dev, b_dev, s);
+            return;
+        }
         assemble_rhs(*c, f_dev, g_dev, c->r.p, s);
-        from_split(*c, c->r.p, b_dev, c->nm, s);
+        from_split<OUT_PLAIN>(*c, c->r.p, b_dev, c->nm, s);
     });
 }
 
@@ -1752,14 +1778,12 @@ extern "C" int32_t poisson_precond(poisson_ctx *c, const double *b_dev, double *
         IBM_REQUIRE(!c->mixed, IBM_EINVAL, "poisson_precond needs an FP64 context");
         StreamJoin j(*c, (hipStream_t)stream);
         hipStream_t s = c->cs;
-        to_split(*c, b_dev, c->r.p, c->nm, s);
-        k_vsum<double, true><<<c->Wc.nb, TPB, 0, s>>>(c->L0(), c->Wc, c->r.p, c->part.p);
-        fin(*c, c->Wc.nb, FIN_SINK, S_SINKP, 0.0, s);
+        k_to_split<true><<<c->Wp.nb, TPB, 0, s>>>(c->L0(), c->Wp, b_dev, pairs_aligned(c->L0().nx, b_dev), c->r.p, c->nm,
+                                                  c->part.p);
+        fin(*c, c->Wp.nb, FIN_SINK, S_SINKP, 0.0, s);
         precond<double>(*c, c->r.p, c->t.p, c->sh.p, c->sc.p + S_SINKP, s);
         // shift: every active unknown minus the pin value, then the pin itself
-        k_shift<double><<<c->W0.nb, TPB, 0, s>>>(c->L0(), c->W0, c->pin, c->t.p);
-        k_shift_pin<<<1, 1, 0, s>>>(c->pin, c->t.p);
-        from_split(*c, c->t.p, x_dev, c->nm, s);
+        from_split<OUT_SHIFT>(*c, c->t.p, x_dev, c->nm, s);
         IBM_LAUNCH_CHECK();
     });
 }

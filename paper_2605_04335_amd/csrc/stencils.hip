@@ -657,31 +657,28 @@ struct Compaction {
         IBM_LAUNCH_CHECK();
     }
 };
-
-// host image of one device region: pieces are reserved, written, and go up in one copy
-struct Image {
-    std::vector<char> h;
-    size_t take(size_t bytes)
-    {
-        const size_t o = (h.size() + 15) / 16 * 16;
-        h.resize(o + bytes);
-        return o;
-    }
-    template <class T>
-    T *at(size_t o) { return reinterpret_cast<T *>(h.data() + o); }
-};
 }  // namespace
 
-// Ordered list of the cells that carry flag bit `mask`; returns the count.
+// Ordered lists of the cells that carry flag bits m0 and m1, and their counts.
+void compact_two(const uint8_t *flags, long long N, uint8_t m0, DBuf<int32_t> &o0, int64_t &n0, uint8_t m1,
+                 DBuf<int32_t> &o1, int64_t &n1, hipStream_t s)
+{
+    Compaction C(flags, N, Bits{{m0, m1, 0}}, m1 ? 2 : 1);
+    int total[2] = {0, 0};
+    C.count(total, s);
+    n0 = total[0];
+    n1 = total[1];
+    o0.alloc(std::max(total[0], 1));
+    if (m1) o1.alloc(std::max(total[1], 1));
+    C.fill(Lists{{o0.p, o1.p, nullptr}}, s);
+    IBM_HIP(hipStreamSynchronize(s));
+}
 int64_t compact_cells(const uint8_t *flags, long long N, uint8_t mask, DBuf<int32_t> &out, hipStream_t s)
 {
-    Compaction C(flags, N, Bits{{mask, 0, 0}}, 1);
-    int total = 0;
-    C.count(&total, s);
-    out.alloc(std::max(total, 1));
-    C.fill(Lists{{out.p, nullptr, nullptr}}, s);
-    IBM_HIP(hipStreamSynchronize(s));
-    return total;
+    DBuf<int32_t> none;
+    int64_t n, z;
+    compact_two(flags, N, mask, out, n, 0, none, z, s);
+    return n;
 }
 
 void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, const uint8_t *flags, ibm_stencils **out,
@@ -741,10 +738,7 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
             const std::vector<double> *ga[4] = {c, w, cp, cm};
             size_t go[4][3];
             for (int q = 0; q < 4; ++q)
-                for (int d = 0; d < 3; ++d) {
-                    go[q][d] = I.take(g.n[d] * sizeof(double));
-                    std::copy(ga[q][d].begin(), ga[q][d].end(), I.at<double>(go[q][d]));
-                }
+                for (int d = 0; d < 3; ++d) go[q][d] = I.put(ga[q][d]);
             // vertices and triangles of all bodies, and the runs by kind
             long long nv = 0, nt = 0;
             std::vector<Run> runs, body;
@@ -772,7 +766,7 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
             }
             const int nr = (int)runs.size(), nb = (int)body.size();
             const size_t ov = I.take(3 * nv * sizeof(double)), ot = I.take(3 * nt * sizeof(int32_t)),
-                         orun = I.take(nr * sizeof(Run)), obody = I.take(nb * sizeof(Run));
+                         orun = I.put(runs), obody = I.put(body);
             double *hv = I.at<double>(ov);
             int32_t *ht = I.at<int32_t>(ot);
             int v0 = 0;
@@ -782,10 +776,7 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
                 for (int t = 0; t < 3 * B.n_tri; ++t) *ht++ = v0 + B.tri[t];
                 v0 += B.n_vert;
             }
-            std::copy(runs.begin(), runs.end(), I.at<Run>(orun));
-            std::copy(body.begin(), body.end(), I.at<Run>(obody));
-            up.alloc(I.h.size());
-            IBM_HIP(hipMemcpyAsync(up.p, I.h.data(), I.h.size(), hipMemcpyHostToDevice, s));
+            I.upload(up, s);
             for (int d = 0; d < 3; ++d) {
                 G.c[d] = (const double *)(up.p + go[0][d]);
                 G.w[d] = (const double *)(up.p + go[1][d]);

@@ -673,25 +673,37 @@ __global__ void __launch_bounds__(NU_T) k_near_final(Lv L, Near U, int nbu, long
 
 // ---- set-up of the lists: irregular and read cells per unit, the near units
 // around them, the listed units
+// (sixteen lanes per unit, four cell pairs each: a word per colour where rows
+// and the mask's halves are aligned to it)
 __global__ void __launch_bounds__(NU_T) k_unit_cells(Lv L, int nux, int nuy, long long nu, uint8_t *__restrict__ bits)
 {
-    const long long u = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (u >= nu) return;
-    const int l = threadIdx.x & 63;
-    const int h = 4 * (int)(u % nux) + (l & 3), j = 4 * (int)((u / nux) % nuy) + ((l >> 2) & 3),
-              k = 4 * (int)(u / ((long long)nux * nuy)) + (l >> 4);
-    uint8_t f = 0;
+    const int l = threadIdx.x & 15, sh = threadIdx.x & 48;
+    const long long u = ((long long)blockIdx.x * NU_T + threadIdx.x) >> 4;
+    const int h = 4 * (int)(u % nux), j = 4 * (int)((u / nux) % nuy) + (l & 3),
+              k = 4 * (int)(u / ((long long)nux * nuy)) + (l >> 2);
+    uint32_t f = 0;
     bool act = false;
-    if (h < L.H && j < L.ny && k < L.nz) {
+    if (u < nu && j < L.ny && k < L.nz) {
         const long long s = h + (long long)L.H * (j + (long long)L.ny * k);
-        f = L.f[s] | L.f[L.Nh + s];
-        act = active0(L.f[s]) || active0(L.f[L.Nh + s]);
+        if (L.H % 4 == 0) {
+            const uint32_t a = *reinterpret_cast<const uint32_t *>(L.f + s),
+                           b = *reinterpret_cast<const uint32_t *>(L.f + L.Nh + s), one = 0x01010101u;
+            f = a | b;
+            act = ((~a | a >> 1 | ~b | b >> 1) & one) != 0;
+        } else {
+            for (int q = 0; q < 4 && h + q < L.H; ++q) {
+                f |= L.f[s + q] | L.f[L.Nh + s + q];
+                act = act || active0(L.f[s + q]) || active0(L.f[L.Nh + s + q]);
+            }
+        }
+        f |= f >> 16;
+        f |= f >> 8;
     }
-    const unsigned long long live = __ballot(act);
-    const unsigned long long irr = __ballot((f & (F_SOLID | F_MGHOST)) != 0), rd = __ballot((f & F_RD) != 0);
-    if (l == 0) {
-        // lane bits: 2-3 row, 4-5 plane
-        const unsigned long long lowj = 0x00ff00ff00ff00ffull, lowk = 0x00000000ffffffffull;
+    // lane bits: 0-1 row, 2-3 plane
+    auto group = [&](bool v) { return (uint32_t)(__ballot(v) >> sh) & 0xffffu; };
+    const uint32_t live = group(act), irr = group((f & (F_SOLID | F_MGHOST)) != 0), rd = group((f & F_RD) != 0);
+    if (l == 0 && u < nu) {
+        const uint32_t lowj = 0x3333u, lowk = 0x00ffu;
         uint8_t o = 0;
         if (irr & lowj & lowk) o |= 1;
         if (irr & ~lowj & lowk) o |= 2;

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
+from tests import refpy
 from paper_2605_04335_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +96,44 @@ def test_rows_of_many_bodies(name):
     assert np.abs(e["w"] - O.st.w).max(initial=0) < 1e-13
     assert np.abs(e["dlb"] - O.st.dlb).max(initial=0) < 1e-13
     assert np.abs(e["geo"] - O.st.geo).max(initial=0) < 1e-13
+
+
+# the operator and the RHS between natural arrays: even rows in 16-byte pairs,
+# the same at an address that is not, odd rows, no body, membranes; and in place,
+# where the split arrays take over.  Bounds of the operator's parity test.
+@pytest.mark.parametrize("shape,bodies", [((24, 20, 16), "both"), ((25, 20, 19), "both"), ((4, 5, 6), ""),
+                                          ((130, 9, 37), "plate"), ((71, 66, 68), "sphere")])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_natural_operator_and_rhs(shape, bodies, shift):
+    import torch
+    import paper_2605_04335_amd as P
+    f = faces(*shape)
+    L = [v[-1] for v in f]
+    c, s = [0.5 * e for e in L], min(L)
+    bl = []
+    if bodies in ("both", "sphere"):
+        bl.append(W.sphere((c[0] - 0.2 * s, c[1], c[2]), 0.2 * s, freq=3))
+    if bodies in ("both", "plate"):
+        bl.append(W.plate((c[0] + 0.2 * s, c[1], c[2]), 0.3 * s, 0.5 * s, 8, 8, 0.02 * s, 0.4))
+    O = oracle.setup(*f, bl)
+    flags, st, sol, _ = P.setup(*f, bl)
+    n, N = sol.n_unknowns, len(O.flags)
+
+    def at(a):  # the same values, off 16-byte alignment with shift 1
+        t = torch.empty(len(a) + 1, dtype=torch.float64, device="cuda")[shift:shift + len(a)]
+        t.copy_(torch.from_numpy(a))
+        return t
+
+    x = W.noise_rhs(n, 3)
+    x[~refpy.active_mask(O.flags, O.st.nm)] = 0.0
+    want = oracle.apply(*f, O.flags, O.st, x)
+    y = at(np.full(n, np.nan))
+    xs = at(x)
+    sol.apply(xs, y)
+    assert np.linalg.norm(y.cpu().numpy() - want) < 1e-14 * np.linalg.norm(want)
+    sol.apply(xs, xs)
+    assert np.linalg.norm(xs.cpu().numpy() - want) < 1e-14 * np.linalg.norm(want)
+    fr = W.noise_rhs(N, 4)
+    wb = oracle.assemble_rhs(*f, O.flags, O.st, fr)
+    b = sol.assemble_rhs(at(fr)).cpu().numpy()
+    assert np.linalg.norm(b - wb) < 1e-14 * np.linalg.norm(wb)
