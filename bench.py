@@ -101,9 +101,9 @@ def sweep_roofline(P, sol, f, T, N, traffic):
     second phase (k_walk_up: prolongation and four half-sweeps in one pass):
     the RHS and the new iterate (T bytes per cell each), the black iterate it
     starts from (half of that) and the coarse correction (an eighth): 2.625 T
-    N bytes.  Otherwise the red/black half-sweep (k0_sweep): the other
-    colour's values, this colour's RHS and flag byte and its new values, over
-    N/2 cells each: (1.5 T + 0.5) N."""
+    N bytes.  Otherwise the red/black half-sweep (k_half with its rows below
+    2^21 cells, k0_sweep above): the other colour's values, this colour's RHS
+    and flag byte and its new values, over N/2 cells each: (1.5 T + 0.5) N."""
     name, bytes_launch = "k_walk_up", 2.625 * T * N
     sol.kernel_timing(P.KERNEL_WALK_UP)
     sol.solve(f)
@@ -112,7 +112,7 @@ def sweep_roofline(P, sol, f, T, N, traffic):
         sol.kernel_timing(-1)
         traffic = None  # counters are kept for the half-sweep
     else:
-        name, bytes_launch = "k0_sweep", (1.5 * T + 0.5) * N
+        name, bytes_launch = "k_half" if N < 1 << 21 else "k0_sweep", (1.5 * T + 0.5) * N
         sol.solve(f)
         tot, cnt = sol.kernel_timing(-1)
     if not cnt:
@@ -155,7 +155,7 @@ def solver_source_digest():
     counters describe only the version they were taken on."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hpp", "fused.hpp", "walk.hpp", "setup.hpp", "solver.hip", "common.hpp"):
+    for f in ("kernels.hpp", "fused.hpp", "walk.hpp", "rows.hpp", "setup.hpp", "solver.hip", "common.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2605_04335_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -558,8 +558,8 @@ def main():
                             "frac": round(ts64 / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                             "vs_model": round(ts64 / model, 3)}
     if roof:
-        log("fp64 %.1f ms/solve (%.1f Mpts/s, %d its); k0_sweep<double> %.1f GB/s (%.3f of peak); error vs oracle "
-            "sample %s" % (ms_per_step, value, s64.iterations, roof["achieved"], roof["frac"], err64))
+        log("fp64 %.1f ms/solve (%.1f Mpts/s, %d its); %s %.1f GB/s (%.3f of peak); error vs oracle "
+            "sample %s" % (ms_per_step, value, s64.iterations, roof["kernel"], roof["achieved"], roof["frac"], err64))
     x = None
 
     # ---- the mixed form on the same system

@@ -296,32 +296,6 @@ __device__ __forceinline__ double nbsum_all(const Lv &L, const T *xo, int h, int
     return acc;
 }
 
-// the diagonal alone (no vector is read): sum of the open faces' coefficients
-template <bool FINE>
-__device__ __forceinline__ double diag_only(const Lv &L, const uint8_t *fo, int h, int j, int k, int i, uint8_t fm)
-{
-    const int p = i & 1;
-    const long long row = (long long)L.H * (j + (long long)L.ny * k);
-    const long long pl = (long long)L.H * L.ny;
-    double d = 0.0;
-    if (FINE) {
-        if (i + 1 < L.nx) d += L.cp[0][i];
-        if (i > 0) d += L.cm[0][i];
-        if (j + 1 < L.ny) d += L.cp[1][j];
-        if (j > 0) d += L.cm[1][j];
-        if (k + 1 < L.nz) d += L.cp[2][k];
-        if (k > 0) d += L.cm[2][k];
-    } else {
-        if (fm & CM_PX) d += L.cp[0][i];
-        if (fm & CM_MX) d += L.cm[0][i];
-        if (fm & CM_PY) d += L.cp[1][j];
-        if (fm & CM_MY) d += L.cm[1][j];
-        if (fm & CM_PZ) d += L.cp[2][k];
-        if (fm & CM_MZ) d += L.cm[2][k];
-    }
-    return d;
-}
-
 // sparse level-0 rows (ghosts, membrane-adjacent cells, pin)
 struct Sp {
     long long N2;          // 2 Nh: first membrane ghost unknown
@@ -1677,18 +1651,6 @@ __device__ __forceinline__ double interp(const Lv &C, const PMap &M, const Tc *x
                        ty * ((1 - tx) * coarse_val(C, xc, I, J + 1, K) + tx * coarse_val(C, xc, I + 1, J + 1, K))) +
            tz * ((1 - ty) * ((1 - tx) * coarse_val(C, xc, I, J, K + 1) + tx * coarse_val(C, xc, I + 1, J, K + 1)) +
                  ty * ((1 - tx) * coarse_val(C, xc, I, J + 1, K + 1) + tx * coarse_val(C, xc, I + 1, J + 1, K + 1)));
-}
-
-template <bool FINE, class Tc, class Tf>
-__device__ __forceinline__ void prolong_one(const Lv &F, const Lv &C, const PMap &M, const Tc *xc, Tf *xf, int c,
-                                            int h, int j, int k)
-{
-    const long long s = slot(F, c, h, j, k);
-    const int i = 2 * h + ((c + j + k) & 1);
-    if (i >= F.nx) return;
-    const uint8_t f = F.f[s];
-    if (FINE ? !active0(f) : !(f & 1)) return;
-    st(xf, s, ld(xf, s) + interp(C, M, xc, i, j, k));
 }
 
 // Prolongation by coarse column: one thread per coarse (I, J) column walks
