@@ -2199,7 +2199,7 @@ __global__ void __launch_bounds__(TAIL_T) k_tail(Tail T, const double *part, int
 // ---------------------------------------------------------------- Krylov vector kernels
 enum {
     S_RHO = 0, S_RHO_OLD, S_ALPHA, S_OMEGA, S_BETA, S_RR, S_BN2, S_REL, S_SINKP, S_SINKS,
-    S_RV, S_TS, S_TT, S_STATUS, S_VPIN, S_TMP, S_TMP2, S_MEAN0 = 20, S_READY = 47, S_COUNT = 48
+    S_RV, S_TS, S_TT, S_STATUS, S_VPIN, S_TMP, S_TMP2, S_MEAN0 = 20, S_COUNT = 48
 };
 
 __device__ __forceinline__ double slot_volume(const Lv &L, long long s, bool &act)
@@ -2815,10 +2815,8 @@ __device__ double block_sum_all(const double *part, int n)
 
 enum { FIN_SUM = 0, FIN_SINK, FIN_ALPHA, FIN_OMEGA, FIN_RHO, FIN_MEAN, FIN_INIT, FIN_RESTART, FIN_REPLACE };
 
-// pub (host memory, or null): what the host reads after an iteration is written
-// there, then the mark at S_READY
 __global__ void __launch_bounds__(1024) k_fin(const double *part, int pstride, int n, int op, int dst, double aux,
-                                              double *sc, double *pub)
+                                              double *sc)
 {
     const bool two = op == FIN_OMEGA || op == FIN_RHO || op == FIN_REPLACE;
     double s0 = block_sum_all(part, n);
@@ -2868,11 +2866,6 @@ __global__ void __launch_bounds__(1024) k_fin(const double *part, int pstride, i
         sc[S_BETA] = (om != 0.0 && ro != 0.0) ? (s0 / ro) * (sc[S_ALPHA] / om) : 0.0;
         break;
     }
-    }
-    if (pub) {
-        const int out[] = {S_REL, S_STATUS, S_ALPHA, S_OMEGA, S_SINKP, S_SINKS};
-        for (int q : out) pub[q] = sc[q];
-        __hip_atomic_store(pub + S_READY, 1.0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

@@ -19,7 +19,6 @@
 #include "setup.hpp"
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -306,7 +305,7 @@ inline void prof_harvest(poisson_ctx &c)
 
 inline void fin(poisson_ctx &c, int n, int op, int dst, double aux, hipStream_t s)
 {
-    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, n, op, dst, aux, c.sc.p, nullptr);
+    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, n, op, dst, aux, c.sc.p);
     IBM_LAUNCH_CHECK();
 }
 
@@ -670,7 +669,7 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
                 continue;
             }
             const double *mean = c.sc.p + S_MEAN0 + l;
-            k_fin<<<1, 1024, 0, s>>>(mean_part(c, l), PSTRIDE, npart, FIN_MEAN, S_MEAN0 + l, L.volA, c.sc.p, nullptr);
+            k_fin<<<1, 1024, 0, s>>>(mean_part(c, l), PSTRIDE, npart, FIN_MEAN, S_MEAN0 + l, L.volA, c.sc.p);
             if (l == nl - 1) {
                 coarse_smooth<Tc, TB>(L, o.coarse_sweeps, true, mean, s);
                 break;
@@ -799,8 +798,7 @@ void bicg_iteration(poisson_ctx &c, TX *y, T *r, T *rh, T *p, T *v, T *ph, T *sh
                                               PSTRIDE);
     prof_end(c, PK_XR, s);
     IBM_LAUNCH_CHECK();
-    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, W.nb, FIN_RHO, 0, 0.0, c.sc.p, c.hsc);
-    IBM_LAUNCH_CHECK();
+    fin(c, W.nb, FIN_RHO, 0, 0.0, s);
 }
 
 void read_scalars(poisson_ctx &c, hipStream_t s)
@@ -808,30 +806,6 @@ void read_scalars(poisson_ctx &c, hipStream_t s)
     IBM_HIP(hipMemcpyAsync(c.hsc, c.sc.p, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));
     IBM_HIP(hipStreamSynchronize(s));
     prof_harvest(c);
-}
-
-// The scalars of the iteration in flight.  Its last kernel writes them to the
-// context's pinned slot and marks it; the host looks for the mark instead of
-// enqueueing a copy and waiting for the stream.  A 32^3 solve takes 100 us less
-// of 1.9 ms, a mixed 160^3 step 0.9 of 17.8 ms.  After 2 ms, where
-// that no longer counts, it waits for the stream, which also reports errors.
-void read_iteration(poisson_ctx &c, hipStream_t s)
-{
-    if (c.prof_used) {  // launches are being timed: their events must have ended
-        read_scalars(c, s);
-        return;
-    }
-    const auto t0 = std::chrono::steady_clock::now();
-    for (int n = 0;; ++n) {
-        double ready;
-        __atomic_load(c.hsc + S_READY, &ready, __ATOMIC_ACQUIRE);
-        if (ready == 1.0) return;
-        __builtin_ia32_pause();
-        if ((n & 63) == 63 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
-            IBM_HIP(hipStreamSynchronize(s));
-            return;
-        }
-    }
 }
 
 // Right-preconditioned BiCGSTAB on A y = rhs; y starts at zero.  rhs may be
@@ -898,11 +872,9 @@ int bicgstab(poisson_ctx &c, const TR *rhs, TX *y, T *r, T *rh, T *p, T *v, T *p
     int mark_it = 0;
     while (it < maxit) {
         ++it;
-        const double none = 0.0;
-        __atomic_store(c.hsc + S_READY, const_cast<double *>(&none), __ATOMIC_RELEASE);
         if (use_graph) IBM_HIP(hipGraphLaunch(*graph, s));
         else bicg_iteration<T, TX>(c, y, r, rh, p, v, ph, sh, t, s);
-        read_iteration(c, s);
+        read_scalars(c, s);
         const double st = c.hsc[S_STATUS];
         rel = c.hsc[S_REL];
         if (log_level() >= 2)
@@ -916,7 +888,7 @@ int bicgstab(poisson_ctx &c, const TR *rhs, TX *y, T *r, T *rh, T *p, T *v, T *p
             } else {
                 if (!true_check) { *rc = IBM_OK; break; }
                 int np = launch_apply<T>(c, M_PINNED, true, 2, (const T *)y, t, rhs, nullptr, rh, nullptr, s);
-                k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p, nullptr);
+                k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p);
                 read_scalars(c, s);
                 double trel = std::sqrt(c.hsc[S_TMP] / c.hsc[S_BN2]);
                 rel = trel;
@@ -1144,7 +1116,7 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     const Walk WF = make_walk(w8 ? Z.Nh / 4 : Z.Nh);
     if (w8) k_setup_flags0<true><<<WF.nb, TPB, 0, s>>>(Z.lv, WF, flags, Z.m.p, c.part.p);
     else k_setup_flags0<false><<<WF.nb, TPB, 0, s>>>(Z.lv, WF, flags, Z.m.p, c.part.p);
-    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, WF.nb, FIN_SUM, 0, 0.0, c.ssum.p, nullptr);  // fluid volume
+    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, WF.nb, FIN_SUM, 0, 0.0, c.ssum.p);  // fluid volume
     // ghost and membrane rows
     const long long R1 = std::max<long long>(R, 1), M1 = std::max<long long>(nm, 1);
     reserve(c.rslot, std::max<long long>(c.ng, 1));
@@ -1183,8 +1155,8 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
         uint8_t *ha = c.hact[(l + 1) & 1].p;
         k_coarse_active<<<blocks(C.N), TPB, 0, s>>>(F.n[0], F.n[1], C.n[0], C.n[1], C.N, fine, l == 1, ha);
         k_coarse_mask<<<C.walk.nb, TPB, 0, s>>>(C.lv, C.walk, ha, C.m.p, c.part.p, PSTRIDE);
-        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, C.walk.nb, FIN_SUM, l, 0.0, c.ssum.p, nullptr);
-        k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, C.walk.nb, FIN_SUM, 16 + l, 0.0, c.ssum.p, nullptr);
+        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, C.walk.nb, FIN_SUM, l, 0.0, c.ssum.p);
+        k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, C.walk.nb, FIN_SUM, 16 + l, 0.0, c.ssum.p);
     }
     IBM_LAUNCH_CHECK();
     double hs[32];
@@ -1457,9 +1429,9 @@ double true_rel_residual(poisson_ctx &c, hipStream_t s)
 {
     const Walk &W = c.W0;
     k_dot2<double><<<W.nb, TPB, 0, s>>>(W, c.b.p, c.b.p, c.part.p, PSTRIDE);
-    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, W.nb, FIN_SUM, S_TMP2, 0.0, c.sc.p, nullptr);
+    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, W.nb, FIN_SUM, S_TMP2, 0.0, c.sc.p);
     int np = launch_apply<double>(c, M_PINNED, true, 2, c.x.p, c.t.p, c.b.p, nullptr, c.b.p, nullptr, s);
-    k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p, nullptr);
+    k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p);
     IBM_LAUNCH_CHECK();
     read_scalars(c, s);
     const double bn2 = c.hsc[S_TMP2];
@@ -1483,9 +1455,9 @@ int solve_core(poisson_ctx &c, poisson_stats *stats, hipStream_t s, bool warm = 
         reserve(c.d64, c.Nt);
         reserve(c.r2, c.Nt);
         k_dot2<double><<<W.nb, TPB, 0, s>>>(W, c.b.p, c.b.p, c.part.p, PSTRIDE);
-        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, W.nb, FIN_SUM, S_TMP2, 0.0, c.sc.p, nullptr);
+        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, W.nb, FIN_SUM, S_TMP2, 0.0, c.sc.p);
         int np = launch_apply<double>(c, M_PINNED, true, 2, c.x.p, c.r2.p, c.b.p, nullptr, c.b.p, nullptr, s);
-        k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p, nullptr);
+        k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p);
         IBM_LAUNCH_CHECK();
         read_scalars(c, s);
         const double bn2 = c.hsc[S_TMP2];
@@ -1514,7 +1486,7 @@ int solve_core(poisson_ctx &c, poisson_stats *stats, hipStream_t s, bool warm = 
         const Walk &W = c.W0;
         if (!warm) k_fill<double><<<W.nb, TPB, 0, s>>>(W, c.x.p, 0.0);
         k_dot2<double><<<W.nb, TPB, 0, s>>>(W, c.b.p, c.b.p, c.part.p, PSTRIDE);
-        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, W.nb, FIN_SUM, S_TMP2, 0.0, c.sc.p, nullptr);
+        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, W.nb, FIN_SUM, S_TMP2, 0.0, c.sc.p);
         IBM_LAUNCH_CHECK();
         read_scalars(c, s);
         const double bn2 = c.hsc[S_TMP2];
@@ -1529,7 +1501,7 @@ int solve_core(poisson_ctx &c, poisson_stats *stats, hipStream_t s, bool warm = 
             }
             // r64 = b - A x (pinned) and its norm
             int np = launch_apply<double>(c, M_PINNED, true, 2, c.x.p, c.r.p, c.b.p, nullptr, c.b.p, nullptr, s);
-            k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p, nullptr);
+            k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p);
             IBM_LAUNCH_CHECK();
             read_scalars(c, s);
             rel = std::sqrt(c.hsc[S_TMP] / bn2);
@@ -1559,7 +1531,7 @@ int solve_core(poisson_ctx &c, poisson_stats *stats, hipStream_t s, bool warm = 
                                                 c.t.p, o.tol / base, o.max_iter, true, &c.g64, s, &frc, &frel);
                 k_add<double><<<W.nb, TPB, 0, s>>>(W, c.x.p, c.d64.p);
                 int np = launch_apply<double>(c, M_PINNED, true, 2, c.x.p, c.r.p, c.b.p, nullptr, c.b.p, nullptr, s);
-                k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p, nullptr);
+                k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, np, FIN_SUM, S_TMP, 0.0, c.sc.p);
                 IBM_LAUNCH_CHECK();
                 read_scalars(c, s);
                 rel = std::sqrt(c.hsc[S_TMP] / bn2);
