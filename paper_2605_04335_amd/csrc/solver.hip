@@ -832,7 +832,11 @@ int bicgstab(poisson_ctx &c, const TR *rhs, TX *y, T *r, T *rh, T *p, T *v, T *p
         *relout = 0.0;
         return 0;
     }
-    const bool use_graph = c.opts.use_graph && c.prof_kernel < 0;
+    // Only an iteration on one stream becomes a graph: with the near sequence
+    // beside the pass (from 2^23 cells) its launches are enqueued one by one.
+    // They take 20 us and more each there, longer than the host needs for one.
+    const bool forked = c.walk && c.beside && c.near.nb() > 0;
+    const bool use_graph = c.opts.use_graph && c.prof_kernel < 0 && !forked;
     if (use_graph && !*graph) {
         // a failure inside the capture still ends it, so the stream never
         // stays in capture mode (the user's stream joins it afterwards)
