@@ -48,3 +48,32 @@ def test_ad_sweep_pairs_match_oracle(shape, bodies, sweeps):
                                       oracle.ad_schedule(sweeps, beta, dg), tol=1e-300, maxcyc=3, x0=u0)
     assert cyc == 3
     assert np.linalg.norm(u.cpu().numpy() - want) < 1e-13 * np.linalg.norm(want)
+
+
+# the reported residual, from pairs of cells (even rows) and single ones (odd
+# rows, or an iterate off 16-byte alignment), against the operator's: sums of a
+# few thousand squares, 1e-12
+@pytest.mark.parametrize("shape", [(4, 4, 4), (130, 9, 37), (66, 21, 18), (35, 20, 17)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_ad_residual_of_the_last_iterate(shape, shift):
+    import torch
+    import paper_2605_04335_amd as P
+    print("[case] residual", shape, shift, flush=True)
+    L = [m / max(shape) for m in shape]
+    f = [W.uniform_faces(m, e) for m, e in zip(shape, L)]
+    s, c = min(L), [0.5 * e for e in L]
+    bl = [] if min(shape) < 8 else [W.sphere((c[0], c[1], c[2]), 0.25 * s, freq=4),
+                                    W.plate((c[0] - 0.3, c[1], c[2]), 0.3 * s, 0.4 * s, 6, 6, 0.0, 0.3)]
+    flags, _ = P.classify(*f, bl)
+    st = P.build_ghost_stencils(*f, bl, flags, bc="dirichlet")
+    fl = flags.cpu().numpy()
+    O = oracle.stencils(*f, bl, fl, bc="dirichlet")
+    beta = 4.0 / oracle.max_cell_scale(*f)
+    sol = P.AdSolver(*f, flags, st, beta, tol=1e-300, sweeps=2, max_cycles=1)
+    n = len(fl) + O.nm
+    rhs = W.noise_rhs(len(fl), 8)
+    u = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[shift:shift + n]
+    _, stats = sol.solve(torch.from_numpy(rhs).cuda(), None, u, check=False)
+    b = oracle.ad_rhs(*f, fl, O, rhs, None)
+    r = b - oracle.ad_apply(*f, fl, O, beta, u.cpu().numpy())
+    assert abs(stats.rel_residual / (np.linalg.norm(r) / np.linalg.norm(b)) - 1.0) < 1e-12
