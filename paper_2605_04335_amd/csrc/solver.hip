@@ -991,10 +991,12 @@ void reserve(DBuf<T> &b, size_t n)
     if (!b.p || b.n < n) b.alloc(n);
 }
 
+// (the passes keep a column's half-index and row in 16 bits each; longer boxes
+// take the one-sweep kernels)
 bool walk_wanted(const poisson_ctx &c)
 {
     return c.opts.precond == IBM_PRECOND_MG && c.opts.nu1 == 2 && c.opts.nu2 == 2 && c.lv.size() > 1 &&
-           c.N >= WALK_MIN_CELLS;
+           c.N >= WALK_MIN_CELLS && c.lv[0].H <= 0xffff && c.lv[0].n[1] <= 0xffff;
 }
 
 // Lists of the fused level-0 pass for the current classification: near and

@@ -98,6 +98,25 @@ def test_fused_pass_matches_oracle(shape, bodies):
     assert torch.equal(z, sol.precond(bt))
 
 
+# a box of more than 2^16 rows, or pairs of cells to a row, beyond the places a
+# pass can hold.  The same bound and comparison; the sink's sum is of the same
+# size as above.
+@pytest.mark.parametrize("shape", [(6, 65540, 6), (131080, 6, 6)])
+def test_longest_boxes_match_oracle(shape):
+    import torch
+    import paper_2605_04335_amd as P
+    print("[case] long", shape, flush=True)
+    f = [W.uniform_faces(m, m / 64.0) for m in shape]
+    O = oracle.setup(*f, [])
+    flags, st, sol, _ = P.setup(*f, [])
+    b = oracle.assemble_rhs(*f, O.flags, O.st, W.noise_rhs(len(O.flags), 47))
+    z = sol.precond(torch.from_numpy(b).cuda()).cpu().numpy()
+    zo = oracle.vcycle(*f, O.flags, O.st, b)
+    act = zo != 0.0
+    d = (z - zo)[act]
+    assert np.linalg.norm(d - d.mean()) < 1e-11 * np.linalg.norm(zo)
+
+
 def test_fused_pass_after_update_equals_fresh_setup():
     """The near units follow the bodies: a context updated to another geometry
     (and back to none) preconditions bit for bit as a fresh one."""
