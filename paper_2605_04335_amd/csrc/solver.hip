@@ -1794,6 +1794,51 @@ extern "C" int32_t poisson_precond(poisson_ctx *c, const double *b_dev, double *
     });
 }
 
+// Test hook, not part of the interface: what a mixed context's inner iterations
+// apply, x = V-cycle(b) in FP32 with BF16 coarse right-hand sides, unshifted
+// (poisson_precond takes FP64 contexts only).  first_phase != 0: the iterate
+// of level 0 after the smoothing steps before the coarse correction instead
+// (of the fused pass only its black cells leave the kernel: the rest is zero).
+// b and x hold N + n_mghost doubles; b is rounded to FP32 on the way in.
+extern "C" int32_t ibm_test_inner_precond(poisson_ctx *c, const double *b_dev, double *x_dev, int32_t first_phase,
+                                          void *stream)
+{
+    return guarded([&] {
+        IBM_REQUIRE(c && b_dev && x_dev && c->mixed && c->opts.precond == IBM_PRECOND_MG, IBM_EINVAL,
+                    "needs a mixed multigrid context");
+        StreamJoin j(*c, (hipStream_t)stream);
+        hipStream_t s = c->cs;
+        k_to_split<true><<<c->Wp.nb, TPB, 0, s>>>(c->L0(), c->Wp, b_dev, pairs_aligned(c->L0().nx, b_dev), c->r.p, c->nm,
+                                                  c->part.p);
+        fin(*c, c->Wp.nb, FIN_SINK, S_SINKP, 0.0, s);
+        k_copy<double, float><<<c->W0.nb, TPB, 0, s>>>(c->W0, c->r.p, c->fp.p);
+        const double *sink = c->sc.p + S_SINKP;
+        if (!first_phase) {
+            vcycle<float>(*c, c->fp.p, c->fph.p, c->ft.p, sink, s);
+            k_copy<float, double><<<c->W0.nb, TPB, 0, s>>>(c->W0, c->fph.p, c->t.p);
+        } else {
+            k_fill<double><<<c->W0.nb, TPB, 0, s>>>(c->W0, c->t.p, 0.0);
+            if (c->walk) {
+                (void)walk_down<float>(*c, c->fp.p, c->ft.p, c->frsp.p, c->fph.p, sink, s);
+                const int nu = c->near.nb();
+                if (nu) k_near_merge<float><<<nu, NU_T, 0, s>>>(c->L0(), c->near, c->ft.p, c->frsp.p);
+                const Walk Wb = make_walk(c->L0().Nh);
+                k_copy<float, double><<<Wb.nb, TPB, 0, s>>>(Wb, c->frsp.p, c->t.p + c->L0().Nh);
+            } else {
+                if (c->flat)
+                    rows_out<float>(*c, c->fph.p, c->fp.p,
+                                    half_sweeps<float, false>(*c, c->fph.p, c->fp.p, sink, 2 * c->opts.nu1, true, s),
+                                    (float *)nullptr, s);
+                else
+                    for (int it = 0; it < c->opts.nu1; ++it) fine_smooth<float>(*c, c->fph.p, c->fp.p, sink, it == 0, s);
+                k_copy<float, double><<<c->W0.nb, TPB, 0, s>>>(c->W0, c->fph.p, c->t.p);
+            }
+        }
+        from_split<OUT_PLAIN>(*c, c->t.p, x_dev, c->nm, s);
+        IBM_LAUNCH_CHECK();
+    });
+}
+
 extern "C" int32_t poisson_kernel_timing(poisson_ctx *c, int32_t kernel, int32_t reset, double *total_ms,
                                          int64_t *launches)
 {
