@@ -162,6 +162,13 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Right-hand sides wait in LDS, in the vectors' type, for their second use.  In
+// FP32 they wait as they were read and the pin's sink is subtracted again (the
+// difference is not an FP32 number); in FP64 less the sink, since to hold both
+// takes registers that the plane loop does not have (64 bytes spilled).
+template <class T>
+constexpr bool lag_raw = !std::is_same<T, double>::value;
+
 // neighbour sum of a cell with index q: centre, outer x and y neighbours from
 // the LDS plane at l, z neighbours zp and zm
 #define WALK_NB(q, l, xc, zp, zm, cp_, cm_)                                                                       \
@@ -216,6 +223,7 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
     const bool odd_row = w.jc() & 1;
     const bool lead = w.own && !odd_row;  // the even row of a pair writes the coarse cell
     __syncthreads();
+    constexpr bool RAW = lag_raw<T>;
     T bR[3], bB[3];
     double czp[6], czm[6], R1[3] = {}, B1[3] = {}, R2[3] = {}, B2[3] = {}, rdR[3] = {}, rdB[3] = {};
 #pragma unroll
@@ -252,7 +260,8 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
             T *const lw = lds + q * 4 * WK_PS + WK_PAD + w.p;
             const T *const lr = lds + (1 - q) * 4 * WK_PS + WK_PAD + w.p;
             // loads of later steps
-            double b0 = bR[s % 3], b1 = bB[(s + 2) % 3];  // red of plane k, black of plane k-1
+            const T r0 = bR[s % 3], r1 = bB[(s + 2) % 3];  // red of plane k, black of plane k-1
+            double b0 = r0, b1 = r1;
             bR[(s + 2) % 3] = ldu(bp[0] + pl * cz(k + 2), w.col);
             bB[(s + 1) % 3] = ldu(bp[1] + pl * cz(k + 1), w.col);
             czp[(s + 1) % 6] = uld(F.cp[2], cz(k + 1));
@@ -280,8 +289,9 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
                 const int m = (s + 4) % 6;
                 const double dg = w.dxy[q] + czp[m] + czm[m];
                 const double nb = WALK_NB(q, lr + WK_PS, B1[(s + 1) % 3], B1[(s + 2) % 3], B1[s % 3], czp[m], czm[m]);
-                const double b2 = lagb[q][tid];
-                lagb[q][tid] = (T)b0;
+                double b2 = lagb[q][tid];
+                lagb[q][tid] = RAW ? r0 : (T)b0;
+                if (RAW && pn.k >= 0 && pn.c == 0 && cz(k - 2) == pn.k && w.col == pn.col) b2 -= pn.sink;
                 const double v = (double)(T)quot(nb - b2, dg, rdR[(s + 1) % 3]);
                 R2[(s + 1) % 3] = v;
                 rk = b2 + dg * v;
@@ -290,8 +300,9 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
                 const int m = (s + 3) % 6;
                 const double dg = w.dxy[q] + czp[m] + czm[m];
                 const double nb = WALK_NB(q, lr + 2 * WK_PS, R2[s % 3], R2[(s + 1) % 3], R2[(s + 2) % 3], czp[m], czm[m]);
-                const double b3 = lagb[2 + q][tid];
-                lagb[2 + q][tid] = (T)b1;
+                double b3 = lagb[2 + q][tid];
+                lagb[2 + q][tid] = RAW ? r1 : (T)b1;
+                if (RAW && pn.k >= 0 && pn.c == 1 && cz(k - 3) == pn.k && w.col == pn.col) b3 -= pn.sink;
                 const T v = (T)quot(nb - b3, dg, rdB[s % 3]);
                 B2[s % 3] = (double)v;
                 lw[3 * WK_PS] = v;
@@ -392,6 +403,7 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
     }
     T cnext = cload(K0 + 2);
     double tz = upper(ks);
+    constexpr bool RAW = lag_raw<T>;
     T KB[3], bR[3], bB[3];
     double czp[6], czm[6], B0[3] = {}, R1[3] = {}, B1[3] = {}, R2[3] = {}, rdR[3] = {}, rdB[3] = {};
 #pragma unroll
@@ -416,7 +428,8 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
             T *const lw = lds + q * 4 * WK_PS + WK_PAD + w.p;
             const T *const lr = lds + (1 - q) * 4 * WK_PS + WK_PAD + w.p;
             KB[(s + 2) % 3] = ldu(xk + pl * cz(k + 2), w.col);
-            double b1 = bR[(s + 2) % 3], b2 = bB[(s + 1) % 3];  // red of plane k-1, black of plane k-2
+            const T r1 = bR[(s + 2) % 3], r2 = bB[(s + 1) % 3];  // red of plane k-1, black of plane k-2
+            double b1 = r1, b2 = r2;
             bR[(s + 1) % 3] = ldu(bp[0] + pl * cz(k + 1), w.col);
             bB[s % 3] = ldu(bp[1] + pl * cz(k), w.col);
             czp[(s + 1) % 6] = uld(F.cp[2], cz(k + 1));
@@ -463,8 +476,9 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
                 const double dg = w.dxy[1 - q] + czp[m] + czm[m];
                 const double nb =
                     WALK_NB(1 - q, lr + 2 * WK_PS, B1[s % 3], B1[(s + 1) % 3], B1[(s + 2) % 3], czp[m], czm[m]);
-                const double b3 = lagb[q][tid];
-                lagb[q][tid] = (T)b1;
+                double b3 = lagb[q][tid];
+                lagb[q][tid] = RAW ? r1 : (T)b1;
+                if (RAW && pn.k >= 0 && pn.c == 0 && cz(k - 3) == pn.k && w.col == pn.col) b3 -= pn.sink;
                 const T v = (T)quot(nb - b3, dg, rdR[s % 3]);
                 R2[s % 3] = (double)v;
                 lw[3 * WK_PS] = v;
@@ -475,8 +489,9 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
                 const double dg = w.dxy[1 - q] + czp[m] + czm[m];
                 const double nb =
                     WALK_NB(1 - q, lr + 3 * WK_PS, R2[(s + 2) % 3], R2[s % 3], R2[(s + 1) % 3], czp[m], czm[m]);
-                const double b4 = lagb[2 + q][tid];
-                lagb[2 + q][tid] = (T)b2;
+                double b4 = lagb[2 + q][tid];
+                lagb[2 + q][tid] = RAW ? r2 : (T)b2;
+                if (RAW && pn.k >= 0 && pn.c == 1 && cz(k - 4) == pn.k && w.col == pn.col) b4 -= pn.sink;
                 const T v = (T)quot(nb - b4, dg, rdB[(s + 2) % 3]);
                 if (w.own && k - 4 >= S.k0 && k - 4 < S.k1) stu_nt(x + F.Nh + pl * (k - 4), w.col, v);
             }

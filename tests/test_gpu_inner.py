@@ -166,3 +166,21 @@ def test_other_routes_of_level_0(shape, bodies, nu1, nu2):
     zo = oracle.vcycle(*f, O.flags, O.st, b, nu1, nu2, 32)
     d = (z.cpu().numpy() - zo)[zo != 0.0]
     assert np.linalg.norm(d - d.mean()) < 1e-11 * np.linalg.norm(zo)
+
+
+# The pin's right-hand side less the sink is not an FP32 number and is used in
+# FP64 in every half-sweep: the pin's neighbours after two steps of the fused
+# pass, over draws, equal the half-sweeps' to the bit (a corner of eight cells
+# per axis holds all they depend on).
+def test_the_sink_stays_in_fp64():
+    import paper_2605_04335_amd as P
+    shape, n = (128, 128, 128), 8
+    f, _ = box_case(*shape, "")
+    flags, st, sol, _ = P.setup(*f, [], precision="mixed")
+    off = []
+    for seed in range(24):
+        b = W.noise_rhs(shape[0] ** 3, 60 + seed).astype(np.float32).astype(np.float64)
+        z = inner(P, sol, b, 1).cpu().numpy().reshape(shape[::-1])
+        want, _ = smoothed(f, b.reshape(shape[::-1])[:n, :n, :n], b.sum(), 2)
+        off += [z[k] - want[k] for k in ((0, 0, 1), (0, 1, 0), (1, 0, 0))]
+    assert not np.any(off), "%d of %d values off, by up to %.1e" % (np.count_nonzero(off), len(off), np.abs(off).max())
