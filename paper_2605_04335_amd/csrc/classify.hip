@@ -112,6 +112,7 @@ struct RayBatch {
     RayBody body[RAY_BODIES];
 };
 constexpr int RAY_LANES = 16;  // per triangle
+constexpr unsigned PAR_BLOCKS = 1 << 16;  // of one body: its wavefronts take several rays each beyond
 
 // Triangles of body blockIdx.y along axis blockIdx.z (closed bodies: x only):
 // every covered ray flips the bit of the first cell whose centre lies strictly
@@ -186,23 +187,25 @@ __global__ void __launch_bounds__(256) k_rays(RayBatch A)
 __global__ void __launch_bounds__(256) k_ray_parity(RayBatch A, uint8_t *flags)
 {
     const RayBody &B = A.body[blockIdx.y];
-    const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (!B.closed || r >= (long long)B.ext[1] * B.ext[2]) return;
+    if (!B.closed) return;
     const int lane = threadIdx.x & 63, nx = A.n[0];
-    const int y = B.at[1] + (int)(r % B.ext[1]), z = B.at[2] + (int)(r / B.ext[1]);
-    uint8_t *row = flags + (long long)nx * (y + (long long)A.n[1] * z);
-    int carry = 0;
-    for (int x0 = 0; x0 < B.ext[0]; x0 += 64) {
-        const int x = x0 + lane;
-        const long long q = r * B.ext[0] + x;
-        const bool on = x < B.ext[0] && ((A.tog[B.w0 + (q >> 5)] >> (q & 31)) & 1u);
-        const unsigned long long m = __ballot(on);
-        const unsigned long long upto = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1ull;
-        if (x < B.ext[0] && ((carry + __popcll(m & upto)) & 1)) row[B.at[0] + x] = F_SOLID;
-        carry += __popcll(m);
+    const long long rays = (long long)B.ext[1] * B.ext[2];
+    for (long long r = 4LL * blockIdx.x + (threadIdx.x >> 6); r < rays; r += 4LL * gridDim.x) {
+        const int y = B.at[1] + (int)(r % B.ext[1]), z = B.at[2] + (int)(r / B.ext[1]);
+        uint8_t *row = flags + (long long)nx * (y + (long long)A.n[1] * z);
+        int carry = 0;
+        for (int x0 = 0; x0 < B.ext[0]; x0 += 64) {
+            const int x = x0 + lane;
+            const long long q = r * B.ext[0] + x;
+            const bool on = x < B.ext[0] && ((A.tog[B.w0 + (q >> 5)] >> (q & 31)) & 1u);
+            const unsigned long long m = __ballot(on);
+            const unsigned long long upto = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1ull;
+            if (x < B.ext[0] && ((carry + __popcll(m & upto)) & 1)) row[B.at[0] + x] = F_SOLID;
+            carry += __popcll(m);
+        }
+        if (carry & 1)
+            for (int x = B.at[0] + B.ext[0] + lane; x < nx; x += 64) row[x] = F_SOLID;
     }
-    if (carry & 1)
-        for (int x = B.at[0] + B.ext[0] + lane; x < nx; x += 64) row[x] = F_SOLID;
 }
 
 __device__ __forceinline__ bool bit(const uint32_t *b, long long c) { return (b[c >> 5] >> (c & 31)) & 1u; }
@@ -485,7 +488,7 @@ void classify_with(const ClassifyPlan &plan, const ibm_body *bodies, int n_body,
         if (!nb) return;
         if (used) k_fill_u32<<<(unsigned)std::min<long long>(2048, (used + 255) / 256), 256, 0, s>>>(S.tog, used, 0u);
         k_rays<<<dim3(cdiv((long long)most * RAY_LANES, 256), nb, mem ? 3 : 1), 256, 0, s>>>(A);
-        if (rays) k_ray_parity<<<dim3(cdiv(rays, 4), nb), 256, 0, s>>>(A, flags);
+        if (rays) k_ray_parity<<<dim3(std::min(cdiv(rays, 4), PAR_BLOCKS), nb), 256, 0, s>>>(A, flags);
         IBM_LAUNCH_CHECK();
         nb = most = 0;
         used = rays = 0;
