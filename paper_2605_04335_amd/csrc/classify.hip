@@ -9,7 +9,7 @@
 // to the triangle for which that edge is "top-left" (d_w < 0, or d_w == 0 and
 // d_u > 0), the same as perturbing the ray by (+e, +e^2).
 //
-// GPU form: sixteen lanes per triangle walk the rays its projected bounding
+// GPU form: up to sixteen lanes per triangle walk the rays its projected bounding
 // box covers, find the first cell beyond the crossing by binary search and flip
 // one bit of a toggle bitset with an integer atomic XOR; one wavefront per ray
 // then turns toggles into parity.  A closed body's toggles cover its own box of
@@ -95,34 +95,53 @@ __device__ __forceinline__ int lower_bound_ll(const long long *a, int n, long lo
 
 // One body of a launch.  Closed: its toggles are one bit per cell of its box
 // [at, at + ext), x fastest, from word w0 of the bitset; every cell that a
-// crossing of the body can toggle lies in the box.
+// crossing of the body can toggle lies in the box.  Its blocks of the two
+// launches are [rays, rays + nray) per axis and [par, par + npar).
 struct RayBody {
     const double *v;     // vertices
     const int32_t *tri;
     int nt, closed;
     int at[3], ext[3];
     long long w0;
+    int lanes;           // per triangle: log2
+    int rays, nray, par, npar;
 };
-constexpr int RAY_BODIES = 40;  // per launch: the descriptions travel as a kernel argument (3 of 4 KiB)
+constexpr int RAY_BODIES = 40;  // per launch: the descriptions travel as a kernel argument (3.3 of 4 KiB)
 struct RayBatch {
     Lat lat;
     const long long *qc[3];  // lattice centres per axis
-    int n[3];
+    int n[3], nb;
     uint32_t *tog, *cut[3];
     RayBody body[RAY_BODIES];
 };
-constexpr int RAY_LANES = 16;  // per triangle
-constexpr unsigned PAR_BLOCKS = 1 << 16;  // of one body: its wavefronts take several rays each beyond
+// Lanes per triangle: as many as a triangle has rays on average (its box holds
+// about four times its share of the body's projection), at most sixteen.  A
+// call at 256^3 with a body of 200 thousand triangles: 714 us with sixteen for
+// every triangle, 638 with this; with 2 million 5.7 and 5.0 ms.
+constexpr int RAY_LANES = 4;         // log2
+constexpr int PAR_BLOCKS = 1 << 16;  // of one body: its wavefronts take several rays each beyond
 
-// Triangles of body blockIdx.y along axis blockIdx.z (closed bodies: x only):
-// every covered ray flips the bit of the first cell whose centre lies strictly
-// beyond the crossing (closed), or the link just before it (membrane).
+// body of the launch that block i belongs to: the last whose first block (m) is not behind it
+__device__ __forceinline__ int body_of(const RayBatch &A, int RayBody::*m, int i)
+{
+    int lo = 0, hi = A.nb - 1;
+    while (lo < hi) {
+        const int q = (lo + hi + 1) >> 1;
+        if (A.body[q].*m <= i) lo = q; else hi = q - 1;
+    }
+    return lo;
+}
+
+// Triangles of a body along one axis (closed bodies: x only): every covered ray
+// flips the bit of the first cell whose centre lies strictly beyond the crossing
+// (closed), or the link just before it (membrane).  Each body has the blocks
+// that its triangles need, whatever mesh stands beside it in the launch.
 __global__ void __launch_bounds__(256) k_rays(RayBatch A)
 {
-    const RayBody &B = A.body[blockIdx.y];
-    const int d = (int)blockIdx.z;
-    if (B.closed && d > 0) return;
-    const int t = (int)((blockIdx.x * 256u + threadIdx.x) / RAY_LANES), lane = threadIdx.x % RAY_LANES;
+    const RayBody &B = A.body[body_of(A, &RayBody::rays, (int)blockIdx.x)];
+    const int q0 = (int)blockIdx.x - B.rays, d = q0 / B.nray, lanes = 1 << B.lanes;
+    const uint32_t th = (uint32_t)(q0 - d * B.nray) * 256u + threadIdx.x;
+    const int t = (int)(th >> B.lanes), lane = (int)th & (lanes - 1);
     if (t >= B.nt) return;
     const int u = (d + 1) % 3, w = (d + 2) % 3;
     long long P[3][3];
@@ -153,7 +172,7 @@ __global__ void __launch_bounds__(256) k_rays(RayBatch A)
     const int na = lower_bound_ll(qu, nu, umax + 1) - ia0, nb = lower_bound_ll(qw, nw, wmax + 1) - ib0;
     const long long rays = (long long)na * nb;
     const long long st[3] = {1, A.n[0], (long long)A.n[0] * A.n[1]};
-    for (long long r = lane; r < rays; r += RAY_LANES) {
+    for (long long r = lane; r < rays; r += lanes) {
         const int ia = ia0 + (int)(r / nb), ib = ib0 + (int)(r % nb);
         long long X[3];
         X[d] = 0;
@@ -186,11 +205,10 @@ __global__ void __launch_bounds__(256) k_rays(RayBatch A)
 // (Bodies of one launch that overlap store the same byte.)
 __global__ void __launch_bounds__(256) k_ray_parity(RayBatch A, uint8_t *flags)
 {
-    const RayBody &B = A.body[blockIdx.y];
-    if (!B.closed) return;
+    const RayBody &B = A.body[body_of(A, &RayBody::par, (int)blockIdx.x)];
     const int lane = threadIdx.x & 63, nx = A.n[0];
     const long long rays = (long long)B.ext[1] * B.ext[2];
-    for (long long r = 4LL * blockIdx.x + (threadIdx.x >> 6); r < rays; r += 4LL * gridDim.x) {
+    for (long long r = 4LL * ((int)blockIdx.x - B.par) + (threadIdx.x >> 6); r < rays; r += 4LL * B.npar) {
         const int y = B.at[1] + (int)(r % B.ext[1]), z = B.at[2] + (int)(r / B.ext[1]);
         uint8_t *row = flags + (long long)nx * (y + (long long)A.n[1] * z);
         int carry = 0;
@@ -369,24 +387,33 @@ size_t classify_bytes(const HostGrid &g, const ibm_body *bodies, int n_body, boo
     return C.off;
 }
 
-// What a classification uses: centres, vertices and triangles (one copy from
-// the host), then the bitsets and the counters.
+// What a classification uses: centres and the small bodies' vertices and
+// triangles (one copy from the host), the large bodies' (a copy each from where
+// the caller holds them), then the bitsets and the counters.
+// Largest body of the common copy.  Twenty bodies of 368 KB at 256^3: 1.09 ms a
+// call staged, 1.22 with two copies each; of 750 KB 2.19 and 1.92; one of 48 MB
+// 15.6 and 5.0.
+constexpr size_t STAGE_BYTES = 512 << 10;
+size_t body_bytes(const ibm_body &B) { return 24 * (size_t)B.n_vert + 12 * (size_t)B.n_tri; }
 struct ClassifyScratch {
     long long *qc[3];
-    double *vert;
-    int32_t *tri;
-    size_t input;  // bytes up to here come from the host
+    double *vert[2];  // small, large
+    int32_t *tri[2];
+    size_t input;  // bytes up to here come in the one copy
     uint32_t *tog = nullptr, *cut[3] = {nullptr, nullptr, nullptr};
     unsigned long long *dev;
 };
-ClassifyScratch carve_classify(Carve &C, const HostGrid &g, size_t nv, size_t nt, bool any_closed, bool any_mem)
+ClassifyScratch carve_classify(Carve &C, const HostGrid &g, const size_t nv[2], const size_t nt[2], bool any_closed,
+                               bool any_mem)
 {
     ClassifyScratch S;
     const size_t words = (size_t)(((long long)g.n[0] * g.n[1] * g.n[2] + 31) / 32 + 1);
     for (int d = 0; d < 3; ++d) S.qc[d] = C.take<long long>(g.n[d]);
-    S.vert = C.take<double>(3 * nv);
-    S.tri = C.take<int32_t>(3 * nt);
+    S.vert[0] = C.take<double>(3 * nv[0]);
+    S.tri[0] = C.take<int32_t>(3 * nt[0]);
     S.input = C.off;
+    S.vert[1] = C.take<double>(3 * nv[1]);
+    S.tri[1] = C.take<int32_t>(3 * nt[1]);
     if (any_closed) S.tog = C.take<uint32_t>(words);
     if (any_mem)
         for (int d = 0; d < 3; ++d) S.cut[d] = C.take<uint32_t>(words);
@@ -397,7 +424,11 @@ ClassifyScratch carve_classify(Carve &C, const HostGrid &g, size_t nv, size_t nt
 struct ClassifyPlan {
     HostGrid g;
     bool any_closed = false, any_mem = false;
-    size_t bytes = 0;  // device scratch the classification needs
+    size_t bytes = 0;  // device scratch the classification is charged with
+    struct Box {
+        double lo[3], hi[3];
+    };
+    std::vector<Box> box;  // of each body's vertices
 };
 
 // Argument checks and the scratch size; nothing touches the device.
@@ -408,18 +439,29 @@ ClassifyPlan plan_classify(const ibm_grid *grid, const ibm_body *bodies, int n_b
     const HostGrid &g = P.g;
     IBM_REQUIRE(flags != nullptr, IBM_EINVAL, "null flags");
     IBM_REQUIRE(n_body >= 0 && (n_body == 0 || bodies != nullptr), IBM_EINVAL, "bad body list");
+    double least[3], most[3];
+    for (int d = 0; d < 3; ++d) {
+        const double Ld = g.f[d][g.n[d]] - g.f[d][0];
+        least[d] = g.f[d][0] - Ld;
+        most[d] = g.f[d][g.n[d]] + Ld;
+    }
     for (int b = 0; b < n_body; ++b) {
         const ibm_body &B = bodies[b];
         IBM_REQUIRE(B.kind == IBM_KIND_CLOSED || B.kind == IBM_KIND_MEMBRANE, IBM_EINVAL, "bad body kind");
         (B.kind == IBM_KIND_CLOSED ? P.any_closed : P.any_mem) = true;
         IBM_REQUIRE(B.n_vert >= 3 && B.n_tri >= 1 && B.vert && B.tri, IBM_EINVAL, "empty body");
-        for (int v = 0; v < 3 * B.n_vert; ++v) {
-            int d = v % 3;
-            double x = B.vert[v];
-            double Ld = g.f[d][g.n[d]] - g.f[d][0];
-            IBM_REQUIRE(std::isfinite(x) && x >= g.f[d][0] - Ld && x <= g.f[d][g.n[d]] + Ld, IBM_EINVAL,
-                        "body vertex more than one domain length outside the domain");
-        }
+        ClassifyPlan::Box X;
+        for (int d = 0; d < 3; ++d) X.lo[d] = X.hi[d] = B.vert[d];
+        bool inside = true;
+        for (int v = 0; v < B.n_vert; ++v)
+            for (int d = 0; d < 3; ++d) {
+                const double x = B.vert[3 * (size_t)v + d];
+                inside = inside && std::isfinite(x) && x >= least[d] && x <= most[d];
+                X.lo[d] = std::min(X.lo[d], x);
+                X.hi[d] = std::max(X.hi[d], x);
+            }
+        IBM_REQUIRE(inside, IBM_EINVAL, "body vertex more than one domain length outside the domain");
+        P.box.push_back(X);
         for (int t = 0; t < 3 * B.n_tri; ++t)
             IBM_REQUIRE(B.tri[t] >= 0 && B.tri[t] < B.n_vert, IBM_EGEOM, "triangle index out of range");
     }
@@ -439,17 +481,17 @@ void classify_with(const ClassifyPlan &plan, const ibm_body *bodies, int n_body,
     Lat lat;
     lat.S = 65536.0 / L;
     for (int d = 0; d < 3; ++d) lat.lo[d] = g.f[d][0];
-    size_t nv = 0, nt = 0;
+    size_t nv[2] = {0, 0}, nt[2] = {0, 0};
     for (int b = 0; b < n_body; ++b) {
-        nv += bodies[b].n_vert;
-        nt += bodies[b].n_tri;
+        const int big = body_bytes(bodies[b]) > STAGE_BYTES;
+        nv[big] += bodies[b].n_vert;
+        nt[big] += bodies[b].n_tri;
     }
     Carve C;
     C.base = scratch;
     const ClassifyScratch S = carve_classify(C, g, nv, nt, plan.any_closed, plan.any_mem);
     IBM_REQUIRE(C.off <= plan.bytes, IBM_EINVAL, "classification scratch above its plan");
 
-    // centres, vertices and triangles go up in one copy
     std::vector<char> image(S.input);
     std::vector<long long> qc[3];
     for (int d = 0; d < 3; ++d) {
@@ -457,13 +499,24 @@ void classify_with(const ClassifyPlan &plan, const ibm_body *bodies, int n_body,
         for (int i = 0; i < g.n[d]; ++i) qc[d][i] = qnt(0.5 * (g.f[d][i] + g.f[d][i + 1]), lat.lo[d], lat.S);
         std::memcpy(image.data() + ((char *)S.qc[d] - scratch), qc[d].data(), g.n[d] * sizeof(long long));
     }
-    char *hv = image.data() + ((char *)S.vert - scratch), *ht = image.data() + ((char *)S.tri - scratch);
+    const double *dv[2] = {S.vert[0], S.vert[1]};
+    const int32_t *dt[2] = {S.tri[0], S.tri[1]};
+    std::vector<RayBody> body(n_body);
     for (int b = 0; b < n_body; ++b) {
-        const size_t bv = (size_t)3 * bodies[b].n_vert * sizeof(double), bt = (size_t)3 * bodies[b].n_tri * sizeof(int32_t);
-        std::memcpy(hv, bodies[b].vert, bv);
-        std::memcpy(ht, bodies[b].tri, bt);
-        hv += bv;
-        ht += bt;
+        const ibm_body &B = bodies[b];
+        const int big = body_bytes(B) > STAGE_BYTES;
+        RayBody &R = body[b];
+        R = RayBody{dv[big], dt[big], B.n_tri, B.kind == IBM_KIND_CLOSED, {0, 0, 0}, {0, 0, 0}, 0, 0, 0, 0, 0, 0};
+        dv[big] += 3 * (size_t)B.n_vert;
+        dt[big] += 3 * (size_t)B.n_tri;
+        const size_t bv = (size_t)3 * B.n_vert * sizeof(double), bt = (size_t)3 * B.n_tri * sizeof(int32_t);
+        if (big) {
+            IBM_HIP(hipMemcpyAsync((void *)R.v, B.vert, bv, hipMemcpyHostToDevice, s));
+            IBM_HIP(hipMemcpyAsync((void *)R.tri, B.tri, bt, hipMemcpyHostToDevice, s));
+        } else {
+            std::memcpy(image.data() + ((const char *)R.v - scratch), B.vert, bv);
+            std::memcpy(image.data() + ((const char *)R.tri - scratch), B.tri, bt);
+        }
     }
     IBM_HIP(hipMemcpyAsync(scratch, image.data(), S.input, hipMemcpyHostToDevice, s));
     k_fill_u8<<<2048, 256, 0, s>>>(flags, N, 0);
@@ -481,51 +534,44 @@ void classify_with(const ClassifyPlan &plan, const ibm_body *bodies, int n_body,
         A.n[d] = g.n[d];
         A.cut[d] = S.cut[d];
     }
-    int nb = 0, most = 0;   // bodies of the launch, its most triangles
-    long long used = 0, rays = 0;  // toggle words, most rays of a closed body
-    bool mem = false;
+    A.nb = 0;
+    int rays = 0, par = 0;  // blocks of the two launches
+    long long used = 0;     // toggle words
     auto flush = [&] {
-        if (!nb) return;
+        if (!A.nb) return;
         if (used) k_fill_u32<<<(unsigned)std::min<long long>(2048, (used + 255) / 256), 256, 0, s>>>(S.tog, used, 0u);
-        k_rays<<<dim3(cdiv((long long)most * RAY_LANES, 256), nb, mem ? 3 : 1), 256, 0, s>>>(A);
-        if (rays) k_ray_parity<<<dim3(std::min(cdiv(rays, 4), PAR_BLOCKS), nb), 256, 0, s>>>(A, flags);
+        k_rays<<<rays, 256, 0, s>>>(A);
+        if (par) k_ray_parity<<<par, 256, 0, s>>>(A, flags);
         IBM_LAUNCH_CHECK();
-        nb = most = 0;
-        used = rays = 0;
-        mem = false;
+        A.nb = rays = par = 0;
+        used = 0;
     };
-    size_t v0 = 0, t0 = 0;
     for (int b = 0; b < n_body; ++b) {
-        const ibm_body &B = bodies[b];
-        RayBody R{S.vert + 3 * v0, S.tri + 3 * t0, B.n_tri, B.kind == IBM_KIND_CLOSED, {0, 0, 0}, {0, 0, 0}, 0};
-        v0 += B.n_vert;
-        t0 += B.n_tri;
-        long long need = 0;
-        if (R.closed) {
-            // a crossing lies within the body's lattice box, the first centre
-            // beyond it at most one past the last centre inside
-            for (int d = 0; d < 3; ++d) {
-                double lo = B.vert[d], hi = B.vert[d];
-                for (int v = 1; v < B.n_vert; ++v) {
-                    lo = std::min(lo, B.vert[3 * (size_t)v + d]);
-                    hi = std::max(hi, B.vert[3 * (size_t)v + d]);
-                }
-                const auto &q = qc[d];
-                const int a = (int)(std::lower_bound(q.begin(), q.end(), qnt(lo, lat.lo[d], lat.S)) - q.begin());
-                const int e = (int)(std::upper_bound(q.begin(), q.end(), qnt(hi, lat.lo[d], lat.S)) - q.begin());
-                R.at[d] = a;
-                R.ext[d] = std::max(0, std::min(g.n[d], d == 0 ? e + 1 : e) - a);
-            }
-            if (!R.ext[0] || !R.ext[1] || !R.ext[2]) continue;  // no ray meets it within the domain
-            need = ((long long)R.ext[0] * R.ext[1] * R.ext[2] + 31) / 32;
+        RayBody &R = body[b];
+        // a crossing lies within the body's lattice box, the first centre
+        // beyond it at most one past the last centre inside
+        for (int d = 0; d < 3; ++d) {
+            const auto &q = qc[d];
+            const int a = (int)(std::lower_bound(q.begin(), q.end(), qnt(plan.box[b].lo[d], lat.lo[d], lat.S)) - q.begin());
+            const int e = (int)(std::upper_bound(q.begin(), q.end(), qnt(plan.box[b].hi[d], lat.lo[d], lat.S)) - q.begin());
+            R.at[d] = a;
+            R.ext[d] = std::max(0, std::min(g.n[d], R.closed && d == 0 ? e + 1 : e) - a);
         }
-        if (nb == RAY_BODIES || used + need > words) flush();
+        const long long x = R.ext[0], y = R.ext[1], z = R.ext[2], box = x * y * z;
+        if (R.closed && !box) continue;  // no ray meets it within the domain
+        const long long need = R.closed ? (box + 31) / 32 : 0, proj = R.closed ? y * z : std::max(y * z, std::max(z * x, x * y));
+        while (R.lanes < RAY_LANES && ((long long)R.nt << R.lanes) < std::min(4 * proj, 1LL << 28)) ++R.lanes;
+        R.nray = (int)cdiv((long long)R.nt << R.lanes, 256);
+        R.npar = R.closed ? (int)std::min<long long>((y * z + 3) / 4, PAR_BLOCKS) : 0;
+        // (2^23 blocks: a launch of fewer than 2^32 threads, which is the limit)
+        if (A.nb == RAY_BODIES || used + need > words || (A.nb && rays + 3LL * R.nray > 1 << 23)) flush();
         R.w0 = used;
+        R.rays = rays;
+        R.par = par;
         used += need;
-        if (R.closed) rays = std::max(rays, (long long)R.ext[1] * R.ext[2]);
-        else mem = true;
-        most = std::max(most, B.n_tri);
-        A.body[nb++] = R;
+        rays += R.closed ? R.nray : 3 * R.nray;
+        par += R.npar;
+        A.body[A.nb++] = R;
     }
     flush();
     k_init_counters<<<1, 64, 0, s>>>(S.dev);

@@ -1,11 +1,34 @@
-"""Geometry set-up of grids far larger than the rest of the tests': rays and rows
-beyond what one launch takes."""
+"""Geometry set-up of meshes and grids far larger than the rest of the tests',
+which take launches of another shape: more triangles than cells, meshes that go
+to the device from where the caller holds them, rays and rows beyond what one
+launch takes."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2605_04335_amd import workloads as W
+from tests.test_gpu_setup import crowd, faces
 
 pytestmark = pytest.mark.gpu
+
+
+# fine meshes (one lane per triangle) and coarse ones (sixteen) in the same
+# launches, closed bodies and membranes, more bodies than a launch takes, some
+# outside the domain: every flag byte equal
+@pytest.mark.parametrize("order", ["fine first", "fine last", "fine alone"])
+def test_classification_of_fine_and_coarse_meshes(order):
+    import paper_2605_04335_amd as P
+    print("[case] fine and coarse", order, flush=True)
+    f = faces(48, 44, 40)
+    fine = [W.sphere((0.5, 0.45, 0.4), 0.2, freq=60), W.plate((0.4, 0.4, 0.4), 0.5, 0.5, 90, 110, 0.02, 0.3),
+            W.sphere((1.2, 0.4, 0.4), 0.15, freq=40)]
+    coarse = crowd(f, 45, 3) + [W.plate((0.6, 0.5, 0.4), 0.5, 0.4, 2, 3, 0.0, 0.9), W.box((0.1, 0.1, 0.1), (0.3, 0.6, 0.2))]
+    bodies = {"fine first": fine + coarse, "fine last": coarse + fine, "fine alone": fine}[order]
+    want = oracle.classify(*f, bodies)
+    got, cst = P.classify(*f, bodies)
+    assert np.array_equal(got.cpu().numpy(), want)
+    got, cst, need = P.classify_noalloc(*f, bodies)
+    assert np.array_equal(got.cpu().numpy(), want)
 
 
 def slab():
