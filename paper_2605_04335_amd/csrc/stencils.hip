@@ -311,10 +311,10 @@ __global__ void __launch_bounds__(64) k_body_boxes(Tris T)
 // rounding.  Then every triangle of every run within the bound, a run to half
 // a wavefront.  The smallest distance wins and on equal ones the first
 // triangle, as in a plain scan.
-__global__ void __launch_bounds__(256) k_nearest(Tris T, GridD G, const int32_t *cells, int ng, int nrows, double *geo,
-                                                 int32_t *near)
+__global__ void __launch_bounds__(256) k_nearest(Tris T, GridD G, const int32_t *cells, int r0, int ng, int nrows,
+                                                 double *geo, int32_t *near)
 {
-    const int r = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int r = r0 + (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (r >= nrows) return;
     const int32_t cell = cells[r];
     const int nx = G.n[0], ny = G.n[1];
@@ -794,7 +794,10 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
                 k_run_boxes<<<cdiv((long long)nr * TGROUP, 256), 256, 0, s>>>(T);
                 k_body_boxes<<<nb, 64, 0, s>>>(T);
             }
-            k_nearest<<<cdiv(rows, 4), 256, 0, s>>>(T, G, S->cell.p, (int)S->ng, (int)rows, S->geo.p, near.p);
+            // (a launch has less than 2^32 threads: 2^24 rows of a wavefront each at a time)
+            for (int64_t r0 = 0; r0 < rows; r0 += 1 << 24)
+                k_nearest<<<cdiv(std::min<int64_t>(rows - r0, 1 << 24), 4), 256, 0, s>>>(
+                    T, G, S->cell.p, (int)r0, (int)S->ng, (int)rows, S->geo.p, near.p);
             k_stencil<<<cdiv(rows, 64), 64, 0, s>>>(T, G, flags, S->cell.p, near.p, (int)S->ng, (int)rows,
                                                    S->cell.p + S->ng, (int)S->nm, N, bc, O);
             IBM_LAUNCH_CHECK();

@@ -31,9 +31,9 @@ def test_classification_of_fine_and_coarse_meshes(order):
     assert np.array_equal(got.cpu().numpy(), want)
 
 
-def slab():
-    """4 x 8208 x 8208 cells, the layer x = 1 solid, between two sheets across the box: 67.4 million rays."""
-    n, m = 8208, 64
+def slab(n=8208):
+    """4 x n x n cells, the layer x = 1 solid, between two sheets across the box; 8208: 67.4 million rays and rows."""
+    m = 64
     f = [np.arange(5.0), np.arange(n + 1.0), np.arange(n + 1.0)]
     g = np.linspace(-3.0, n + 3.0, m + 1)
     y, z = np.meshgrid(g, g, indexing="ij")
@@ -53,3 +53,25 @@ def test_classification_of_the_largest_projection():
     x = flags.view(n * n, 4)
     assert bool((x[:, 1] == 3).all()) and bool((x[:, 2:] == 0).all()) and bool((x[1:, 0] == 0).all())
     assert int(x[0, 0]) == 8
+
+
+# as many ghost rows: every row is the one of a small slab (the same box, image
+# point and matrix, at coordinates up to 2^13: rounding of 2^-53 * 2^13, times
+# the eight unknowns of a row)
+def test_rows_of_the_largest_projection():
+    import ctypes
+    import paper_2605_04335_amd as P
+    f, bodies, n = slab(12)
+    O = oracle.setup(*f, bodies)
+    assert O.st.ng == n * n and np.ptp(O.st.dlb) < 1e-13 and np.all(O.st.rfl == O.st.rfl[0])
+    f, bodies, n = slab()
+    flags, _ = P.classify(*f, bodies)
+    st = P.build_ghost_stencils(*f, bodies, flags)
+    assert st.info() == (n * n, 0, 0)
+    cell, dlb, rfl = np.zeros(n * n, np.int32), np.zeros(n * n), np.zeros(n * n, np.uint8)
+    rc = P.lib().ibm_stencils_export(st.h, ctypes.c_void_p(cell.ctypes.data), None, None, None,
+                                     ctypes.c_void_p(dlb.ctypes.data), ctypes.c_void_p(rfl.ctypes.data), None)
+    assert rc == 0
+    assert np.array_equal(cell, np.arange(n * n, dtype=np.int32) * 4 + 1)
+    assert np.all(rfl == O.st.rfl[0])
+    assert np.abs(dlb - O.st.dlb[0]).max() < 1e-11
