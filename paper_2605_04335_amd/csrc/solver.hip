@@ -65,6 +65,14 @@ constexpr long long BESIDE_MIN_CELLS = 1 << 23;
 // without, 406 us with; 256^3 with 63 thousand rows: 41.2 and 42.2 ms per
 // solve; 512^3 with 150 thousand: 11.1 and 11.4 ms per iteration.
 constexpr long long FEW_ROWS = 1 << 15;
+// The same on all of level 0 below WALK_MIN_CELLS: up to this many rows, or with
+// closed ghosts and membranes together (five launches otherwise).  Per
+// iteration, rows.hpp against the one-sweep kernels, FP64 and mixed: 10 thousand
+// rows at 64^3 0.97 and 0.97, 28 at 80^3 0.96 and 1.01, 35 at 96^3 0.99 and
+// 1.00, 44 at 112^3 0.99 and 1.01, 52 there 1.00 and 1.03, 59 at 124^3 1.03 and
+// 1.10; membranes alone: 29 at 96^3 0.98 and 0.93, 61 at 124^3 1.02 and 1.02;
+// both kinds, 79 at 124^3, 0.94 and 0.99.
+constexpr long long FLAT_ROWS = 45000;
 
 inline int sparse_blocks(long long n) { return (int)std::max<long long>(1, std::min<long long>(XB, (n + TPB - 1) / TPB)); }
 
@@ -1172,7 +1180,8 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     IBM_HIP(hipStreamSynchronize(s));
     IBM_REQUIRE(herr == 0, IBM_EGEOM, "cut link without ghost");
     plan_walk(c, s);
-    c.flat = c.opts.precond == IBM_PRECOND_MG && c.N < WALK_MIN_CELLS;
+    c.flat = c.opts.precond == IBM_PRECOND_MG && c.N < WALK_MIN_CELLS &&
+             (c.nrows <= FLAT_ROWS || (c.ng && c.nm));
     c.few = c.walk && c.nrows <= FEW_ROWS;
     if (c.few || c.flat) code_rows(c, st, s);
     c.vol_fluid = hs[0];

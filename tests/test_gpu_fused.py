@@ -117,6 +117,33 @@ def test_longest_boxes_match_oracle(shape):
     assert np.linalg.norm(d - d.mean()) < 1e-11 * np.linalg.norm(zo)
 
 
+def test_update_across_the_row_limit_equals_fresh_setup():
+    """A context below the pass's size takes the half-sweeps with their rows or
+    the one-sweep kernels by the count of rows: an update to more rows than the
+    limit, and back, preconditions bit for bit as a fresh context, and as the
+    oracle (the V-cycle's parity bound)."""
+    import torch
+    import paper_2605_04335_amd as P
+    shape = (124, 120, 116)
+    f, small = box_case(*shape, "sphere")
+    L = [m / max(shape) for m in shape]
+    big = [W.sphere((L[0] * (i + 0.5) / 3, L[1] * (j + 0.5) / 3, L[2] * (k + 0.5) / 3), 0.125, freq=6)
+           for i in range(3) for j in range(3) for k in range(3)]
+    _, _, sol, _ = P.setup(*f, small)
+    for bodies in (big, small):
+        flags, st, fresh, _ = P.setup(*f, bodies)
+        assert (sum(st.info()[:2]) > 45000) == (bodies is big)
+        sol.update(flags, st)
+        O = oracle.setup(*f, bodies)
+        b = oracle.assemble_rhs(*f, O.flags, O.st, W.noise_rhs(len(O.flags), 48))
+        x = torch.from_numpy(b).cuda()
+        z = sol.precond(x)
+        assert torch.equal(z, fresh.precond(x))
+        zo = oracle.vcycle(*f, O.flags, O.st, b)
+        d = (z.cpu().numpy() - zo)[zo != 0.0]
+        assert np.linalg.norm(d - d.mean()) < 1e-11 * np.linalg.norm(zo)
+
+
 def test_fused_pass_after_update_equals_fresh_setup():
     """The near units follow the bodies: a context updated to another geometry
     (and back to none) preconditions bit for bit as a fresh one."""

@@ -58,7 +58,7 @@ def case(shape, bodies):
     ((50, 42, 62), "sphere plate", 1, 1),      # an odd coarsest level on bricks
     ((40, 34, 38), "wall", 3, 1),
     ((32, 32, 32), "sphere plate", 2, 2),      # two cell pairs per thread in the tail
-    ((120, 120, 116), "large", 2, 2),          # more closed ghosts than the recomputing half-sweeps take
+    ((124, 120, 116), "many", 2, 2),           # more rows than the recomputing half-sweeps take
     ((128, 128, 128), "sphere plate", 2, 2),   # the pass, few rows
     ((176, 160, 152), "large", 2, 2),          # the pass, many rows
     ((160, 116, 116), "plate", 2, 2),
@@ -150,7 +150,7 @@ def test_inner_smoothing_cell_by_cell(shape, nu1):
     ((128, 128, 132), "sphere plate", 1, 2),
     ((128, 128, 132), "plate", 2, 0),
     ((128, 132, 128), "sphere", 3, 3),
-    ((120, 120, 116), "large", 2, 2),
+    ((124, 120, 116), "many", 2, 2),
 ])
 def test_other_routes_of_level_0(shape, bodies, nu1, nu2):
     import torch
