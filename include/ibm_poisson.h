@@ -406,7 +406,8 @@ int32_t poisson_solve_assembled(poisson_ctx *ctx, const double *b_dev, double *x
  * second smoothing phase of level 0 (prolongation and four half-sweeps in one
  * pass; it takes the half-sweeps' place on large grids); -1 = off.  While
  * a kernel is selected, solves run without graph replay and bracket each of
- * its launches with HIP events on the solve stream.  Returns (and with reset
+ * its launches with HIP events on the solve stream; while it is kernel 0,
+ * level 0 smooths with half-sweep launches on grids of every size.  Returns (and with reset
  * != 0 clears) the accumulated milliseconds and launch count, then selects
  * `kernel` for the following solves. */
 int32_t poisson_kernel_timing(poisson_ctx *ctx, int32_t kernel, int32_t reset, double *total_ms, int64_t *launches);

@@ -648,15 +648,16 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
     typedef typename Store<T>::TB TB;
     const int nl = (int)c.lv.size();
     const poisson_opts &o = c.opts;
+    const bool walk = c.walk && c.prof_kernel != PK_SWEEP0;  // timing the half-sweeps needs their launches
     T *r0 = std::is_same<T, double>::value ? (T *)c.rsp.p : (T *)c.frsp.p;
     if (c.flat)
         rows_out<T>(c, x, b, half_sweeps<T, false>(c, x, b, sink, 2 * o.nu1, true, s), nl > 1 ? r0 : (T *)nullptr, s);
-    else if (!c.walk)
+    else if (!walk)
         for (int it = 0; it < o.nu1; ++it) fine_smooth<T>(c, x, b, sink, it == 0, s);
     if (nl > 1) {
         Level &L1 = c.lv[1];
         int npart;  // partial sums of the next level's mean
-        if (c.walk) {
+        if (walk) {
             npart = walk_down<T>(c, b, w, r0, x, sink, s);  // x is free until the second phase
         } else {
             // level-0 residual: the sparse rows into r0, then the regular rows
@@ -724,7 +725,7 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
             launch_prolong<false>(L, C, o.nu2 > 0, Store<T>::x(C), Store<T>::x(L), s);
             coarse_smooth<Tc, TB>(L, o.nu2, false, c.sc.p + S_MEAN0 + l, s);
         }
-        if (c.walk) {
+        if (walk) {
             walk_up<T>(c, b, x, w, r0, sink, s);
             return;
         }

@@ -225,3 +225,30 @@ def test_coarse_tail_matches_oracle(shape, bodies, nu1, nu2, ncs):
     z = sol.precond(bt)
     assert rel(z.cpu().numpy(), oracle.vcycle(*f, O.flags, O.st, b, nu1, nu2, ncs)) < 1e-11
     assert torch.equal(z, sol.precond(bt))
+
+
+# the kernels that a program times per launch: half-sweeps on every grid, also
+# where passes take their place in untimed solves; the pass only there
+@pytest.mark.parametrize("shape,passes", [((64, 48, 40), False), ((128, 128, 128), True)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_kernel_timing_counts_launches(shape, passes, precision):
+    import torch
+    import paper_2605_04335_amd as P
+    f, bl = box_case(*shape, "sphere plate")
+    flags, st, sol, _ = P.setup(*f, bl, precision=precision, tol=1e-9)
+    rhs = torch.from_numpy(W.noise_rhs(len(flags), 49)).cuda()
+    x, _ = sol.solve(rhs)
+    counts = []
+    for kernel in (P.KERNEL_SWEEP0, P.KERNEL_APPLY0, P.KERNEL_XR, P.KERNEL_WALK_UP):
+        sol.kernel_timing(kernel)
+        y, stats = sol.solve(rhs)
+        ms, n = sol.kernel_timing(-1)
+        counts.append(n)
+        assert (ms > 0.0) == (n > 0)
+        assert float((x - y).norm() / x.norm()) < 1e-6  # a solve to the same tolerance
+    # per iteration two V-cycles of two phases, two steps of two half-sweeps each; what starts from zero is not
+    # timed: the first half-sweep (with its rows), or the first step (one-sweep kernels)
+    per = 12 if passes else 14
+    its = stats.iterations
+    assert counts[1] == counts[2] == its and counts[3] == (2 * its if passes else 0)
+    assert counts[0] % per == 0 and abs(counts[0] // per - its) <= 2
