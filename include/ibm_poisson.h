@@ -110,7 +110,8 @@ typedef struct poisson_opts {
     int32_t coarse_sweeps;  /* red-black sweeps on the coarsest level */
     double inner_tol;       /* mixed: relative tolerance of each inner solve */
     int32_t max_outer;      /* mixed: outer refinement steps */
-    int32_t use_graph;      /* replay each iteration as a captured HIP graph */
+    int32_t use_graph;      /* replay each iteration as a captured HIP graph (where it runs on one
+                               stream: not from 2^23 cells with bodies; requests to the server never) */
     int32_t precond;        /* IBM_PRECOND_MG or IBM_PRECOND_SRJ */
     int32_t srj_sweeps;     /* SRJ: Jacobi sweeps per preconditioner application */
 } poisson_opts;

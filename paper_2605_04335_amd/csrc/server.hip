@@ -229,7 +229,15 @@ void poisson_server::run_request(Request *r)
             build_stencils(&g, bd.data(), (int)bd.size(), flags.p, &st, s);
             std::unique_ptr<ibm_stencils> stg(st);
             size_t bytes = 0;
-            int e = poisson_setup(&g, flags.p, st, &r->opts, &bytes, &ctx);
+            // Iterations are enqueued, whatever the request's use_graph says:
+            // two serving runs ended with a host segmentation fault, one of them
+            // inside a graph launch, and the cause is not known.  The results are
+            // the same, and a burst is no slower (eight requests to 128^3: 67 to
+            // 68 ms with graphs, 62 to 63 without; eight to 48^3 14.7 to 16.0 and
+            // 14.0 to 14.4; one at a time 37.6 and 37.5, 127.1 and 126.6).
+            poisson_opts opts = r->opts;
+            opts.use_graph = 0;
+            int e = poisson_setup(&g, flags.p, st, &opts, &bytes, &ctx);
             if (e) throw Error(e, ibm_last_error());
         }
         if (!r->ctx) setup_ms = now_ms(ts);  // the temporaries' release included

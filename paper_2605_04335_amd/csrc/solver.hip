@@ -246,11 +246,20 @@ struct poisson_ctx {
 
     const Lv &L0() const { return lv[0].lv; }
 
+    // (making and destroying an executable graph allocates and frees: like
+    // every such call, not while another thread captures)
+    void drop_graphs()
+    {
+        for (hipGraphExec_t *g : {&g64, &g32, &g64w}) {
+            if (!*g) continue;
+            std::shared_lock<std::shared_mutex> cl(capture_mutex());
+            (void)hipGraphExecDestroy(*g);
+            *g = nullptr;
+        }
+    }
     ~poisson_ctx()
     {
-        if (g64) (void)hipGraphExecDestroy(g64);
-        if (g32) (void)hipGraphExecDestroy(g32);
-        if (g64w) (void)hipGraphExecDestroy(g64w);
+        drop_graphs();
         if (hsc) pinned_release(hsc);
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
@@ -847,6 +856,7 @@ int bicgstab(poisson_ctx &c, const TR *rhs, TX *y, T *r, T *rh, T *p, T *v, T *p
     const bool forked = c.walk && c.beside && c.near.nb() > 0;
     const bool use_graph = c.opts.use_graph && c.prof_kernel < 0 && !forked;
     if (use_graph && !*graph) {
+        std::unique_lock<std::shared_mutex> lk(capture_mutex());
         // a failure inside the capture still ends it, so the stream never
         // stays in capture mode (the user's stream joins it afterwards)
         struct Capture {
@@ -865,15 +875,12 @@ int bicgstab(poisson_ctx &c, const TR *rhs, TX *y, T *r, T *rh, T *p, T *v, T *p
                 c.capturing = false;
             }
         } cap{c, s};
-        {
-            std::unique_lock<std::shared_mutex> lk(capture_mutex());
-            c.capturing = true;
-            IBM_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            cap.open = true;
-            bicg_iteration<T, TX>(c, y, r, rh, p, v, ph, sh, t, s);
-            cap.open = false;
-            IBM_HIP(hipStreamEndCapture(s, &cap.gr));
-        }
+        c.capturing = true;
+        IBM_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+        cap.open = true;
+        bicg_iteration<T, TX>(c, y, r, rh, p, v, ph, sh, t, s);
+        cap.open = false;
+        IBM_HIP(hipStreamEndCapture(s, &cap.gr));
         IBM_HIP(hipGraphInstantiate(graph, cap.gr, nullptr, nullptr, 0));
     }
     int it = 0;
@@ -1124,9 +1131,7 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     }
     // the captured iterations and the vectors below may change
     IBM_HIP(hipStreamSynchronize(s));
-    if (c.g64) { (void)hipGraphExecDestroy(c.g64); c.g64 = nullptr; }
-    if (c.g32) { (void)hipGraphExecDestroy(c.g32); c.g32 = nullptr; }
-    if (c.g64w) { (void)hipGraphExecDestroy(c.g64w); c.g64w = nullptr; }
+    c.drop_graphs();
     const bool w8 = nx % 8 == 0 && ((uintptr_t)flags & 7) == 0;
     const Walk WF = make_walk(w8 ? Z.Nh / 4 : Z.Nh);
     if (w8) k_setup_flags0<true><<<WF.nb, TPB, 0, s>>>(Z.lv, WF, flags, Z.m.p, c.part.p);
@@ -1920,9 +1925,7 @@ extern "C" int32_t poisson_bind_workspace(poisson_ctx *c, void *ws_dev, size_t b
                                                    std::to_string(need));
         IBM_HIP(hipStreamSynchronize(c->cs));
         // captured iterations hold the old addresses
-        if (c->g64) { (void)hipGraphExecDestroy(c->g64); c->g64 = nullptr; }
-        if (c->g32) { (void)hipGraphExecDestroy(c->g32); c->g32 = nullptr; }
-        if (c->g64w) { (void)hipGraphExecDestroy(c->g64w); c->g64w = nullptr; }
+        c->drop_graphs();
         char *base = (char *)ws_dev;
         size_t off = 0;
         for_scratch(*c, [&](auto &b) {
