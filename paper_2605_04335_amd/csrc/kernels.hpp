@@ -234,64 +234,20 @@ __device__ __forceinline__ bool active0(uint8_t f) { return !(f & F_SOLID) || (f
 // cells so a row needs only its own byte
 enum : uint8_t { CM_ACT = 1, CM_PX = 2, CM_PY = 4, CM_PZ = 8, CM_MX = 16, CM_MY = 32, CM_MZ = 64 };
 
-// Sum over the open faces of coefficient * neighbour value, and the diagonal.
-// xo is the other colour's array (base of that colour).  FINE: the faces of a
-// regular level-0 cell are open inside the domain; coarse: the cell's own
-// open-face bits (fo is not read).
-template <bool FINE, class T>
-__device__ __forceinline__ double nbsum(const Lv &L, const T *xo, const uint8_t *fo, int h, int j, int k, int i,
-                                        uint8_t fm, double &dg)
+// Regular level-0 cell: sum over the faces inside the domain of coefficient *
+// neighbour value (xo: base of the other colour's array), and the diagonal.
+template <class T>
+__device__ __forceinline__ double nbsum(const Lv &L, const T *xo, int h, int j, int k, int i, double &dg)
 {
     const int p = i & 1;  // (c + j + k) & 1
-    const long long row = (long long)L.H * (j + (long long)L.ny * k);
+    const long long row = (long long)L.H * (j + (long long)L.ny * k), pl = (long long)L.H * L.ny;
     double acc = 0.0, d = 0.0;
-    if (FINE) {
-        if (i + 1 < L.nx) { double c = L.cp[0][i]; acc += c * ld(xo, row + h + p); d += c; }
-        if (i > 0) { double c = L.cm[0][i]; acc += c * ld(xo, row + h + p - 1); d += c; }
-        if (j + 1 < L.ny) { double c = L.cp[1][j]; acc += c * ld(xo, row + h + L.H); d += c; }
-        if (j > 0) { double c = L.cm[1][j]; acc += c * ld(xo, row + h - L.H); d += c; }
-        const long long pl = (long long)L.H * L.ny;
-        if (k + 1 < L.nz) { double c = L.cp[2][k]; acc += c * ld(xo, row + h + pl); d += c; }
-        if (k > 0) { double c = L.cm[2][k]; acc += c * ld(xo, row + h - pl); d += c; }
-    } else {
-        const long long pl = (long long)L.H * L.ny;
-        if (fm & CM_PX) { double c = L.cp[0][i]; acc += c * ld(xo, row + h + p); d += c; }
-        if (fm & CM_MX) { double c = L.cm[0][i]; acc += c * ld(xo, row + h + p - 1); d += c; }
-        if (fm & CM_PY) { double c = L.cp[1][j]; acc += c * ld(xo, row + h + L.H); d += c; }
-        if (fm & CM_MY) { double c = L.cm[1][j]; acc += c * ld(xo, row + h - L.H); d += c; }
-        if (fm & CM_PZ) { double c = L.cp[2][k]; acc += c * ld(xo, row + h + pl); d += c; }
-        if (fm & CM_MZ) { double c = L.cm[2][k]; acc += c * ld(xo, row + h - pl); d += c; }
-    }
-    dg = d;
-    return acc;
-}
-
-// nbsum<false> without branches: every neighbour value and coefficient is
-// loaded (a closed face reads the cell's own slot in the other colour) and a
-// closed face's coefficient is replaced by zero, so all six loads are in
-// flight together.  Adding a zero product or a zero coefficient leaves the
-// sums unchanged (the sums are never -0), so the result is nbsum's.  Used
-// where the level is LDS-resident (the coarse tail).
-template <class T>
-__device__ __forceinline__ double nbsum_all(const Lv &L, const T *xo, int h, int j, int k, int i, uint8_t fm,
-                                            double &dg)
-{
-    const int p = i & 1;
-    const int pl = L.H * L.ny, base = h + L.H * j + pl * k;
-    const bool o[6] = {(fm & CM_PX) != 0, (fm & CM_MX) != 0, (fm & CM_PY) != 0,
-                       (fm & CM_MY) != 0, (fm & CM_PZ) != 0, (fm & CM_MZ) != 0};
-    const int dx[6] = {p, p - 1, L.H, -L.H, pl, -pl};
-    const double cv[6] = {L.cp[0][i], L.cm[0][i], L.cp[1][j], L.cm[1][j], L.cp[2][k], L.cm[2][k]};
-    double xv[6];
-#pragma unroll
-    for (int t = 0; t < 6; ++t) xv[t] = ld(xo, base + (o[t] ? dx[t] : 0));
-    double acc = 0.0, d = 0.0;
-#pragma unroll
-    for (int t = 0; t < 6; ++t) {
-        const double c = o[t] ? cv[t] : 0.0;
-        acc += c * xv[t];
-        d += c;
-    }
+    if (i + 1 < L.nx) { double c = L.cp[0][i]; acc += c * ld(xo, row + h + p); d += c; }
+    if (i > 0) { double c = L.cm[0][i]; acc += c * ld(xo, row + h + p - 1); d += c; }
+    if (j + 1 < L.ny) { double c = L.cp[1][j]; acc += c * ld(xo, row + h + L.H); d += c; }
+    if (j > 0) { double c = L.cm[1][j]; acc += c * ld(xo, row + h - L.H); d += c; }
+    if (k + 1 < L.nz) { double c = L.cp[2][k]; acc += c * ld(xo, row + h + pl); d += c; }
+    if (k > 0) { double c = L.cm[2][k]; acc += c * ld(xo, row + h - pl); d += c; }
     dg = d;
     return acc;
 }
@@ -1293,67 +1249,13 @@ __global__ void __launch_bounds__(TPB) k0_sparse_res(Lv L, Sp S, const T *x, con
 }
 
 // ---------------------------------------------------------------- transfers
-// residual of one fine slot, computed on the fly (regular cells) or read
-// from rsp (irregular level-0 rows)
-template <bool FINE, class T, class TB>
-__device__ __forceinline__ bool child_res(const Lv &F, long long pin, const T *x, const TB *b, const double *bsh,
-                                          const T *rsp, int cf, int h, int j, int k, double &r)
-{
-    const long long so = (long long)cf * F.Nh;
-    const long long s = h + (long long)F.H * (j + (long long)F.ny * k);
-    const uint8_t f = F.f[so + s];
-    const int i = 2 * h + ((cf + j + k) & 1);
-    if (FINE) {
-        if ((f & F_SOLID) && !(f & F_GHOST)) return false;
-        if (f & (F_GHOST | F_MGHOST)) { r = ld(rsp, so + s); return true; }
-        double dg;
-        double off = nbsum<true>(F, x + (long long)(1 - cf) * F.Nh, F.f + (long long)(1 - cf) * F.Nh, h, j, k, i, f, dg);
-        double bb = ld(b, so + s);
-        if (so + s == pin && bsh) bb -= bsh[0];
-        r = bb - (off - dg * ld(x, so + s));
-        return true;
-    } else {
-        if (!(f & 1)) return false;
-        double dg;
-        double off = nbsum_all(F, x + (long long)(1 - cf) * F.Nh, h, j, k, i, f, dg);
-        r = ld(b, so + s) - (bsh ? bsh[0] : 0.0) - (off - dg * ld(x, so + s));
-        return true;
-    }
-}
-
-// fused residual + restriction: coarse RHS = the volume integral of the
-// active children's residuals divided by the full coarse-cell volume (the
-// coarse operator is per full volume); partial sums of V_C b_C for the
-// coarse mean
-template <bool FINE, class T, class TB, class TBc>
-__device__ __forceinline__ double restrict_one(const Lv &F, const Lv &C, long long pin, const T *x, const TB *b,
-                                               const double *bsh, const T *rsp, TBc *bc, int cc, int hc, int J,
-                                               int K)
-{
-    const long long sc = slot(C, cc, hc, J, K);
-    const int I = 2 * hc + ((cc + J + K) & 1);
-    if (I >= C.nx) { st(bc, sc, 0.0); return 0.0; }
-    double sv = 0.0, svr = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int dx = q & 1, dy = (q >> 1) & 1, dz = (q >> 2) & 1;
-        const int j = 2 * J + dy, k = 2 * K + dz, i = 2 * I + dx;
-        double r;
-        if (!child_res<FINE>(F, pin, x, b, bsh, rsp, (dx + dy + dz) & 1, I, j, k, r)) continue;
-        const double V = F.w[0][i] * F.w[1][j] * F.w[2][k];
-        sv += V;
-        svr += V * r;
-    }
-    const double VC = C.w[0][I] * C.w[1][J] * C.w[2][K];
-    st(bc, sc, sv > 0.0 ? svr / VC : 0.0);
-    return (C.f[sc] & 1) ? VC * ld(bc, sc) : 0.0;
-}
-
-// restrict_one<false> for a coarse level in global memory, with the loads of
-// all 8 children issued before any is used: the 2x2x2 box, the 3 outer face
+// Residual of a coarse cell's children, volume-weighted and summed, for a level
+// below the finest: coarse RHS = the volume integral of the active children's
+// residuals divided by the full coarse-cell volume (the coarse operator is per
+// full volume); returns V_C b_C for the coarse mean.  The loads of all 8
+// children go out before any is used: the 2x2x2 box, the 3 outer face
 // neighbours of each child (outside the level: the child itself, whose face
-// is closed in the mask), their RHS and masks, and the coefficients.  Same
-// arithmetic in the same order.
+// is closed in the mask), their RHS and masks, and the coefficients.
 template <class T, class TB, class TBc>
 __device__ __forceinline__ double restrict_box(const Lv &F, const Lv &C, const T *x, const TB *b, double mu, TBc *bc,
                                                int cc, int hc, int J, int K)
@@ -1406,7 +1308,7 @@ __device__ __forceinline__ double restrict_box(const Lv &F, const Lv &C, const T
         const int dx = q & 1, dy = (q >> 1) & 1, dz = q >> 2;
         const uint8_t f = fb[q];
         if (!(f & 1)) continue;
-        // face values in the order of nbsum: +x, -x, +y, -y, +z, -z
+        // face values in the order +x, -x, +y, -y, +z, -z
         const double vpx = dx ? (double)xn[q][0] : (double)xb[q ^ 1], vmx = dx ? (double)xb[q ^ 1] : (double)xn[q][0];
         const double vpy = dy ? (double)xn[q][1] : (double)xb[q ^ 2], vmy = dy ? (double)xb[q ^ 2] : (double)xn[q][1];
         const double vpz = dz ? (double)xn[q][2] : (double)xb[q ^ 4], vmz = dz ? (double)xb[q ^ 4] : (double)xn[q][2];
@@ -1429,22 +1331,16 @@ __device__ __forceinline__ double restrict_box(const Lv &F, const Lv &C, const T
 
 // one thread per coarse cell in natural x order (Gc tiles I over C.nx), so a
 // wave reads the children's rows with unit stride
-template <bool FINE, class T, class TB, class TBc>
-__global__ void __launch_bounds__(TPB) k_restrict(Lv F, Lv C, Geo Gc, long long pin, const T *x, const TB *b,
-                                                  const double *bsh, const T *rsp, TBc *bc, double *part)
+template <class T, class TB, class TBc>
+__global__ void __launch_bounds__(TPB) k_restrict(Lv F, Lv C, Geo Gc, const T *x, const TB *b, const double *mean, TBc *bc,
+                                                  double *part)
 {
     Acc<1> a;
     a.v[0] = 0.0;
     int I, J, k0, k1;
     if (geo_tile(Gc, I, J, k0, k1)) {
-        const double mu = FINE ? 0.0 : (bsh ? bsh[0] : 0.0);
-        for (int K = k0; K < k1; ++K) {
-            const int cc = (I + J + K) & 1;
-            if constexpr (FINE)
-                a.v[0] += restrict_one<FINE>(F, C, pin, x, b, bsh, rsp, bc, cc, I >> 1, J, K);
-            else
-                a.v[0] += restrict_box(F, C, x, b, mu, bc, cc, I >> 1, J, K);
-        }
+        const double mu = mean[0];
+        for (int K = k0; K < k1; ++K) a.v[0] += restrict_box(F, C, x, b, mu, bc, (I + J + K) & 1, I >> 1, J, K);
     }
     block_reduce<1>(a, part, 0, blockIdx.x);
 }

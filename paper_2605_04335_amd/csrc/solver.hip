@@ -694,9 +694,8 @@ void vcycle(poisson_ctx &c, const T *b, T *x, T *w, const double *sink, hipStrea
             }
             coarse_smooth<Tc, TB>(L, o.nu1, true, mean, s);
             Level &C = c.lv[l + 1];
-            k_restrict<false, Tc, TB, TB><<<C.geon.nb, TPB, 0, s>>>(L.lv, C.lv, C.geon, -1, Store<T>::x(L),
-                                                                   Store<T>::b(L), mean, (const Tc *)nullptr,
-                                                                   Store<T>::b(C), mean_part(c, l + 1));
+            k_restrict<Tc, TB, TB><<<C.geon.nb, TPB, 0, s>>>(L.lv, C.lv, C.geon, Store<T>::x(L), Store<T>::b(L), mean,
+                                                            Store<T>::b(C), mean_part(c, l + 1));
             IBM_LAUNCH_CHECK();
             npart = C.geon.nb;
         }
@@ -969,8 +968,7 @@ __global__ void k_pinres(Lv L, long long pin, const double *x, double *sc)
     int c, h, j, k, i;
     decode_slot(L, pin, c, h, j, k, i);
     double dg;
-    const double off = nbsum<true>(L, x + (long long)(1 - c) * L.Nh, L.f + (long long)(1 - c) * L.Nh, h, j, k, i,
-                                   L.f[pin], dg);
+    const double off = nbsum(L, x + (long long)(1 - c) * L.Nh, h, j, k, i, dg);
     sc[S_TMP] = off - dg * x[pin];
 }
 
