@@ -155,7 +155,7 @@ def solver_source_digest():
     counters describe only the version they were taken on."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hpp", "fused.hpp", "walk.hpp", "rows.hpp", "setup.hpp", "solver.hip", "common.hpp"):
+    for f in ("kernels.hpp", "division.hpp", "fused.hpp", "walk.hpp", "rows.hpp", "setup.hpp", "solver.hip", "common.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2605_04335_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

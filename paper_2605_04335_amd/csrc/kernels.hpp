@@ -30,6 +30,7 @@
 #include <cstdint>
 
 #include "common.hpp"
+#include "division.hpp"
 
 namespace ibm {
 
@@ -1739,13 +1740,6 @@ __device__ double tail_sum(double v)
     for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += sm[w];
     __syncthreads();
     return s;
-}
-
-// a / d from the rounded reciprocal of d: one correction by the remainder
-__device__ __forceinline__ double quot(double a, double d, double r)
-{
-    const double q = a * r;
-    return __builtin_fma(__builtin_fma(-q, d, a), r, q);
 }
 
 // the thread's cell pairs of a level: place, coefficients (order +x, -x, +y,

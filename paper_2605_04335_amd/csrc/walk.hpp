@@ -54,13 +54,6 @@ struct WalkSeg {
     int h0, j0, k0, k1;
 };
 
-// 1 / d to rounding (d normal and positive)
-__device__ __forceinline__ double recip(double d)
-{
-    double r = __builtin_amdgcn_rcp(d);
-    r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
-    return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
-}
 // wave-uniform load of data that no kernel in flight writes: through the
 // constant address space it becomes a scalar load, which needs no vector
 // register and does not queue behind the vector loads in flight
