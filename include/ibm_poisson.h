@@ -161,13 +161,14 @@ int32_t ibm_classify(const ibm_grid *grid, const ibm_body *bodies, int32_t n_bod
  * ibm_classify_noalloc -- ibm_classify for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, hosts
  * that forbid hipMalloc).  Same arguments, results and synchronisation as
- * ibm_classify, but every device buffer of the call (faces, quantised
- * centres and vertices, toggle and cut-link bitsets, per-ray markers,
- * counters) is carved from one fixed array of IBM_CLASSIFY_NOALLOC_MAX_BYTES
+ * ibm_classify, but every device buffer of the call (quantised centres,
+ * vertices and triangles, toggle and cut-link bitsets, counters) is carved
+ * from one fixed array of IBM_CLASSIFY_NOALLOC_MAX_BYTES
  * in device memory that each GPU the library runs on holds until the process
  * ends; the call makes no hipMalloc, hipFree or other allocating call.
- *   scratch_bytes (host, may be NULL): the scratch this input needs.
- * Needs about N/8 bytes with closed bodies, 3N/8 with membranes, N/2 with
+ *   scratch_bytes (host, may be NULL): the scratch this input is charged with,
+ *   which the limit is checked against: an upper bound on what the call uses.
+ * About N/8 bytes with closed bodies, 3N/8 with membranes, N/2 with
  * both (N cells), plus 48 bytes per vertex and 12 per triangle (a 512^3
  * grid with membranes takes 48 MiB of bitsets; closed bodies alone fit up to
  * about 800^3 cells).  An input that needs more
