@@ -46,6 +46,14 @@ constexpr int XB = 1024;               // cap on blocks of the sparse row kernel
 // takes 19 us against 23 to 29 us of one-sweep launches; at 128^3 the bricks'
 // eightfold recomputation alone is eight times that work, against 34 to 37 us.
 constexpr long long BRICK_MAX_CELLS = 300000;
+// A level that is thin in y or z fills its bricks in part: by their count, except
+// where the level is narrow in x, which leaves the one-sweep tiles of 64 pairs
+// emptier still.  FP64 V-cycle, bricks against one-sweep launches on level 1: 625
+// bricks 330 and 336 us, 729 (65^3, odd) 447 and 523, 784 (220 x 220 x 5) 519 and
+// 482, 1444 (300 x 300 x 3) 670 and 481; 3 x 300 x 300 903 and 2036.  The mixed
+// form's solves cross at 700.
+constexpr long long BRICK_MAX = 750;
+constexpr int BRICK_NARROW = 16;
 
 // Whether level 0 may smooth with the fused passes: the two-step V-cycle of a
 // hierarchy with coarse levels (every dimension even), and enough cells.  At
@@ -1350,8 +1358,9 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
                 L.pm.pt[d] = (const double *)(c->coef.p + L.pt[d]);
             }
         if (l > 0) {
-            L.brick = L.N <= BRICK_MAX_CELLS && o.nu1 <= 2 && o.nu2 >= 1 && o.nu2 <= 2;
-            if (L.brick) L.br = make_brick(L.n[0], L.n[1], L.n[2]);
+            L.br = make_brick(L.n[0], L.n[1], L.n[2]);
+            L.brick = L.N <= BRICK_MAX_CELLS && ((long long)L.br.gx * L.br.gy * L.br.gz <= BRICK_MAX || L.n[0] <= BRICK_NARROW) &&
+                      o.nu1 <= 2 && o.nu2 >= 1 && o.nu2 <= 2;
             if (c->mixed) { L.x32.alloc(2 * L.Nh); L.b16.alloc(2 * L.Nh); if (L.brick) L.k32.alloc(L.Nh); }
             else { L.x64.alloc(2 * L.Nh); L.b64.alloc(2 * L.Nh); if (L.brick) L.k64.alloc(L.Nh); }
         }

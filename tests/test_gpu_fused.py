@@ -98,6 +98,23 @@ def test_fused_pass_matches_oracle(shape, bodies):
     assert torch.equal(z, sol.precond(bt))
 
 
+# thin boxes: a coarse level of more bricks than they pay for (one-sweep
+# kernels), and as many on a level too narrow for those (bricks).  The same.
+@pytest.mark.parametrize("shape", [(440, 440, 10), (300, 6, 312), (600, 6, 600), (6, 600, 600)])
+def test_thin_boxes_match_oracle(shape):
+    import torch
+    import paper_2605_04335_amd as P
+    print("[case] thin", shape, flush=True)
+    f, _ = box_case(*shape, "")
+    O = oracle.setup(*f, [])
+    flags, st, sol, _ = P.setup(*f, [])
+    b = oracle.assemble_rhs(*f, O.flags, O.st, W.noise_rhs(len(O.flags), 50))
+    z = sol.precond(torch.from_numpy(b).cuda()).cpu().numpy()
+    zo = oracle.vcycle(*f, O.flags, O.st, b)
+    d = (z - zo)[zo != 0.0]
+    assert np.linalg.norm(d - d.mean()) < 1e-11 * np.linalg.norm(zo)
+
+
 # a box of more than 2^16 rows, or pairs of cells to a row, beyond the places a
 # pass can hold.  The same bound and comparison; the sink's sum is of the same
 # size as above.
