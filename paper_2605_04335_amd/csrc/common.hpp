@@ -159,6 +159,21 @@ struct Image {
 
 inline unsigned cdiv(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
 
+// Ordered lists of the cells whose flag byte has a given bit, up to three of
+// them in one pass, in two halves: the counts (into device memory, behind the
+// work on the stream), and the lists once the caller has read them and has
+// room (stencils.hip).  The flags stay as they are in between.
+struct CellLists {
+    const uint8_t *flags;
+    long long N;
+    int K, nb;
+    uint8_t m[3];    // single bits
+    DBuf<int> off;   // [K*nb] block counts, then their prefix sums
+    CellLists(const uint8_t *f, long long n, int k, uint8_t m0, uint8_t m1 = 0, uint8_t m2 = 0);
+    void count(int *total_dev, hipStream_t s);  // K totals
+    void fill(int32_t *o0, int32_t *o1, int32_t *o2, hipStream_t s);
+};
+
 // ---------------------------------------------------------------- grid (host)
 struct HostGrid {
     int n[3];

@@ -63,15 +63,24 @@ __global__ void __launch_bounds__(TPB) k_setup_flags0(Lv L, Walk W, const uint8_
     block_reduce<1>(s, part, 0, blockIdx.x);
 }
 
-// ghost rows: slot of each closed ghost cell, unknowns of every stencil column
+// ghost rows: slot of each closed ghost cell, unknowns and weights of every
+// stencil column, the rows' scales (wi, sGi, dlbi: the table's)
 __global__ void __launch_bounds__(TPB) k_setup_rows(SlotMap m, long long ng, long long R,
                                                     const int32_t *__restrict__ cell, const int32_t *__restrict__ col,
-                                                    int32_t *__restrict__ rslot, int32_t *__restrict__ rcol)
+                                                    const double *__restrict__ wi, const double *__restrict__ sGi,
+                                                    const double *__restrict__ dlbi, int32_t *__restrict__ rslot,
+                                                    int32_t *__restrict__ rcol, double *__restrict__ w,
+                                                    double *__restrict__ sG, double *__restrict__ dlb)
 {
     for (long long q = blockIdx.x * (long long)TPB + threadIdx.x; q < 8 * R; q += (long long)gridDim.x * TPB) {
         const int32_t v = col[q];
         rcol[q] = v >= 0 ? (int32_t)col_unknown(m, v) : -1;
-        if ((q & 7) == 0 && (q >> 3) < ng) rslot[q >> 3] = (int32_t)cell_slot(m, cell[q >> 3]);
+        w[q] = wi[q];
+        if (q & 7) continue;
+        const long long r = q >> 3;
+        sG[r] = sGi[r];
+        dlb[r] = dlbi[r];
+        if (r < ng) rslot[r] = (int32_t)cell_slot(m, cell[r]);
     }
 }
 

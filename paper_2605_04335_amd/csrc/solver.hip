@@ -28,10 +28,6 @@
 #include <type_traits>
 
 namespace ibm {
-int64_t compact_cells(const uint8_t *flags, long long N, uint8_t mask, DBuf<int32_t> &out, hipStream_t s);
-void compact_two(const uint8_t *flags, long long N, uint8_t m0, DBuf<int32_t> &o0, int64_t &n0, uint8_t m1,
-                 DBuf<int32_t> &o1, int64_t &n1, hipStream_t s);
-
 namespace {
 
 // The Krylov vector updates run one block per 256 groups of four unknowns up
@@ -193,6 +189,12 @@ void pinned_release(double *p)
 }  // namespace
 }  // namespace ibm
 
+// what a set-up sums and counts on the device
+struct SetupSums {
+    double volume[16], inactive[16];  // fluid volume (level 0), active volumes; inactive cells
+    int units[2], adjacent, err;
+};
+
 struct poisson_ctx {
     poisson_opts opts;
     HostGrid g;
@@ -219,8 +221,7 @@ struct poisson_ctx {
     DBuf<double> d64;
     DBuf<double> r2;           // mixed: right-hand side of the FP64 fallback solve
     DBuf<double> gtmp, mtmp, sc, part;  // ghost and membrane staging; scalars; partials
-    DBuf<double> ssum;          // set-up sums (fluid volume, active volume per level)
-    DBuf<int> serr;             // set-up error flag
+    DBuf<SetupSums> ssum;       // set-up sums, read back once
     DBuf<uint8_t> hact[2];      // set-up: natural-order coarse active/cut bits of two consecutive levels
     // fused level-0 smoothing (walk.hpp) and the units around irregular cells
     bool walk = false, beside = false;
@@ -1021,27 +1022,33 @@ bool walk_wanted(const poisson_ctx &c)
            c.N >= WALK_MIN_CELLS && c.lv[0].H <= 0xffff && c.lv[0].n[1] <= 0xffff;
 }
 
-// Lists of the fused level-0 pass for the current classification: near and
-// listed units, the blocks' plane runs.
-void plan_walk(poisson_ctx &c, hipStream_t s)
+// Lists of the fused level-0 pass for the current classification, in two
+// halves: bits of the near and listed units and their counts; then, with the
+// counts read, the lists and the blocks' plane runs.
+void count_units(poisson_ctx &c, CellLists &U, hipStream_t s)
+{
+    const Level &Z = c.lv[0];
+    const int nux = (Z.H + 3) / 4, nuy = (Z.n[1] + 3) / 4, nuz = (Z.n[2] + 3) / 4;
+    const long long nu = (long long)nux * nuy * nuz;
+    k_unit_cells<<<cdiv(16 * nu, NU_T), NU_T, 0, s>>>(Z.lv, nux, nuy, nu, c.ubits[0].p);
+    k_unit_near<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[0].p, c.ubits[1].p);
+    k_unit_list<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[1].p, c.ubits[0].p);
+    U.count(c.ssum.p->units, s);
+}
+void plan_walk(poisson_ctx &c, CellLists *U, const int n[2], hipStream_t s)
 {
     c.walk = walk_wanted(c);
     if (!c.walk) return;
     const Level &Z = c.lv[0];
-    const int nux = (Z.H + 3) / 4, nuy = (Z.n[1] + 3) / 4, nuz = (Z.n[2] + 3) / 4;
-    const long long nu = (long long)nux * nuy * nuz;
     c.near = Near{};
-    if (c.nrows || c.nm) {
-        for (auto &q : c.ubits) reserve(q, nu);
-        k_unit_cells<<<cdiv(16 * nu, NU_T), NU_T, 0, s>>>(Z.lv, nux, nuy, nu, c.ubits[0].p);
-        k_unit_near<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[0].p, c.ubits[1].p);
-        k_unit_list<<<cdiv(nu, 256), 256, 0, s>>>(nux, nuy, nuz, c.ubits[1].p, c.ubits[0].p);
-        IBM_LAUNCH_CHECK();
-        int64_t n, nr;
-        compact_two(c.ubits[0].p, nu, UB_LIST, c.units, n, UB_NEAR, c.nunits, nr, s);
-        c.near = Near{c.units.p, c.ubits[0].p, (int)n, nux, nuy, nuz};
-        c.nearres = Near{c.nunits.p, c.ubits[0].p, (int)nr, nux, nuy, nuz};
-        c.walk = n <= WALK_MAX_NEAR * nu;
+    if (U) {
+        const int nux = (Z.H + 3) / 4, nuy = (Z.n[1] + 3) / 4, nuz = (Z.n[2] + 3) / 4;
+        reserve(c.units, std::max(n[0], 1));
+        reserve(c.nunits, std::max(n[1], 1));
+        U->fill(c.units.p, c.nunits.p, nullptr, s);
+        c.near = Near{c.units.p, c.ubits[0].p, n[0], nux, nuy, nuz};
+        c.nearres = Near{c.nunits.p, c.ubits[0].p, n[1], nux, nuy, nuz};
+        c.walk = n[0] <= WALK_MAX_NEAR * U->N;
     }
     // planes per block: a block fills a CU and computes eight planes more than
     // it owns; the length that takes the fewest plane steps over the rounds
@@ -1068,8 +1075,9 @@ void plan_walk(poisson_ctx &c, hipStream_t s)
     }
 }
 
-// Coded sparse rows of the fused half-sweeps, from the rows in slot numbering.
-void code_rows(poisson_ctx &c, const ibm_stencils *st, hipStream_t s)
+// Coded sparse rows of the fused half-sweeps, from the rows in slot numbering;
+// A: the adjacent cells, na of them (null without closed ghosts).
+void code_rows(poisson_ctx &c, const ibm_stencils *st, CellLists *A, int na, hipStream_t s)
 {
     const Level &Z = c.lv[0];
     Rows &R = c.rows;
@@ -1081,10 +1089,10 @@ void code_rows(poisson_ctx &c, const ibm_stencils *st, hipStream_t s)
     R.nrows = (int)c.nrows;
     R.nm = (int)c.nm;
     if (!c.nrows) return;
-    if (c.ng) {
-        k_mark_adjacent<<<Z.walk.nb, TPB, 0, s>>>(Z.lv, Z.walk, Z.m.p);
-        IBM_LAUNCH_CHECK();
-        R.na = (int)compact_cells(Z.m.p, c.N2, F_ADJ, c.aslot, s);
+    if (A) {
+        R.na = na;
+        reserve(c.aslot, std::max(na, 1));
+        A->fill(c.aslot.p, nullptr, nullptr, s);
     }
     const CodeMap M{Z.lv, st->cell.p, st->cell.p + c.ng, c.aslot.p, R.ng, R.nm, R.na};
     auto blocks = [](long long n) { return (int)std::min<long long>(std::max<long long>((n + TPB - 1) / TPB, 1), 4096); };
@@ -1142,7 +1150,7 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     const Walk WF = make_walk(w8 ? Z.Nh / 4 : Z.Nh);
     if (w8) k_setup_flags0<true><<<WF.nb, TPB, 0, s>>>(Z.lv, WF, flags, Z.m.p, c.part.p);
     else k_setup_flags0<false><<<WF.nb, TPB, 0, s>>>(Z.lv, WF, flags, Z.m.p, c.part.p);
-    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, WF.nb, FIN_SUM, 0, 0.0, c.ssum.p);  // fluid volume
+    k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, WF.nb, FIN_SUM, 0, 0.0, c.ssum.p->volume);  // fluid volume
     // ghost and membrane rows
     const long long R1 = std::max<long long>(R, 1), M1 = std::max<long long>(nm, 1);
     reserve(c.rslot, std::max<long long>(c.ng, 1));
@@ -1159,15 +1167,13 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
     reserve(c.mcolor, M1);
     auto blocks = [](long long n) { return (int)std::min<long long>(std::max<long long>((n + TPB - 1) / TPB, 1), 4096); };
     if (R) {
-        k_setup_rows<<<blocks(8 * R), TPB, 0, s>>>(sm, c.ng, R, st->cell.p, st->col.p, c.rslot.p, c.rcol.p);
-        IBM_HIP(hipMemcpyAsync(c.rw.p, st->w.p, R * 64, hipMemcpyDeviceToDevice, s));
-        IBM_HIP(hipMemcpyAsync(c.rsG.p, st->sG.p, R * 8, hipMemcpyDeviceToDevice, s));
-        IBM_HIP(hipMemcpyAsync(c.rdlb.p, st->dlb.p, R * 8, hipMemcpyDeviceToDevice, s));
+        k_setup_rows<<<blocks(8 * R), TPB, 0, s>>>(sm, c.ng, R, st->cell.p, st->col.p, st->w.p, st->sG.p, st->dlb.p,
+                                                  c.rslot.p, c.rcol.p, c.rw.p, c.rsG.p, c.rdlb.p);
     }
-    IBM_HIP(hipMemsetAsync(c.serr.p, 0, sizeof(int), s));
+    if (nm) IBM_HIP(hipMemsetAsync(&c.ssum.p->err, 0, sizeof(int), s));
     if (nm)
         k_setup_membrane<<<blocks(nm), TPB, 0, s>>>(sm, nz, nm, st->cell.p + c.ng, flags, c.mslot.p, c.mcol.p,
-                                                    c.mcolor.p, c.serr.p);
+                                                    c.mcolor.p, &c.ssum.p->err);
     if (R && nm)
         k_map_mrows<<<blocks(8 * R), TPB, 0, s>>>(8 * R, st->col.p, N, flags, st->cell.p + c.ng, nm, c.rmrow.p);
     // the slots those rows read (the first half-sweep of a V-cycle zeroes
@@ -1181,25 +1187,37 @@ void setup_geometry(poisson_ctx &c, const uint8_t *flags, const ibm_stencils *st
         uint8_t *ha = c.hact[(l + 1) & 1].p;
         k_coarse_active<<<blocks(C.N), TPB, 0, s>>>(F.n[0], F.n[1], C.n[0], C.n[1], C.N, fine, l == 1, ha);
         k_coarse_mask<<<C.walk.nb, TPB, 0, s>>>(C.lv, C.walk, ha, C.m.p, c.part.p, PSTRIDE);
-        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, C.walk.nb, FIN_SUM, l, 0.0, c.ssum.p);
-        k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, C.walk.nb, FIN_SUM, 16 + l, 0.0, c.ssum.p);
+        k_fin<<<1, 1024, 0, s>>>(c.part.p, PSTRIDE, C.walk.nb, FIN_SUM, l, 0.0, c.ssum.p->volume);
+        k_fin<<<1, 1024, 0, s>>>(c.part.p + PSTRIDE, PSTRIDE, C.walk.nb, FIN_SUM, l, 0.0, c.ssum.p->inactive);
     }
     IBM_LAUNCH_CHECK();
-    double hs[32];
-    int herr = 0;
-    IBM_HIP(hipMemcpyAsync(hs, c.ssum.p, 32 * sizeof(double), hipMemcpyDeviceToHost, s));
-    IBM_HIP(hipMemcpyAsync(&herr, c.serr.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    IBM_HIP(hipStreamSynchronize(s));
-    IBM_REQUIRE(herr == 0, IBM_EGEOM, "cut link without ghost");
-    plan_walk(c, s);
+    // lists that smoothing takes: their counts come back with the sums, in one wait
     c.flat = c.opts.precond == IBM_PRECOND_MG && c.N < WALK_MIN_CELLS &&
              (c.nrows <= FLAT_ROWS || (c.ng && c.nm));
+    std::unique_ptr<CellLists> adjacent, units;
+    if (R && walk_wanted(c)) {
+        const long long nu = (long long)((Z.H + 3) / 4) * ((ny + 3) / 4) * ((nz + 3) / 4);
+        for (auto &q : c.ubits) reserve(q, nu);
+        units.reset(new CellLists(c.ubits[0].p, nu, 2, UB_LIST, UB_NEAR));
+        count_units(c, *units, s);
+    }
+    if (c.ng && (c.flat || (walk_wanted(c) && c.nrows <= FEW_ROWS))) {
+        k_mark_adjacent<<<Z.walk.nb, TPB, 0, s>>>(Z.lv, Z.walk, Z.m.p);
+        IBM_LAUNCH_CHECK();
+        adjacent.reset(new CellLists(Z.m.p, c.N2, 1, F_ADJ));
+        adjacent->count(&c.ssum.p->adjacent, s);
+    }
+    SetupSums hs;
+    IBM_HIP(hipMemcpyAsync(&hs, c.ssum.p, sizeof hs, hipMemcpyDeviceToHost, s));
+    IBM_HIP(hipStreamSynchronize(s));
+    IBM_REQUIRE(!nm || hs.err == 0, IBM_EGEOM, "cut link without ghost");
+    plan_walk(c, units.get(), hs.units, s);
     c.few = c.walk && c.nrows <= FEW_ROWS;
-    if (c.few || c.flat) code_rows(c, st, s);
-    c.vol_fluid = hs[0];
+    if (c.few || c.flat) code_rows(c, st, adjacent.get(), hs.adjacent, s);
+    c.vol_fluid = hs.volume[0];
     for (int l = 1; l < nl; ++l) {
-        c.lv[l].volA = hs[l];
-        c.lv[l].n_inactive = (long long)hs[16 + l];
+        c.lv[l].volA = hs.volume[l];
+        c.lv[l].n_inactive = (long long)hs.inactive[l];
     }
     Sp &S = c.sp;
     S.N2 = c.N2;
@@ -1374,8 +1392,7 @@ poisson_ctx *setup(const ibm_grid *grid, const uint8_t *flags, const ibm_stencil
     c->Wc = make_walk(c->N2);
     c->sc.alloc(S_COUNT);
     c->part.alloc((size_t)PSTRIDE * 4);
-    c->ssum.alloc(32);
-    c->serr.alloc(1);
+    c->ssum.alloc(1);
     if (nl > 1) {
         c->hact[0].alloc(c->lv[1].N);
         if (nl > 2) c->hact[1].alloc(c->lv[2].N);

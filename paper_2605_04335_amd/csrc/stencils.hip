@@ -631,54 +631,21 @@ __global__ void __launch_bounds__(1024) k_count_fallback(const uint8_t *rfl, int
 
 }  // namespace
 
-namespace {
-// Ordered lists of the cells that carry each of K flag bits, in two halves:
-// the counts, and the lists once the caller has room for them.
-struct Compaction {
-    const uint8_t *flags;
-    long long N;
-    int K, nb;
-    Bits M;
-    DBuf<int> off;  // [K*nb], then the K totals
-    Compaction(const uint8_t *f, long long n, Bits m, int k) : flags(f), N(n), K(k), nb((int)cdiv(n, CH)), M(m) {}
-    void count(int *total, hipStream_t s)
-    {
-        off.alloc((size_t)K * nb + K);
-        int *tot = off.p + (size_t)K * nb;
-        k_count<<<nb, CB, 0, s>>>(flags, N, M, K, nb, off.p);
-        k_scan<<<K, 1024, 0, s>>>(off.p, nb, tot);
-        IBM_LAUNCH_CHECK();
-        IBM_HIP(hipMemcpyAsync(total, tot, K * sizeof(int), hipMemcpyDeviceToHost, s));
-        IBM_HIP(hipStreamSynchronize(s));
-    }
-    void fill(Lists O, hipStream_t s)
-    {
-        k_fill<<<nb, CB, 0, s>>>(flags, N, M, K, nb, off.p, O);
-        IBM_LAUNCH_CHECK();
-    }
-};
-}  // namespace
-
-// Ordered lists of the cells that carry flag bits m0 and m1, and their counts.
-void compact_two(const uint8_t *flags, long long N, uint8_t m0, DBuf<int32_t> &o0, int64_t &n0, uint8_t m1,
-                 DBuf<int32_t> &o1, int64_t &n1, hipStream_t s)
+CellLists::CellLists(const uint8_t *f, long long n, int k, uint8_t m0, uint8_t m1, uint8_t m2)
+    : flags(f), N(n), K(k), nb((int)cdiv(n, CH)), m{m0, m1, m2}
 {
-    Compaction C(flags, N, Bits{{m0, m1, 0}}, m1 ? 2 : 1);
-    int total[2] = {0, 0};
-    C.count(total, s);
-    n0 = total[0];
-    n1 = total[1];
-    o0.alloc(std::max(total[0], 1));
-    if (m1) o1.alloc(std::max(total[1], 1));
-    C.fill(Lists{{o0.p, o1.p, nullptr}}, s);
-    IBM_HIP(hipStreamSynchronize(s));
 }
-int64_t compact_cells(const uint8_t *flags, long long N, uint8_t mask, DBuf<int32_t> &out, hipStream_t s)
+void CellLists::count(int *total_dev, hipStream_t s)
 {
-    DBuf<int32_t> none;
-    int64_t n, z;
-    compact_two(flags, N, mask, out, n, 0, none, z, s);
-    return n;
+    off.alloc((size_t)K * nb);
+    k_count<<<nb, CB, 0, s>>>(flags, N, Bits{{m[0], m[1], m[2]}}, K, nb, off.p);
+    k_scan<<<K, 1024, 0, s>>>(off.p, nb, total_dev);
+    IBM_LAUNCH_CHECK();
+}
+void CellLists::fill(int32_t *o0, int32_t *o1, int32_t *o2, hipStream_t s)
+{
+    k_fill<<<nb, CB, 0, s>>>(flags, N, Bits{{m[0], m[1], m[2]}}, K, nb, off.p, Lists{{o0, o1, o2}});
+    IBM_LAUNCH_CHECK();
 }
 
 void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, const uint8_t *flags, ibm_stencils **out,
@@ -695,9 +662,12 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
         S->N = N;
         S->bc = bc;
         // closed ghosts, membrane ghosts and the pin (kept with the table for the solver)
-        Compaction C(flags, N, Bits{{F_GHOST, F_MGHOST, F_PIN}}, 3);
+        CellLists C(flags, N, 3, F_GHOST, F_MGHOST, F_PIN);
+        DBuf<int> res(5);  // the pin, fallback rows; counts of the lists
         int tot[3];
-        C.count(tot, s);
+        C.count(res.p + 2, s);
+        IBM_HIP(hipMemcpyAsync(tot, res.p + 2, sizeof tot, hipMemcpyDeviceToHost, s));
+        IBM_HIP(hipStreamSynchronize(s));
         S->ng = tot[0];
         S->nm = tot[1];
         // stencil columns are int32: grid unknowns, then membrane ghost unknowns
@@ -711,8 +681,7 @@ void build_stencils(const ibm_grid *grid, const ibm_body *bodies, int n_body, co
         S->dlb.alloc(std::max<int64_t>(rows, 1));
         S->rfl.alloc(std::max<int64_t>(rows, 1));
         S->geo.alloc(std::max<int64_t>(rows, 1) * 12);
-        DBuf<int> res(2);  // pin, fallback rows
-        C.fill(Lists{{S->cell.p, S->cell.p + S->ng, res.p}}, s);
+        C.fill(S->cell.p, S->cell.p + S->ng, res.p, s);
         Image I;  // (its copy has ended when the results are read)
         DBuf<char> up;
         DBuf<double> box;
