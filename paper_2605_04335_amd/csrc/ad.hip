@@ -665,7 +665,8 @@ AdTiles ad_tiles(const AdGrid &G, int width = 64)
 }
 
 // Plane runs of a block of k_ad_pair: the length that takes the fewest plane
-// steps over the rounds of 512 resident blocks.
+// steps (two more than the planes, four to a turn) over the rounds of 512
+// resident blocks.
 void ad_pair_plan(const AdGrid &G, AdPair &T)
 {
     T.gx = (G.nx + PX - 1) / PX;
@@ -673,7 +674,7 @@ void ad_pair_plan(const AdGrid &G, AdPair &T)
     long long best = -1;
     for (int kz = 4; kz <= PZ; kz += 4) {
         const int gz = (G.nz + kz - 1) / kz;
-        const long long cost = ((long long)T.gx * T.gy * gz + 511) / 512 * (kz + 4);
+        const long long cost = ((long long)T.gx * T.gy * gz + 511) / 512 * ((std::min(kz, G.nz) + 2 + 3) / 4 * 4);
         if (best < 0 || cost < best) {
             best = cost;
             T.kz = kz;
