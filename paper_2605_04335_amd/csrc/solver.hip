@@ -56,9 +56,22 @@ constexpr int BRICK_NARROW = 16;
 // 128^3 with a membrane the two forms are equal (447 and 449 us per FP64
 // V-cycle); below, a pass leaves part of the chip idle.
 constexpr long long WALK_MIN_CELLS = 1 << 21;
-// Largest share of the units in the near list: the listed units cost about 1.3
-// times their share of the one-sweep launches, the pass 0.4 of them all.
-constexpr double WALK_MAX_NEAR = 0.4;
+// Largest share of the units in the near list: where the pass (a of the one-sweep
+// launches' time when both fill their tiles, over the share of its own tiles that
+// is filled) and the listed units (b times their share of it) take as long as
+// the launches (over the share of theirs).  FP64 a = 0.64, b = 1.2; mixed 0.8 and
+// 1.1: the FP32 pass moves half the bytes in nearly the same time.  Iterations
+// of whole solves by listed share, the pass over one-sweep launches: 256^3 FP64
+// 0.87 (0.17), 0.97 (0.28), 1.07 (0.50), mixed 0.99 (0.13), 1.03 (0.21), 1.10
+// (0.28); 208^3 FP64 0.97 (0.23), 1.04 (0.35), mixed 0.85 (0.03), 1.04 (0.23); 160^3,
+// which fills 0.63 of the launches' tiles, FP64 0.87 (0.45), mixed 0.95 (0.51); 128^3
+// FP64 0.96 (0.22), 1.02 (0.50), mixed 0.98 (0.06), 1.05 (0.21).
+double walk_max_near(int H, int ny, bool mixed)
+{
+    auto fill = [&](int h, int j) { return (double)H * ny / ((double)cdiv(H, h) * h * cdiv(ny, j) * j); };
+    const double a = mixed ? 0.8 : 0.64, b = mixed ? 1.1 : 1.2;
+    return std::max(0.05, (1.0 / fill(64, 4) - a / fill(WK_OH, WK_OJ)) / b);  // (64 x 4: make_geo's tiles)
+}
 // From here on the near sequence runs beside the pass on a stream of its own;
 // the fork and join cost 10 us.  160^3 mixed: one after the other 22.3 ms per
 // step, beside 25.9; 256^3 FP64 42.0 and 40.5 ms per solve, 512^3 mixed 288 and 264.
@@ -1048,7 +1061,7 @@ void plan_walk(poisson_ctx &c, CellLists *U, const int n[2], hipStream_t s)
         U->fill(c.units.p, c.nunits.p, nullptr, s);
         c.near = Near{c.units.p, c.ubits[0].p, n[0], nux, nuy, nuz};
         c.nearres = Near{c.nunits.p, c.ubits[0].p, n[1], nux, nuy, nuz};
-        c.walk = n[0] <= WALK_MAX_NEAR * U->N;
+        c.walk = n[0] <= walk_max_near(Z.H, Z.n[1], c.mixed) * U->N;
     }
     // planes per block: a block fills a CU and computes eight planes more than
     // it owns; the length that takes the fewest plane steps over the rounds

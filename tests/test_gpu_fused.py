@@ -251,7 +251,7 @@ def test_coarse_tail_matches_oracle(shape, bodies, nu1, nu2, ncs):
 def test_kernel_timing_counts_launches(shape, passes, precision):
     import torch
     import paper_2605_04335_amd as P
-    f, bl = box_case(*shape, "sphere plate")
+    f, bl = box_case(*shape, "plate")
     flags, st, sol, _ = P.setup(*f, bl, precision=precision, tol=1e-9)
     rhs = torch.from_numpy(W.noise_rhs(len(flags), 49)).cuda()
     x, _ = sol.solve(rhs)

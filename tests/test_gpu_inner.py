@@ -32,7 +32,7 @@ def case(shape, bodies):
     if "large" in bodies:
         L = [m / max(shape) for m in shape]
         bl = [W.sphere([0.5 * e for e in L], 0.4 * min(L), freq=12)]
-    if "many" in bodies:  # more than two fifths of the units near a body
+    if "many" in bodies:  # nearly every unit near a body
         L = [m / max(shape) for m in shape]
         bl = [W.sphere((L[0] * (i + 0.5) / 4, L[1] * (j + 0.5) / 4, L[2] * (k + 0.5) / 4), 0.08 * min(L), freq=3)
               for i in range(4) for j in range(4) for k in range(4)]
@@ -59,7 +59,8 @@ def case(shape, bodies):
     ((40, 34, 38), "wall", 3, 1),
     ((32, 32, 32), "sphere plate", 2, 2),      # two cell pairs per thread in the tail
     ((124, 120, 116), "many", 2, 2),           # more rows than the recomputing half-sweeps take
-    ((128, 128, 128), "sphere plate", 2, 2),   # the pass, few rows
+    ((128, 128, 128), "sphere plate", 2, 2),   # a fifth of the units near a body: one-sweep kernels
+    ((96, 152, 148), "sphere", 2, 2),          # the pass, few rows
     ((176, 160, 152), "large", 2, 2),          # the pass, many rows
     ((160, 116, 116), "plate", 2, 2),
     ((32, 264, 260), "", 2, 2),                # narrower than a tile, cut tiles
