@@ -95,7 +95,7 @@ def time_solves(sol, f, reps):
     return (time.perf_counter() - t0) / reps * 1e3, x, st
 
 
-def sweep_roofline(P, sol, f, T, N, traffic):
+def sweep_roofline(P, sol, f, T, N, key):
     """Roofline of level 0's smoothing kernel: its launches in one solve timed
     with HIP events on the solve stream.  On large grids that is the fused
     second phase (k_walk_up: prolongation and four half-sweeps in one pass):
@@ -104,15 +104,17 @@ def sweep_roofline(P, sol, f, T, N, traffic):
     N bytes.  Otherwise the red/black half-sweep (k_half with its rows below
     2^21 cells, k0_sweep above): the other colour's values, this colour's RHS
     and flag byte and its new values, over N/2 cells each: (1.5 T + 0.5) N."""
+    prec = "f64" if T == 8 else "f32"
     name, bytes_launch = "k_walk_up", 2.625 * T * N
     sol.kernel_timing(P.KERNEL_WALK_UP)
     sol.solve(f)
     tot, cnt = sol.kernel_timing(P.KERNEL_SWEEP0)
     if cnt:
         sol.kernel_timing(-1)
-        traffic = None  # counters are kept for the half-sweep
+        traffic = measured_traffic(key, prec, name)
     else:
         name, bytes_launch = "k_half" if N < 1 << 21 else "k0_sweep", (1.5 * T + 0.5) * N
+        traffic = measured_traffic(key, prec)
         sol.solve(f)
         tot, cnt = sol.kernel_timing(-1)
     if not cnt:
@@ -150,6 +152,15 @@ def sweep_source_digest():
     return hashlib.sha256((src[a:b] + src[c:d]).encode()).hexdigest()[:16]
 
 
+def walk_source_digest():
+    """The same for the fused passes: their file and the division they share."""
+    import hashlib
+    h = hashlib.sha256()
+    for f in ("walk.hpp", "division.hpp"):
+        h.update(open(os.path.join(ROOT, "paper_2605_04335_amd", "csrc", f), "rb").read())
+    return h.hexdigest()[:16]
+
+
 def solver_source_digest():
     """Digest of every kernel and host source of the solve: whole-solve HBM
     counters describe only the version they were taken on."""
@@ -181,12 +192,12 @@ def measured_solve_traffic(workload_key, prec="f64"):
         return None
 
 
-def measured_traffic(workload_key, prec="f64"):
-    """HBM bytes per launch of k0_sweep in one precision ("f64" or "f32")
-    from the committed rocprofv3 counter summary (FETCH_SIZE + WRITE_SIZE,
-    scaled by a plain copy), or None when the summary is missing or was taken
-    on a different kernel source."""
-    path = os.path.join(ROOT, "profiles", "k0_sweep_%s_%s_traffic.md" % (prec, workload_key))
+def measured_traffic(workload_key, prec="f64", kernel="k0_sweep"):
+    """HBM bytes per launch of k0_sweep or k_walk_up in one precision ("f64"
+    or "f32") from the committed rocprofv3 counter summary (FETCH_SIZE +
+    WRITE_SIZE, scaled by a plain copy), or None when the summary is missing
+    or was taken on a different kernel source."""
+    path = os.path.join(ROOT, "profiles", "%s_%s_%s_traffic.md" % (kernel, prec, workload_key))
     if not os.path.exists(path):
         return None
     vals = {}
@@ -194,7 +205,7 @@ def measured_traffic(workload_key, prec="f64"):
         if ":" in line and line.strip().startswith("- "):
             k, v = line.strip()[2:].split(":", 1)
             vals[k.strip()] = v.strip().strip("`")
-    if vals.get("source_digest") != sweep_source_digest():
+    if vals.get("source_digest") != (sweep_source_digest() if kernel == "k0_sweep" else walk_source_digest()):
         return None
     try:
         return float(vals["traffic_bytes_per_launch"])
@@ -509,7 +520,7 @@ def main():
         for _ in range(args.warmup):
             solm.solve(f)
         msm, xm, sm = time_solves(solm, f, args.steps)
-        roofm = sweep_roofline(P, solm, f, 4, N, measured_traffic(key, "f32"))
+        roofm = sweep_roofline(P, solm, f, 4, N, key)
         if args.copy_calibration:
             P.hbm_stream(P.STREAM_COPY, 1 << 30, 3)
         print(json.dumps({"mixed": {"ms_per_solve": round(msm, 3), "iterations": sm.iterations,
@@ -536,7 +547,7 @@ def main():
     ms_per_step = wall / args.steps * 1e3
     value = N / (ms_per_step / 1e3) / 1e6
     err64 = sampled_error(x, G) if G is not None else None
-    roof = sweep_roofline(P, sol, f, 8, N, measured_traffic(key, "f64"))
+    roof = sweep_roofline(P, sol, f, 8, N, key)
     out = {"metric": METRIC, "value": round(value, 2), "unit": "Mpts/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": round(ms_per_step, 3), "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": "f64", "data": "synthetic",
@@ -572,7 +583,7 @@ def main():
         reps = max(2, min(5, args.steps))
         msm, xm, sm = time_solves(solm, f, reps)
         errm = sampled_error(xm, G) if G is not None else None
-        roofm = sweep_roofline(P, solm, f, 4, N, measured_traffic(key, "f32"))
+        roofm = sweep_roofline(P, solm, f, 4, N, key)
         ts = measured_solve_traffic(key, "mixed")
         out["mixed"] = {"ms_per_solve": round(msm, 3), "Mpts_s": round(N / msm * 1e3 / 1e6, 2),
                         "dtype": "f64+f32+bf16", "tol": p.tol, "iterations": sm.iterations,

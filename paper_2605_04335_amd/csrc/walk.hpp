@@ -9,6 +9,17 @@
 // Tiles overlap by the pipeline's dependency depth (2 half-indices, 4 rows, 4
 // planes) and recompute the overlap.
 //
+// Bound: the chain of LDS reads and barriers at one block per CU, and in FP64
+// also bytes.  At 512^3, with nothing beside it, the first phase takes 0.79 ms
+// and the second 0.80 (2.0 and 1.9 with one launch per half-sweep); per cell 69
+// and 79 vector instructions (the vector units issue in 0.39 and 0.45 of the
+// busy cycles), 2.06 and 3.58 GB from and to memory (1.18 and 1.27 of what they
+// cannot do without), 2.6 and 4.5 TB/s.  FP32 0.72 and 0.83 ms: 94 and 107
+// instructions (conversions), 0.61 and 0.58 of the cycles, 1.00 and 1.69 GB.
+// In a solve with bodies the near cells' launches (below) run beside the passes
+// from 2^23 cells on and take registers and bandwidth: 0.93 and 0.89 ms in FP64,
+// 0.73 and 0.77 in FP32.
+//
 // The pass covers the whole level and treats every cell as a regular one.  Its
 // results are wrong near cells with a row of their own (solid, ghost,
 // membrane); a list of small units around those runs the one-sweep sequence
@@ -155,13 +166,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Right-hand sides wait in LDS, in the vectors' type, for their second use.  In
-// FP32 they wait as they were read and the pin's sink is subtracted again (the
-// difference is not an FP32 number); in FP64 less the sink, since to hold both
-// takes registers that the plane loop does not have (64 bytes spilled).
-template <class T>
-constexpr bool lag_raw = !std::is_same<T, double>::value;
-
 // neighbour sum of a cell with index q: centre, outer x and y neighbours from
 // the LDS plane at l, z neighbours zp and zm
 #define WALK_NB(q, l, xc, zp, zm, cp_, cm_)                                                                       \
@@ -179,7 +183,9 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
                                                     T *__restrict__ xk, TBc *__restrict__ bc, double *part)
 {
     __shared__ T lds[2 * 4 * WK_PS];
-    __shared__ T lagb[4][WK_T];       // right-hand sides kept for their second use two planes on
+    // right-hand sides kept for their second use two planes on (in FP64 whatever T:
+    // the pin's less the sink is not a T)
+    __shared__ double lagb[4][WK_T];
     __shared__ double lagr[2][WK_T];  // b + dg x of the red cells, for the residual two planes on
     __shared__ double e0[WK_T], ex[WK_T + WK_H];  // per column: the residual of a coarse cell's lower plane; of both
     __shared__ double ms[WK_T];         // per column: its share of the coarse mean
@@ -216,13 +222,12 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
     const bool odd_row = w.jc() & 1;
     const bool lead = w.own && !odd_row;  // the even row of a pair writes the coarse cell
     __syncthreads();
-    constexpr bool RAW = lag_raw<T>;
     T bR[3], bB[3];
     double czp[6], czm[6], R1[3] = {}, B1[3] = {}, R2[3] = {}, B2[3] = {}, rdR[3] = {}, rdB[3] = {};
 #pragma unroll
     for (int q = 0; q < 6; ++q) czp[q] = czm[q] = 1.0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) lagb[q][tid] = (T)0;
+    for (int q = 0; q < 4; ++q) lagb[q][tid] = 0.0;
     lagr[0][tid] = lagr[1][tid] = ms[tid] = 0.0;
     bB[2] = (T)0;
     const int ks = S.k0 - 4, ke = S.k1 + 4;  // steps load-plane ks .. ke-1
@@ -253,8 +258,7 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
             T *const lw = lds + q * 4 * WK_PS + WK_PAD + w.p;
             const T *const lr = lds + (1 - q) * 4 * WK_PS + WK_PAD + w.p;
             // loads of later steps
-            const T r0 = bR[s % 3], r1 = bB[(s + 2) % 3];  // red of plane k, black of plane k-1
-            double b0 = r0, b1 = r1;
+            double b0 = bR[s % 3], b1 = bB[(s + 2) % 3];  // red of plane k, black of plane k-1
             bR[(s + 2) % 3] = ldu(bp[0] + pl * cz(k + 2), w.col);
             bB[(s + 1) % 3] = ldu(bp[1] + pl * cz(k + 1), w.col);
             czp[(s + 1) % 6] = uld(F.cp[2], cz(k + 1));
@@ -282,9 +286,8 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
                 const int m = (s + 4) % 6;
                 const double dg = w.dxy[q] + czp[m] + czm[m];
                 const double nb = WALK_NB(q, lr + WK_PS, B1[(s + 1) % 3], B1[(s + 2) % 3], B1[s % 3], czp[m], czm[m]);
-                double b2 = lagb[q][tid];
-                lagb[q][tid] = RAW ? r0 : (T)b0;
-                if (RAW && pn.k >= 0 && pn.c == 0 && cz(k - 2) == pn.k && w.col == pn.col) b2 -= pn.sink;
+                const double b2 = lagb[q][tid];
+                lagb[q][tid] = b0;
                 const double v = (double)(T)quot(nb - b2, dg, rdR[(s + 1) % 3]);
                 R2[(s + 1) % 3] = v;
                 rk = b2 + dg * v;
@@ -293,9 +296,8 @@ __global__ void __launch_bounds__(WK_T) k_walk_down(Lv F, Lv C, WalkGeo G, Near 
                 const int m = (s + 3) % 6;
                 const double dg = w.dxy[q] + czp[m] + czm[m];
                 const double nb = WALK_NB(q, lr + 2 * WK_PS, R2[s % 3], R2[(s + 1) % 3], R2[(s + 2) % 3], czp[m], czm[m]);
-                double b3 = lagb[2 + q][tid];
-                lagb[2 + q][tid] = RAW ? r1 : (T)b1;
-                if (RAW && pn.k >= 0 && pn.c == 1 && cz(k - 3) == pn.k && w.col == pn.col) b3 -= pn.sink;
+                const double b3 = lagb[2 + q][tid];
+                lagb[2 + q][tid] = b1;
                 const T v = (T)quot(nb - b3, dg, rdB[s % 3]);
                 B2[s % 3] = (double)v;
                 lw[3 * WK_PS] = v;
@@ -342,7 +344,7 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
                                                   const T *__restrict__ xc, T *__restrict__ x)
 {
     __shared__ T lds[2 * 4 * WK_PS];
-    __shared__ T lagb[4][WK_T];              // right-hand sides kept for their second use two planes on
+    __shared__ double lagb[4][WK_T];         // right-hand sides kept for their second use two planes on
     __shared__ T cl[3][WK_CH * WK_CJ];       // coarse planes by their number modulo 3
     __shared__ double txl[2 * WK_H], tyl[WK_J];
     WalkSeg S;
@@ -396,7 +398,6 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
     }
     T cnext = cload(K0 + 2);
     double tz = upper(ks);
-    constexpr bool RAW = lag_raw<T>;
     T KB[3], bR[3], bB[3];
     double czp[6], czm[6], B0[3] = {}, R1[3] = {}, B1[3] = {}, R2[3] = {}, rdR[3] = {}, rdB[3] = {};
 #pragma unroll
@@ -404,7 +405,7 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
 #pragma unroll
     for (int q = 0; q < 3; ++q) bR[q] = bB[q] = (T)0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) lagb[q][tid] = (T)0;
+    for (int q = 0; q < 4; ++q) lagb[q][tid] = 0.0;
     KB[0] = ldu(xk + pl * cz(ks), w.col);
     KB[1] = ldu(xk + pl * cz(ks + 1), w.col);
     KB[2] = (T)0;
@@ -421,8 +422,7 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
             T *const lw = lds + q * 4 * WK_PS + WK_PAD + w.p;
             const T *const lr = lds + (1 - q) * 4 * WK_PS + WK_PAD + w.p;
             KB[(s + 2) % 3] = ldu(xk + pl * cz(k + 2), w.col);
-            const T r1 = bR[(s + 2) % 3], r2 = bB[(s + 1) % 3];  // red of plane k-1, black of plane k-2
-            double b1 = r1, b2 = r2;
+            double b1 = bR[(s + 2) % 3], b2 = bB[(s + 1) % 3];  // red of plane k-1, black of plane k-2
             bR[(s + 1) % 3] = ldu(bp[0] + pl * cz(k + 1), w.col);
             bB[s % 3] = ldu(bp[1] + pl * cz(k), w.col);
             czp[(s + 1) % 6] = uld(F.cp[2], cz(k + 1));
@@ -469,9 +469,8 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
                 const double dg = w.dxy[1 - q] + czp[m] + czm[m];
                 const double nb =
                     WALK_NB(1 - q, lr + 2 * WK_PS, B1[s % 3], B1[(s + 1) % 3], B1[(s + 2) % 3], czp[m], czm[m]);
-                double b3 = lagb[q][tid];
-                lagb[q][tid] = RAW ? r1 : (T)b1;
-                if (RAW && pn.k >= 0 && pn.c == 0 && cz(k - 3) == pn.k && w.col == pn.col) b3 -= pn.sink;
+                const double b3 = lagb[q][tid];
+                lagb[q][tid] = b1;
                 const T v = (T)quot(nb - b3, dg, rdR[s % 3]);
                 R2[s % 3] = (double)v;
                 lw[3 * WK_PS] = v;
@@ -482,9 +481,8 @@ __global__ void __launch_bounds__(WK_T) k_walk_up(Lv F, Lv C, PMap M, WalkGeo G,
                 const double dg = w.dxy[1 - q] + czp[m] + czm[m];
                 const double nb =
                     WALK_NB(1 - q, lr + 3 * WK_PS, R2[(s + 2) % 3], R2[s % 3], R2[(s + 1) % 3], czp[m], czm[m]);
-                double b4 = lagb[2 + q][tid];
-                lagb[2 + q][tid] = RAW ? r2 : (T)b2;
-                if (RAW && pn.k >= 0 && pn.c == 1 && cz(k - 4) == pn.k && w.col == pn.col) b4 -= pn.sink;
+                const double b4 = lagb[2 + q][tid];
+                lagb[2 + q][tid] = b2;
                 const T v = (T)quot(nb - b4, dg, rdB[(s + 2) % 3]);
                 if (w.own && k - 4 >= S.k0 && k - 4 < S.k1) stu_nt(x + F.Nh + pl * (k - 4), w.col, v);
             }
