@@ -13,12 +13,12 @@
 // also bytes.  At 512^3, with nothing beside it, the first phase takes 0.79 ms
 // and the second 0.80 (2.0 and 1.9 with one launch per half-sweep); per cell 69
 // and 79 vector instructions (the vector units issue in 0.39 and 0.45 of the
-// busy cycles), 2.06 and 3.58 GB from and to memory (1.18 and 1.27 of what they
-// cannot do without), 2.6 and 4.5 TB/s.  FP32 0.72 and 0.83 ms: 94 and 107
-// instructions (conversions), 0.61 and 0.58 of the cycles, 1.00 and 1.69 GB.
-// In a solve with bodies the near cells' launches (below) run beside the passes
-// from 2^23 cells on and take registers and bandwidth: 0.93 and 0.89 ms in FP64,
-// 0.73 and 0.77 in FP32.
+// busy cycles), 2.05 and 3.53 GB from and to memory (1.18 and 1.25 of what they
+// cannot do without), 2.6 and 4.4 TB/s.  FP32 0.68 and 0.77 ms: 91 and 105
+// instructions (conversions), 0.61 of the cycles, 1.01 and 1.68 GB.  In a solve
+// with bodies the near cells' launches (below) run beside the passes from 2^23
+// cells on and take registers and bandwidth: 0.92 and 0.88 ms in FP64; 0.73 and
+// 0.75 in FP32.
 //
 // The pass covers the whole level and treats every cell as a regular one.  Its
 // results are wrong near cells with a row of their own (solid, ghost,
